@@ -3,14 +3,20 @@
 //
 // Gate handling (paper, Appendix A: the chunkwise form divides by cumulative decays,
 // which overflows; GLA's remedy is a secondary chunking).  Here rows of a chunk are
-// grouped in blocks of 16 tokens, one wave per block.  For row block I the reference
-// is the cumulative log gate just before the block, Gref_I, and
-//     exp(G_t - G_r) = exp(G_t - Gref_I) * exp(Gref_I - G_r).
-// The first factor is <= 1.  The second is <= 1 for every earlier block and, inside
-// the diagonal block, bounded by the decay across 16 tokens.  If that decay exceeds
-// e^80 for some slot (alpha < 0.007 sustained over a block; not reachable with the
-// paper's sigmoid^(1/8) gates) the diagonal block is evaluated pair by pair with the
-// unfactored exponent instead.
+// grouped in blocks of 16 tokens, one wave per block, and every gate factor is relative
+// to a block's own start or end (see BlockGates).  Factors between different blocks are
+// all <= 1; inside the diagonal block one factor grows with the decay across 16 tokens.
+// If that decay exceeds e^80 for some slot (alpha < 0.007 sustained over a block; not
+// reachable with the paper's sigmoid^(1/8) gates) the diagonal block is evaluated pair by
+// pair with the unfactored exponent instead.
+//
+// Orientation: the per-token slot vectors (scores, read weights, their gradients) are kept
+// in matrix-core tiles D[slot][token]: lane l holds token l%16 of the wave's row block and
+// slots 16*ni + 4*(l/16) + j.  Three things follow.  Such a tile, rounded to the I/O type, IS
+// the operand of a contraction over the slots, and a tile D[r][t] of pair products IS the
+// operand of a contraction over r, so neither goes through LDS.  A sum over the slots of a
+// token is a sum over a lane's own registers and two shuffles.  And a cumulative sum over the
+// tokens of a block runs over 16 neighbouring lanes (DPP row shifts), with no barrier.
 #pragma once
 #include "gsa_common.h"
 
@@ -96,205 +102,339 @@ __device__ __forceinline__ void reduce_row_blocks(f32x4 (&own)[NB], const f32x4 
     }
 }
 
-// Write-intensity tiles of one chunk, referenced to the END of each token's own 16-token block:
-//   V[kk][i] = s_kk[i] * exp(G_end(kk)[i] - G_kk[i])  <= 1        (G_end = cumulative gate at the block's last token)
-// stored transposed, Vt[i][kk] (operand of contractions over tokens); plus the decay across each block,
-//   Rb[b][i] = exp(G_end(b)[i] - G_end(b-1)[i]).
-// With these, the weight between a token of row block w and an EARLIER block's token needs no
-// exponential of its own: exp(G_t - G_kk) = exp(G_t - G_start(w)) * prod of Rb over the blocks in
-// between * exp(G_end(kk) - G_kk), every factor <= 1 (nothing to clamp).  One (block, slot) pair
-// per thread and pass; no barrier inside.
-template <typename T, int M, int C>
-__device__ __forceinline__ void build_write_tiles(const float *Gs, const float *Ss, int ldg, T *Vt, int ldv, float *Rb,
-                                                  int tid)
+// ----------------------------------------------------------------------------
+// Row shifts inside the 16 lanes that share l/16 (DPP; lanes without a source read zero).
+// ----------------------------------------------------------------------------
+template <int CTRL> __device__ __forceinline__ float dpp_or_zero(float x)
 {
-    constexpr int CI = C / 16, NT = Geo<T>::NT;
-    for (int idx = tid; idx < CI * M; idx += NT) {
-        const int b = idx / M, i = idx - b * M;
-        const float gend = Gs[(16 * b + 15) * ldg + i];
-        const float gstart = b ? Gs[(16 * b - 1) * ldg + i] : 0.f;
-        Rb[b * M + i] = __expf(gend - gstart);
-        float x[16];
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const int kk = 16 * b + e;
-            x[e] = Ss[kk * ldg + i] * __expf(gend - Gs[kk * ldg + i]);
-        }
-        float lo[8], hi[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) { lo[e] = x[e]; hi[e] = x[8 + e]; }
-        store8<T>(Vt + i * ldv + 16 * b, lo);
-        store8<T>(Vt + i * ldv + 16 * b + 8, hi);
-    }
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float row16_prefix_sum(float x)   // inclusive, over lanes l%16 = 0 .. own
+{
+    x += dpp_or_zero<0x111>(x);   // row_shr:1, 2, 4, 8
+    x += dpp_or_zero<0x112>(x);
+    x += dpp_or_zero<0x114>(x);
+    x += dpp_or_zero<0x118>(x);
+    return x;
+}
+__device__ __forceinline__ float row16_last(float x) { return dpp_or_zero<0x15f>(x); }   // row_newbcast:15
+
+// Sum / maximum over the slots of a token: over the four lanes that share l%16, after the lane's own registers.
+__device__ __forceinline__ float slots_sum(float x)
+{
+    x += __shfl_xor(x, 16, 64);
+    return x + __shfl_xor(x, 32, 64);
+}
+__device__ __forceinline__ float slots_max(float x)
+{
+    x = fmaxf(x, __shfl_xor(x, 16, 64));
+    return fmaxf(x, __shfl_xor(x, 32, 64));
 }
 
-// For this wave's row block (rows t = rowb .. rowb+15), in D layout (lane holds slot
-// i = 16*ni + lane%16, rows t = rowb + 4*(lane/16) + j):
-//
-//   out[ni][j] = exp(G_t[i]) * <X_t, St[i]>  +  sum_{r<=t} <X_t, Y_r> s_r[i] exp(G_t[i]-G_r[i])
-//
-// i.e. the inter-chunk plus intra-chunk parts of one gated pass whose gate sits on the
-// slot side (pass 1 of Eq. (gsa-2pass) with X=q, Y=k, St=Kt; its mirror in the backward
-// with X=dO, Y=v, St=Vt).  X, Y: [len][d] rows in global memory (row stride ldx elements);
-// St: one part of a memory snapshot (M slots, d columns, tiled as StateLayout describes).
+// Softmax over the slots of every token of the block, in place (D[slot][token] tiles).
+template <int M> __device__ __forceinline__ void softmax_slots(f32x4 (&p)[M / 16])
+{
+    float mx = p[0][0], sum = 0.f;
+#pragma unroll
+    for (int ni = 0; ni < M / 16; ++ni)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) mx = fmaxf(mx, p[ni][j]);
+    mx = slots_max(mx);
+#pragma unroll
+    for (int ni = 0; ni < M / 16; ++ni)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { p[ni][j] = __expf(p[ni][j] - mx); sum += p[ni][j]; }
+    const float inv = 1.f / slots_sum(sum);
+#pragma unroll
+    for (int ni = 0; ni < M / 16; ++ni) p[ni] *= inv;
+}
+
+// D tile -> depth-16 operand of the same lane (rows 4*(l/16)+j become contraction indices).
+template <typename T> __device__ __forceinline__ typename Atom<T>::Frag16 to_frag16(const f32x4 &x)
+{
+    typename Atom<T>::Frag16 f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) f[j] = from_f32<T>(x[j]);
+    return f;
+}
+// What that rounding left behind, as a second operand: a contraction with both carries the tile to twice the
+// I/O type's precision (bf16; nothing is left behind in fp32, and the second product is not issued).
+template <typename T> __device__ __forceinline__ typename Atom<T>::Frag16 rest_frag16(const f32x4 &x, const typename Atom<T>::Frag16 &f)
+{
+    f32x4 y;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) y[j] = x[j] - to_f32(f[j]);
+    return to_frag16<T>(y);
+}
+template <typename T> __device__ __forceinline__ void store_frag16(T *p, const f32x4 &x)
+{
+    store4(p, x[0], x[1], x[2], x[3]);
+}
+
+// ----------------------------------------------------------------------------
+// Gates of one wave's row block (16 tokens, all slots), in D[slot][token] registers.
+//   L[ni][j]   = sum over the block's tokens up to and including t of g       (block-local, inclusive)
+//   tot[ni][j] = the same over the whole block (equal in the 16 lanes of a row)
+//   s[ni][j]   = write intensity, 0 on rows past the end of the chunk
+// What other waves need of them goes to LDS once (write_tiles): the write-intensity tile referenced to
+// the END of its block,
+//   V[r][i] = s_r[i] * exp(tot[i] - L_r[i])  <= 1,
+// in both orientations (Vn[token][slot], Vt[slot][token]), and the decay across the block Rb[b][i] =
+// exp(tot[i]).  The weight between a token t of block w and a token r of block b <= w is then
+//   exp(G_t - G_r) s_r = exp(L_t - tot_w) * (product of Rb over the blocks b+1 .. w) * V[r]
+// for the diagonal block as well: no operand of a gated contraction needs an exponential of its own, and
+// no exponential is evaluated twice.
+// ----------------------------------------------------------------------------
+template <int M, bool GEN> struct BlockGates {
+    static constexpr int MI = M / 16;
+    f32x4 L[MI], s[MI], tot[MI];
+    bool given = false;
+    float tau = 0.f;
+    // Issues the loads (rows clamped into the chunk); may be called well before finish().
+    __device__ __forceinline__ void load(const float *g, size_t gld, int len, int rowb, int lane, const float *sin,
+                                         float gate_tau)
+    {
+        const size_t off = (size_t)min(rowb + (lane & 15), len - 1) * gld + (lane >> 4) * 4;
+#pragma unroll
+        for (int ni = 0; ni < MI; ++ni) L[ni] = *reinterpret_cast<const f32x4 *>(g + off + ni * 16);
+        if (GEN) tau = gate_tau;
+        if (GEN && sin) {   // uniform over the grid
+            given = true;
+#pragma unroll
+            for (int ni = 0; ni < MI; ++ni) s[ni] = *reinterpret_cast<const f32x4 *>(sin + off + ni * 16);
+        }
+    }
+    // Returns whether the factored form is unsafe for this block (wave-uniform).
+    __device__ __forceinline__ bool finish(int len, int rowb, int lane)
+    {
+        const bool live = rowb + (lane & 15) < len;
+        float least = 0.f;
+#pragma unroll
+        for (int ni = 0; ni < MI; ++ni)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                float x = L[ni][j];
+                if (GEN && tau > 0.f) x = log_gate_from_logit(x, tau);
+                x = live ? fmaxf(x, kGateFloor) : 0.f;
+                const float sx = (GEN && given) ? s[ni][j] : write_intensity(x);
+                s[ni][j] = live ? sx : 0.f;
+                x = row16_prefix_sum(x);
+                L[ni][j] = x;
+                tot[ni][j] = row16_last(x);
+                least = fminf(least, tot[ni][j]);
+            }
+        return __any(least < -kExpClamp);
+    }
+    template <typename T>
+    __device__ __forceinline__ void write_tiles(T *Vn, int ldn, T *Vt, int ldt, float *Rb, int rowb, int lane) const
+    {
+        const int r = lane & 15, g4 = (lane >> 4) * 4;
+#pragma unroll
+        for (int ni = 0; ni < MI; ++ni) {
+            f32x4 v, e;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                v[j] = s[ni][j] * __expf(tot[ni][j] - L[ni][j]);
+                e[j] = __expf(tot[ni][j]);
+            }
+            if (Vn) store_frag16<T>(Vn + (rowb + r) * ldn + ni * 16 + g4, v);
+            if (Vt) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) Vt[(ni * 16 + g4 + j) * ldt + rowb + r] = from_f32<T>(v[j]);
+            }
+            if (r == 0) *reinterpret_cast<f32x4 *>(Rb + (rowb / 16) * M + ni * 16 + g4) = e;
+        }
+    }
+};
+
+// One gated pass whose gate sits on the slot side (pass 1 of Eq. (gsa-2pass) with X=q, Y=k, St=Kt; its
+// mirror in the backward with X=dO, Y=v, St=Vt), first part: the contractions over the head dimension.
+//   a[cb][.]  = D[r][t] tile of X_t . Y_r for this wave's row block t and the row blocks cb <= w of r,
+//               rounded to T and causally masked: an operand of contractions over r; alo[cb]: the rest
+//   run[ni]   = D[slot][t] tile of <X_t, St[slot]>
+// X, Y: [len][d] rows in global memory (row stride ldx elements); St: one part of a memory snapshot
+// (M slots, d columns, tiled as StateLayout describes).
 // The contraction over d reads its operand fragments straight from global memory (each lane 16
-// bytes of one row; no staging).  It is split over the waves in steps of 64 columns, wave w taking steps w, w+NW, ...: a wave asks for the two
-// halves of a 128-byte line in consecutive instructions, so each line crosses the
-// memory system once.  The partial sums meet through Red (see reduce_row_blocks; Red may
-// alias As).  d must be a multiple of 64.
-// The gate tiles Gs, Ss are produced in here as well (from g: [len][M] fp32, row stride gld;
-// `tot`: scratch of NT floats): the gate loads are issued after the contraction and land during
-// the reduction, and the tiles are written once the reduction buffer is dead, so Red may alias
-// Gs and Ss too.  As [C][lda] is left holding the causally masked X Y^T rounded to T, and the tiles
-// of build_write_tiles are left in Vt, Rb for the caller's own use.
-// All threads of the workgroup must call it.
-// GEN: general form; sin = write intensities [len][M] (layout of g) or NULL for 1 - exp(g).
+// bytes of one row; no staging).  It is split over the waves in steps of 64 columns, wave w taking steps
+// w, w+NW, ...: a wave asks for the two halves of a 128-byte line in consecutive instructions, so each line
+// crosses the memory system once.  The partial sums meet through Red (see reduce_row_blocks).  d must be a
+// multiple of 64.  The gate loads are issued after the contraction and land during the reduction.
+// All threads of the workgroup must call it; it ends with a barrier.
 // RPR: row blocks per round of the reduction (Red must hold reduce_fragments<..., RPR>() * NW * 64 f32x4).
 // HINT: which operands are loaded with the non-temporal hint (kHintX | kHintY | kHintSt) -- those the
 // caller knows nobody reads again soon.  Both halves of every 128-byte line are asked for by the
 // same wave in the same step, so a hinted line is never dropped between its two readers.
 constexpr int kHintX = 1, kHintY = 2, kHintSt = 4;
 // phi (general form only): which of X, Y get the feature map after the load (kHintX | kHintY bits).
-template <typename T, int M, int C, bool GEN = false, int RPR = 1, int HINT = 0>
-__device__ __forceinline__ void gated_scores(float (&out)[M / 16][4], bool &unsafe, float *Gs, float *Ss, int ldg,
-                                             float *tot, const float *g, size_t gld, T *As, int lda, T *Vt, int ldv,
-                                             float *Rb, f32x4 *Red, const T *X, const T *Y,
-                                             size_t ldx, int d, const T *St, int len, int tid,
-                                             const float *sin = nullptr, float gate_tau = 0.f, int phi = 0)
+template <typename T, int M, int C, bool GEN, int RPR, int HINT, typename Early>
+__device__ __forceinline__ void contract_heads(f32x4 (&run)[M / 16], typename Atom<T>::Frag16 (&a)[C / 16],
+                                               typename Atom<T>::Frag16 (&alo)[C / 16], f32x4 *Red,
+                                               const T *X, const T *Y, size_t ldx, int d, const T *St, int len,
+                                               int lane, int w, int phi, Early &&early_loads)
 {
     constexpr int MI = M / 16, CI = C / 16, NW = CI, NB = CI + MI;
-    const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 15, g4 = (lane >> 4) * 4, g8 = (lane >> 4) * 8;
-    const int rowb = 16 * w;
-
-    f32x4 accA[CI], accZ[MI];
-    {
-        f32x4 acc[NW][NB];   // [row block][Y blocks | St blocks]
+    f32x4 acc[NW][NB];   // [row block][Y blocks | St blocks]
 #pragma unroll
-        for (int rb = 0; rb < NW; ++rb)
+    for (int rb = 0; rb < NW; ++rb)
 #pragma unroll
-            for (int cb = 0; cb < NB; ++cb) acc[rb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
-        // Rows past the end of a ragged chunk are read as copies of its last row: they stay finite
-        // and only ever produce rows of the result that are not stored or that meet zero weights.
-        uint32_t xo[CI], so[MI];
+        for (int cb = 0; cb < NB; ++cb) acc[rb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // Rows past the end of a ragged chunk are read as copies of its last row: they stay finite
+    // and only ever produce rows of the result that are not stored or that meet zero weights.
+    uint32_t xo[CI], so[MI];
 #pragma unroll
-        for (int ni = 0; ni < CI; ++ni) xo[ni] = (uint32_t)min(ni * 16 + r, len - 1) * (uint32_t)ldx + g8;
+    for (int ni = 0; ni < CI; ++ni) xo[ni] = (uint32_t)min(ni * 16 + r, len - 1) * (uint32_t)ldx + g8;
 #pragma unroll
-        for (int ni = 0; ni < MI; ++ni) so[ni] = (uint32_t)(ni * 16 + r) * kSnapTile + g8;
-        typedef typename Atom<T>::Frag Frag;
-        // a wave takes 64 columns at a time: the two halves of every 128-byte line are asked for by the
-        // same wave in consecutive instructions
-        for (int kk = 64 * w; kk < d; kk += 64 * NW) {
-            Frag fx[2][CI], fy[2][CI], fs[2][MI];
+    for (int ni = 0; ni < MI; ++ni) so[ni] = (uint32_t)(ni * 16 + r) * kSnapTile + g8;
+    typedef typename Atom<T>::Frag Frag;
+    // a wave takes 64 columns at a time: the two halves of every 128-byte line are asked for by the
+    // same wave in consecutive instructions
+    for (int kk = 64 * w; kk < d; kk += 64 * NW) {
+        Frag fx[2][CI], fy[2][CI], fs[2][MI];
 #pragma unroll
-            for (int hh = 0; hh < 2; ++hh) {
-                const int k0 = kk + 32 * hh;
+        for (int hh = 0; hh < 2; ++hh) {
+            const int k0 = kk + 32 * hh;
 #pragma unroll
-                for (int ni = 0; ni < CI; ++ni) fx[hh][ni] = (HINT & kHintX) ? Atom<T>::load_nt(X + xo[ni] + k0) : Atom<T>::load(X + xo[ni] + k0);
-            }
+            for (int ni = 0; ni < CI; ++ni) fx[hh][ni] = (HINT & kHintX) ? Atom<T>::load_nt(X + xo[ni] + k0) : Atom<T>::load(X + xo[ni] + k0);
+        }
 #pragma unroll
-            for (int hh = 0; hh < 2; ++hh) {
-                const int k0 = kk + 32 * hh;
+        for (int hh = 0; hh < 2; ++hh) {
+            const int k0 = kk + 32 * hh;
 #pragma unroll
-                for (int ni = 0; ni < CI; ++ni) fy[hh][ni] = (HINT & kHintY) ? Atom<T>::load_nt(Y + xo[ni] + k0) : Atom<T>::load(Y + xo[ni] + k0);
-            }
+            for (int ni = 0; ni < CI; ++ni) fy[hh][ni] = (HINT & kHintY) ? Atom<T>::load_nt(Y + xo[ni] + k0) : Atom<T>::load(Y + xo[ni] + k0);
+        }
 #pragma unroll
-            for (int hh = 0; hh < 2; ++hh) {
-                const int k0 = kk + 32 * hh;
+        for (int hh = 0; hh < 2; ++hh) {
+            const int k0 = kk + 32 * hh;
 #pragma unroll
-                for (int ni = 0; ni < MI; ++ni) fs[hh][ni] = (HINT & kHintSt) ? Atom<T>::load_nt(St + so[ni] + snap_col<M>(k0)) : Atom<T>::load(St + so[ni] + snap_col<M>(k0));
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            if (GEN && phi) {
-#pragma unroll
-                for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-                    for (int ni = 0; ni < CI; ++ni) {
-                        if (phi & kHintX) swish_frag<T>(fx[hh][ni]);
-                        if (phi & kHintY) swish_frag<T>(fy[hh][ni]);
-                    }
-            }
+            for (int ni = 0; ni < MI; ++ni) fs[hh][ni] = (HINT & kHintSt) ? Atom<T>::load_nt(St + so[ni] + snap_col<M>(k0)) : Atom<T>::load(St + so[ni] + snap_col<M>(k0));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (GEN && phi) {
 #pragma unroll
             for (int hh = 0; hh < 2; ++hh)
 #pragma unroll
-                for (int rb = 0; rb < NW; ++rb) {
-#pragma unroll
-                    for (int cb = 0; cb <= rb; ++cb) Atom<T>::mma(acc[rb][cb], fx[hh][rb], fy[hh][cb]);
-#pragma unroll
-                    for (int ni = 0; ni < MI; ++ni) Atom<T>::mma(acc[rb][CI + ni], fx[hh][rb], fs[hh][ni]);
+                for (int ni = 0; ni < CI; ++ni) {
+                    if (phi & kHintX) swish_frag<T>(fx[hh][ni]);
+                    if (phi & kHintY) swish_frag<T>(fy[hh][ni]);
                 }
         }
-        GatePrep<M, Geo<T>::NT, C, GEN> gp;
-        gp.load(g, gld, len, tid, sin, gate_tau);
-        f32x4 own[NB];
-        reduce_row_blocks<NW, NB, CI, RPR>(own, acc, Red, lane, w);
 #pragma unroll
-        for (int ni = 0; ni < CI; ++ni) accA[ni] = own[ni];
+        for (int hh = 0; hh < 2; ++hh)
 #pragma unroll
-        for (int ni = 0; ni < MI; ++ni) accZ[ni] = own[CI + ni];
-        gp.finish(Gs, Ss, ldg, tot, len, tid);
-    }
-    // causally masked X Y^T, as an operand
+            for (int rb = 0; rb < NW; ++rb) {
 #pragma unroll
-    for (int ni = 0; ni < CI; ++ni)
+                for (int cb = 0; cb <= rb; ++cb) Atom<T>::mma(acc[rb][cb], fy[hh][cb], fx[hh][rb]);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int t = rowb + g4 + j, rr = ni * 16 + r;
-            As[t * lda + rr] = from_f32<T>((ni <= w && rr <= t) ? accA[ni][j] : 0.f);
-        }
-    build_write_tiles<T, M, C>(Gs, Ss, ldg, Vt, ldv, Rb, tid);
-    __syncthreads();
-    unsafe = block_unsafe<M>(Gs, ldg, rowb, lane);
-    // ---- earlier row blocks, through the end-referenced tile: `run` walks its reference from the chunk
-    // start (where it is the inter-chunk term) to the start of this wave's block, one block at a time
-    f32x4 run[MI];
-#pragma unroll
-    for (int ni = 0; ni < MI; ++ni) run[ni] = accZ[ni];
-    for (int bp = 0; bp < w; ++bp) {
-        const typename Atom<T>::Frag16 a = Atom<T>::load16(As + (rowb + r) * lda + bp * 16 + g4);
-#pragma unroll
-        for (int ni = 0; ni < MI; ++ni) {
-            const float dec = Rb[bp * M + ni * 16 + r];
-            run[ni] *= dec;
-            const typename Atom<T>::Frag16 bfr = Atom<T>::load16(Vt + (ni * 16 + r) * ldv + bp * 16 + g4);
-            Atom<T>::mma16(run[ni], a, bfr);
-        }
-    }
-    // ---- this wave's own block: operand generated here, referenced to the block's start
-    float gref[MI];
-#pragma unroll
-    for (int ni = 0; ni < MI; ++ni) gref[ni] = rowb ? Gs[(rowb - 1) * ldg + ni * 16 + r] : 0.f;
-    if (!unsafe) {
-        const typename Atom<T>::Frag16 a = Atom<T>::load16(As + (rowb + r) * lda + rowb + g4);
-#pragma unroll
-        for (int ni = 0; ni < MI; ++ni) {
-            const int i = ni * 16 + r;
-            typename Atom<T>::Frag16 bfr;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int kk = rowb + g4 + e;
-                bfr[e] = from_f32<T>(Ss[kk * ldg + i] * __expf(fminf(gref[ni] - Gs[kk * ldg + i], kExpClamp)));
+                for (int ni = 0; ni < MI; ++ni) Atom<T>::mma(acc[rb][CI + ni], fs[hh][ni], fx[hh][rb]);
             }
-            Atom<T>::mma16(run[ni], a, bfr);
+    }
+    early_loads();
+    f32x4 own[NB];
+    reduce_row_blocks<NW, NB, CI, RPR>(own, acc, Red, lane, w);
+#pragma unroll
+    for (int cb = 0; cb < CI; ++cb) {
+        f32x4 x = own[cb];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) x[j] = (cb < w || (cb == w && g4 + j <= r)) ? x[j] : 0.f;
+        a[cb] = to_frag16<T>(x);
+        alo[cb] = rest_frag16<T>(x, a[cb]);
+    }
+#pragma unroll
+    for (int ni = 0; ni < MI; ++ni) run[ni] = own[CI + ni];
+}
+
+// Second part: the gated sum itself, from the tiles of contract_heads and of BlockGates::write_tiles (which
+// must be visible to all waves):
+//   run[ni][j] <- exp(G_t[i]) * <X_t, St[i]>  +  sum_{r<=t} <X_t, Y_r> s_r[i] exp(G_t[i]-G_r[i])
+// `run` walks its reference from the chunk start (where it is the inter-chunk term) to the end of this
+// wave's block, one block at a time: run <- run * Rb[b] + V_b^T a_b.
+template <typename T, int M, int C, bool GEN>
+__device__ __forceinline__ void gated_rows(f32x4 (&run)[M / 16], const typename Atom<T>::Frag16 (&a)[C / 16],
+                                           const typename Atom<T>::Frag16 (&alo)[C / 16],
+                                           const BlockGates<M, GEN> &bg, bool unsafe, const T *Vt, int ldt,
+                                           const float *Rb, int lane, int w)
+{
+    constexpr int MI = M / 16, CI = C / 16;
+    const int r = lane & 15, g4 = (lane >> 4) * 4;
+    typename Atom<T>::Frag16 own = a[0];
+#pragma unroll
+    for (int b = 0; b < CI; ++b) {
+        if (b > w) continue;   // wave-uniform
+        own = a[b];
+        if (b == w && unsafe) continue;
+#pragma unroll
+        for (int ni = 0; ni < MI; ++ni) {
+            run[ni] *= *reinterpret_cast<const f32x4 *>(Rb + b * M + ni * 16 + g4);
+            const typename Atom<T>::Frag16 v = Atom<T>::load16(Vt + (ni * 16 + r) * ldt + b * 16 + g4);
+            Atom<T>::mma16(run[ni], v, a[b]);
+            if (sizeof(T) == 2) Atom<T>::mma16(run[ni], v, alo[b]);
         }
     }
+#pragma unroll
+    for (int ni = 0; ni < MI; ++ni)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) run[ni][j] *= __expf(unsafe ? bg.L[ni][j] : bg.L[ni][j] - bg.tot[ni][j]);
+    if (unsafe) {   // the diagonal block pair by pair
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const int rr = 4 * q + c;
+                const float av = __shfl(to_f32(own[c]), 16 * q + r, 64);   // zero for rr > t
+#pragma unroll
+                for (int ni = 0; ni < MI; ++ni)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const float Lr = __shfl(bg.L[ni][j], (lane & 48) | rr, 64), sr = __shfl(bg.s[ni][j], (lane & 48) | rr, 64);
+                        run[ni][j] += av * sr * __expf(fminf(bg.L[ni][j] - Lr, 0.f));
+                    }
+            }
+    }
+}
+
+// Pair weights of this wave's row block w against row block b <= w, with the slots contracted in registers:
+//   out[j] = sum_i wt[i] V[r][i],   D[r][t] (T_FIRST = false) or D[t][r] (T_FIRST = true)
+// wt: D[slot][t] tiles referenced to the END of block b.  Entries with r > t are returned as computed.
+template <typename T, int M, bool T_FIRST>
+__device__ __forceinline__ f32x4 pair_tile(const f32x4 (&wt)[M / 16], const T *Vn, int ldn, int b, int lane)
+{
+    constexpr int MI = M / 16;
+    const int r = lane & 15, g4 = (lane >> 4) * 4;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int ni = 0; ni < MI; ++ni) {
-        const int i = ni * 16 + r;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int t = rowb + g4 + j;
-            const float G = Gs[t * ldg + i];
-            float val = __expf(G - gref[ni]) * run[ni][j];
-            if (unsafe) {
-                float sum = 0.f;
-                for (int rr = rowb; rr <= t; ++rr)
-                    sum += to_f32(As[t * lda + rr]) * Ss[rr * ldg + i] * __expf(G - Gs[rr * ldg + i]);
-                val += sum;
-            }
-            out[ni][j] = val;
-        }
+        const typename Atom<T>::Frag16 v = Atom<T>::load16(Vn + (b * 16 + r) * ldn + ni * 16 + g4);
+        const typename Atom<T>::Frag16 p = to_frag16<T>(wt[ni]);
+        if (T_FIRST) Atom<T>::mma16(acc, p, v);
+        else Atom<T>::mma16(acc, v, p);
     }
+    return acc;
+}
+
+// The diagonal tile D[r][t] of the pair weights without factoring: sum_i wt[i] s_r[i] exp(L_t[i] - L_r[i]) for
+// r <= t, else 0.  wt: ungated D[slot][t] weights.
+template <int M, bool GEN>
+__device__ __forceinline__ f32x4 pair_tile_exact(const f32x4 (&wt)[M / 16], const BlockGates<M, GEN> &bg, int lane)
+{
+    constexpr int MI = M / 16;
+    const int r = lane & 15, g = lane >> 4;
+    f32x4 out = {0.f, 0.f, 0.f, 0.f};
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int rr = 4 * q + c;
+            float sum = 0.f;
+#pragma unroll
+            for (int ni = 0; ni < MI; ++ni)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const float Lr = __shfl(bg.L[ni][j], (lane & 48) | rr, 64), sr = __shfl(bg.s[ni][j], (lane & 48) | rr, 64);
+                    sum += wt[ni][j] * sr * __expf(fminf(bg.L[ni][j] - Lr, 0.f));
+                }
+            sum = slots_sum(sum);
+            if (q == g) out[c] = rr <= r ? sum : 0.f;
+        }
+    return out;
 }
 
 // Eight consecutive floats of an LDS row (16-byte aligned).

@@ -355,6 +355,23 @@ __device__ __forceinline__ float log_gate_from_logit(float u, float tau)
 }
 __device__ __forceinline__ float log_gate_slope(float u, float tau) { return 1.f / ((1.f + __expf(u)) * tau); }
 
+// Write intensity 1 - exp(x) of a log gate x in [kGateFloor, 0]: the Taylor series of expm1 to x^9 above -0.5 (its
+// remainder is below 1e-9 there), the plain difference below (at most 1 + exp(x) half units in the last place lost).
+// About 14 vector instructions; the library's expm1f is about 25.
+__device__ __forceinline__ float write_intensity(float x)
+{
+    float p = 1.f / 362880.f;
+    p = fmaf(p, x, 1.f / 40320.f);
+    p = fmaf(p, x, 1.f / 5040.f);
+    p = fmaf(p, x, 1.f / 720.f);
+    p = fmaf(p, x, 1.f / 120.f);
+    p = fmaf(p, x, 1.f / 24.f);
+    p = fmaf(p, x, 1.f / 6.f);
+    p = fmaf(p, x, 0.5f);
+    p = fmaf(p, x, 1.f);
+    return x > -0.5f ? -x * p : 1.f - __expf(x);
+}
+
 // GEN: the general form, in which the write intensity may come from an array of its own
 // (sin: [len][M] fp32, same layout as g; NULL = 1 - exp(g) as above), and the array g may hold gate
 // LOGITS u instead of log gates: with tau > 0 the log gate is logsigmoid(u) / tau, the layer's gate
@@ -395,7 +412,7 @@ template <int M, int NT, int C, bool GEN = false> struct GatePrep {
             const float x = (t < len) ? fmaxf(graw, kGateFloor) : 0.f;
             run += x;
             Gs[t * ldg + i] = run;
-            float sx = -expm1f(x);
+            float sx = write_intensity(x);
             if (GEN && given) sx = sv[GEN ? tt : 0];
             Ss[t * ldg + i] = (t < len) ? sx : 0.f;
         }

@@ -15,13 +15,6 @@
 //                     the pair weights A2 [C x C].  z and p never round-trip HBM except for
 //                     the z the backward needs.
 //   apply_kernel      (gsa_apply.hip) o = (p e^G) Vt_start + A2 V, the wide contraction.
-//
-// Gate handling inside a chunk: rows are grouped in blocks of 16 tokens.  For row block I
-// the reference is the cumulative log gate just before the block, Gref_I.  exp(G_t - G_r)
-// is factored as exp(G_t - Gref_I) * exp(Gref_I - G_r): the first factor is <= 1, the
-// second is <= 1 for every earlier block and bounded by the decay inside one 16-token
-// block on the diagonal.  If that bound exceeds e^80 (not reachable with the paper's gate
-// parameterisation) the diagonal block is evaluated pairwise without factoring.
 #include "gsa_chunk.h"
 #include "gsa_launch.h"
 
@@ -85,23 +78,21 @@ hipError_t launch_prepare(const Plan &pl, const Work &w, hipStream_t st)
 
 // ---------------------------------------------------------------------------------------
 // Chunk kernel of the forward: scores, softmax, pass-2 weights.
+//
+// After the contraction over the head dimension there is one barrier (the write-intensity tiles become
+// visible); everything behind it stays in the registers of the wave that owns the 16-token row block.
+// Measured against a form that kept gates, scores and weights as fp32 LDS tiles (eight barriers, 2,700 vector
+// instructions per wave): B=8, T=2048, H=4, m=64, bf16: d=512 66 -> 56 us, d=128 43 -> 31 us; one sequence of 2048
+// tokens, d=512: 21.6 -> 16.6 us; T=256, d=64, m=16, fp32: 9 -> 5.4 us.
 // ---------------------------------------------------------------------------------------
 template <typename T, int M> struct ChunkFwdLds {
     static constexpr int C = Geo<T>::C;
     static constexpr int PAD = Atom<T>::kPad;
-    static constexpr int KM = (M < 32) ? 32 : M;   // slots padded to the contraction depth
-    static constexpr int ldg = M + 4;
-    static constexpr int lda = C + PAD;            // As
-    static constexpr int ldp = KM + PAD;           // Ps
-    static constexpr size_t oG = 0;
-    static constexpr size_t oS = oG + sizeof(float) * C * ldg;
-    static constexpr size_t oA = oS + sizeof(float) * C * ldg;
-    static constexpr size_t oTot = oA;             // gate_prep's scratch, dead before As is written
-    static constexpr size_t szA = sizeof(T) * C * lda > sizeof(float) * Geo<T>::NT ? sizeof(T) * C * lda
-                                                                                  : sizeof(float) * Geo<T>::NT;
-    static constexpr size_t oP = oA + szA;
-    static constexpr size_t oVt = oP + sizeof(T) * C * ldp;           // Vt [M][lda]
-    static constexpr size_t oRb = oVt + sizeof(T) * M * lda;          // Rb [C/16][M] fp32
+    static constexpr int KM = (M < 32) ? 32 : M;   // slots padded to the contraction depth of the apply kernel
+    static constexpr int ldn = M + PAD, ldt = C + PAD;
+    static constexpr size_t oVn = 0;                                  // Vn [C][ldn]
+    static constexpr size_t oVt = oVn + sizeof(T) * C * ldn;          // Vt [M][ldt]
+    static constexpr size_t oRb = oVt + sizeof(T) * M * ldt;          // Rb [C/16][M] fp32
     static constexpr size_t end = oRb + sizeof(float) * (C / 16) * M;
     static constexpr int kRpr = 2;                 // row blocks per round of the reduction
     static constexpr size_t szRed = sizeof(f32x4) * kWave * (C / 16) *
@@ -122,143 +113,83 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_fwd_kernel
 {
     using L = ChunkFwdLds<T, M>;
     const int readout = opts & kReadoutMask;
-    constexpr int C = Geo<T>::C, NT = Geo<T>::NT;
+    constexpr int C = Geo<T>::C;
     constexpr int MI = M / 16, CI = C / 16, KM = L::KM;
     extern __shared__ __align__(16) unsigned char smem[];
-    float *Gs = reinterpret_cast<float *>(smem + L::oG);
-    float *Ss = reinterpret_cast<float *>(smem + L::oS);
-    float *tot = reinterpret_cast<float *>(smem + L::oTot);
-    T *As = reinterpret_cast<T *>(smem + L::oA);      // [C][lda]  A = QK^T masked, later A2
-    T *Ps = reinterpret_cast<T *>(smem + L::oP);      // [C][ldp]  softmax weights in their gated forms
+    T *Vn = reinterpret_cast<T *>(smem + L::oVn), *Vt = reinterpret_cast<T *>(smem + L::oVt);
+    float *Rb = reinterpret_cast<float *>(smem + L::oRb);
 
     ChunkInfo ci;
     int cid, h;
     chunk_order(cm, H, true, cid, h);   // the forward scan has just written the last chunks
     if (!chunk_lookup(cm, cid, ci)) return;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 15, g4 = (lane >> 4) * 4;
     const size_t tokh = (size_t)ci.tok0 * H + h;
     const size_t ch = (size_t)cid * H + h;
     const T *Kn = S + ch * lay.stride + lay.oK;      // key memory at chunk start (tiled)
-    const int rowb = 16 * w;                          // this wave's row block
+    const int rowb = 16 * w, t = rowb + r;            // this wave's row block, this lane's token
 
     // ---- pass 1: z = scale * (inter + gated intra), Eq. (gla-chunk) with the gate on the slot side
-    float p[MI][4];
-    bool unsafe;
-    T *Vt = reinterpret_cast<T *>(smem + L::oVt);
-    float *Rb = reinterpret_cast<float *>(smem + L::oRb);
+    f32x4 p[MI];
+    typename Atom<T>::Frag16 a[CI], alo[CI];
+    BlockGates<M, GEN> bg;
     // q, k and the key memory are not read again by this forward call: all three hinted
-    gated_scores<T, M, C, GEN, L::kRpr, kHintX | kHintY | kHintSt>(
-        p, unsafe, Gs, Ss, L::ldg, tot, g + tokh * M, (size_t)H * M, As, L::lda, Vt, L::lda, Rb,
-        reinterpret_cast<f32x4 *>(smem), q + tokh * d_k, k + tokh * d_k,
-        (size_t)H * d_k, d_k, Kn, ci.len, tid, (GEN && sin) ? sin + tokh * M : nullptr, gate_tau,
-        PHI ? (kHintX | kHintY) : 0);
+    contract_heads<T, M, C, GEN, L::kRpr, kHintX | kHintY | kHintSt>(
+        p, a, alo, reinterpret_cast<f32x4 *>(smem), q + tokh * d_k, k + tokh * d_k, (size_t)H * d_k, d_k, Kn, ci.len, lane, w,
+        PHI ? (kHintX | kHintY) : 0,
+        [&] { bg.load(g + tokh * M, (size_t)H * M, ci.len, rowb, lane, (GEN && sin) ? sin + tokh * M : nullptr, gate_tau); });
+    const bool unsafe = bg.finish(ci.len, rowb, lane);
+    bg.template write_tiles<T>(Vn, L::ldn, Vt, L::ldt, Rb, rowb, lane);
+    __syncthreads();
+    gated_rows<T, M, C, GEN>(p, a, alo, bg, unsafe, Vt, L::ldt, Rb, lane, w);
     // ---- softmax over the slots, in registers
-    float rmax[4], rsum[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) rmax[j] = -INFINITY;
+    for (int ni = 0; ni < MI; ++ni) p[ni] *= scale;
+    if (z_saved && t < ci.len) {
 #pragma unroll
-    for (int ni = 0; ni < MI; ++ni) {
-        const int i = ni * 16 + r;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int t = rowb + g4 + j;
-            const float z = scale * p[ni][j];
-            p[ni][j] = z;
-            rmax[j] = fmaxf(rmax[j], z);
-            if (z_saved && t < ci.len) z_saved[(tokh + (size_t)t * H) * M + i] = z;
-        }
+        for (int ni = 0; ni < MI; ++ni)
+            *reinterpret_cast<f32x4 *>(z_saved + (tokh + (size_t)t * H) * M + ni * 16 + g4) = p[ni];
     }
     if (!GEN || readout == kReadSoftmax) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) { rmax[j] = row16_max(rmax[j]); rsum[j] = 0.f; }
-#pragma unroll
-        for (int ni = 0; ni < MI; ++ni)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) { p[ni][j] = __expf(p[ni][j] - rmax[j]); rsum[j] += p[ni][j]; }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) rsum[j] = 1.f / row16_sum(rsum[j]);
-#pragma unroll
-        for (int ni = 0; ni < MI; ++ni)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) p[ni][j] *= rsum[j];
+        softmax_slots<M>(p);
     } else {   // element-wise read-out (ablations of Section 4)
 #pragma unroll
         for (int ni = 0; ni < MI; ++ni)
 #pragma unroll
             for (int j = 0; j < 4; ++j) p[ni][j] = readout_value(readout, p[ni][j]);
     }
-    if (M < KM) {   // zero the padded slot columns once
-#pragma unroll
-        for (int j = 0; j < 4; ++j) Ps[(rowb + g4 + j) * L::ldp + M + r] = from_f32<T>(0.f);
-    }
-    // ---- pass-2 pair weights A2[t][r] = sum_i p_t[i] s_r[i] exp(G_t[i] - G_r[i]), r <= t
+    // ---- pass-2 pair weights A2[t][r] = sum_i p_t[i] s_r[i] exp(G_t[i] - G_r[i]), r <= t: row t of this wave's
+    // block, one column block after the other, nearest first; `p` walks its reference backwards with them and
+    // ends as the inter-chunk weights p * exp(G)
+    T *dA = tA + ch * C * C + (size_t)t * C, *dP = tP + ch * C * KM + (size_t)t * KM;
     f32x4 exact = {0.f, 0.f, 0.f, 0.f};
-    if (__syncthreads_or(unsafe)) {   // rare: some row block needs its diagonal unfactored
+    if (unsafe) exact = pair_tile_exact<M, GEN>(p, bg, lane);
 #pragma unroll
-        for (int ni = 0; ni < MI; ++ni)
+    for (int ni = 0; ni < MI; ++ni)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) Ps[(rowb + g4 + j) * L::ldp + ni * 16 + r] = from_f32<T>(p[ni][j]);
-        __syncthreads();
-        if (unsafe) exact = pair_weights_exact<M, T>(Ps, L::ldp, Gs, Ss, L::ldg, lane, rowb);
-        __syncthreads();
-    }
+        for (int j = 0; j < 4; ++j) p[ni][j] *= __expf(unsafe ? bg.L[ni][j] : bg.L[ni][j] - bg.tot[ni][j]);
 #pragma unroll
-    for (int ni = 0; ni < MI; ++ni) {
-        const int i = ni * 16 + r;
-        const float gref = rowb ? Gs[(rowb - 1) * L::ldg + i] : 0.f;
+    for (int b = CI - 1; b >= 0; --b) {
+        f32x4 x = {0.f, 0.f, 0.f, 0.f};
+        if (b <= w) {   // wave-uniform
+            if (b == w && unsafe) {
+                x = exact;   // p is already at the start of the block
+            } else {
+                x = pair_tile<T, M, false>(p, Vn, L::ldn, b, lane);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int t = rowb + g4 + j;
-            Ps[t * L::ldp + i] = from_f32<T>(p[ni][j] * __expf(Gs[t * L::ldg + i] - gref));
-        }
-    }
-    __syncthreads();
-    {
-        f32x4 acc2[CI];
-        pair_weights<T, M, C, KM>(acc2, Ps, L::ldp, Gs, Ss, L::ldg, unsafe, lane, w);
-        if (unsafe) {
+                for (int ni = 0; ni < MI; ++ni) p[ni] *= *reinterpret_cast<const f32x4 *>(Rb + b * M + ni * 16 + g4);
+            }
+            if (b == w) {
 #pragma unroll
-            for (int ni = 0; ni < CI; ++ni)
-                if (ni == w) acc2[ni] = exact;
-        }
-#pragma unroll
-        for (int ni = 0; ni < CI; ++ni) {
-            if (ni > w) continue;   // those columns already hold zeros from the masked A
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int t = rowb + g4 + j, rr = ni * 16 + r;
-                As[t * L::lda + rr] = from_f32<T>(rr <= t ? acc2[ni][j] : 0.f);
+                for (int j = 0; j < 4; ++j) x[j] = g4 + j <= r ? x[j] : 0.f;
             }
         }
+        store_frag16<T>(dA + b * 16 + g4, x);
     }
-    // inter-chunk pass-2 weights p * exp(G) (this wave's rows of Ps were read by this wave only)
 #pragma unroll
-    for (int ni = 0; ni < MI; ++ni) {
-        const int i = ni * 16 + r;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int t = rowb + g4 + j;
-            Ps[t * L::ldp + i] = from_f32<T>(p[ni][j] * __expf(Gs[t * L::ldg + i]));
-        }
-    }
-    __syncthreads();
-    // ---- hand the two small matrices to the apply kernel
-    {
-        T *dA = tA + ch * C * C, *dP = tP + ch * C * KM;
-        for (int idx = tid; idx < C * C / 8; idx += NT) {
-            const int t = idx / (C / 8), c8 = (idx - t * (C / 8)) * 8;
-            Raw8<T> x;
-            x.load(As + t * L::lda + c8);
-            x.store(dA + t * C + c8);
-        }
-        for (int idx = tid; idx < C * KM / 8; idx += NT) {
-            const int t = idx / (KM / 8), c8 = (idx - t * (KM / 8)) * 8;
-            Raw8<T> x;
-            x.load(Ps + t * L::ldp + c8);
-            x.store(dP + t * KM + c8);
-        }
-    }
+    for (int ni = 0; ni < MI; ++ni) store_frag16<T>(dP + ni * 16 + g4, p[ni]);
+    if (M < KM) store_frag16<T>(dP + M + g4, f32x4{0.f, 0.f, 0.f, 0.f});   // the padded slot columns
 }
 
 // ---------------------------------------------------------------------------------------
