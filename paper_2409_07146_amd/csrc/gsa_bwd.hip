@@ -41,8 +41,9 @@ template <typename T, int M> struct DzLds {
     static constexpr int ldt = C + PAD, ldx = 16 + PAD;
     static constexpr size_t oVt = 0;                                  // Vt [M][ldt]
     static constexpr size_t oRb = oVt + sizeof(T) * M * ldt;          // Rb [C/16][M] fp32
-    static constexpr size_t oX = oRb + sizeof(float) * (C / 16) * M;  // per wave: [2M + C][ldx], transposing scratch
-    static constexpr size_t szX = sizeof(T) * (2 * M + C) * ldx;
+    static constexpr size_t oX = oRb + sizeof(float) * (C / 16) * M;  // per wave: [kRows][ldx], transposing scratch
+    static constexpr int kRows = 2 * M + (sizeof(T) == 2 ? 2 : 1) * C;   // the products' roundings leave a rest in bf16
+    static constexpr size_t szX = sizeof(T) * kRows * ldx;
     static constexpr size_t end = oX + szX * (C / 16);
     static constexpr int kRpr = 2;                 // row blocks per round of the reduction
     static constexpr size_t szRed = sizeof(f32x4) * kWave * (C / 16) *
@@ -58,7 +59,7 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_dz_kernel(
                                                               const float *__restrict__ g, const float *__restrict__ z,
                                                               const T *__restrict__ S, StateLayout lay,
                                                               float *__restrict__ dz, float *__restrict__ dgf,
-                                                              T *__restrict__ Wr, T *__restrict__ tAvT,
+                                                              T *__restrict__ Wr, T *__restrict__ tAvT, T *__restrict__ tAvLo,
                                                               const float *__restrict__ sin, int opts,
                                                               float gate_tau)
 {
@@ -105,13 +106,14 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_dz_kernel(
 #pragma unroll
         for (int ni = 0; ni < MI; ++ni) p[ni] = zv[ni];
         softmax_slots<M>(p);
+        f32x4 sum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ni = 0; ni < MI; ++ni) {
             slope[ni] = p[ni];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) pdp += p[ni][j] * dp[ni][j];
+            for (int j = 0; j < 4; ++j) sum[j] += p[ni][j] * dp[ni][j];
         }
-        pdp = slots_sum(pdp);
+        pdp = slots_sum((sum[0] + sum[1]) + (sum[2] + sum[3]));
     } else {
 #pragma unroll
         for (int ni = 0; ni < MI; ++ni)
@@ -150,15 +152,20 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_dz_kernel(
 #pragma unroll
     for (int b = 0; b < CI; ++b)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) X[(2 * M + b * 16 + g4 + j) * L::ldx + r] = a[b][j];
+        for (int j = 0; j < 4; ++j) {
+            X[(2 * M + b * 16 + g4 + j) * L::ldx + r] = a[b][j];
+            // dp carries what the rounding of the products left behind; ds has to as well, so that the errors of the two
+            // cancel in dg (bf16, rel-L2 from the fp64 recurrence: 3.1e-3 where only one does)
+            if (sizeof(T) == 2) X[(2 * M + C + b * 16 + g4 + j) * L::ldx + r] = alo[b][j];
+        }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    T *dW = Wr + ch * 2 * M * C + rowb, *dAv = tAvT + ch * C * C + rowb;
+    T *dW = Wr + ch * 2 * M * C + rowb, *dAv = tAvT + ch * C * C + rowb, *dLo = tAvLo + ch * C * C + rowb;
 #pragma unroll
-    for (int u = 0; u < 2 * (2 * M + C) / kWave; ++u) {
+    for (int u = 0; u < 2 * L::kRows / kWave; ++u) {
         const int idx = lane + u * kWave, rr = idx >> 1, c8 = (idx & 1) * 8;
         Raw8<T> x;
         x.load(X + rr * L::ldx + c8);
-        x.store((rr < 2 * M ? dW + (size_t)rr * C : dAv + (size_t)(rr - 2 * M) * C) + c8);
+        x.store((rr < 2 * M ? dW + (size_t)rr * C : rr < 2 * M + C ? dAv + (size_t)(rr - 2 * M) * C : dLo + (size_t)(rr - 2 * M - C) * C) + c8);
     }
 }
 
@@ -178,19 +185,16 @@ template <typename T, int M> struct IntraLds {
     static constexpr int C = Geo<T>::C;
     static constexpr int PAD = Atom<T>::kPad;
     static constexpr int KM = (M < 32) ? 32 : M;
-    static constexpr int ldg = M + 4, lda = C + PAD;
-    static constexpr size_t oG = 0;
-    static constexpr size_t oS = oG + sizeof(float) * C * ldg;
-    static constexpr size_t oPf = oS + sizeof(float) * C * ldg;
-    static constexpr size_t oDf = oPf + sizeof(float) * C * ldg;
-    static constexpr size_t oAT = oDf + sizeof(float) * C * ldg;
-    static constexpr size_t oTot = oAT;   // gate_prep's and the suffix sum's scratch (ATs is dead by then)
-    static constexpr size_t szAT = sizeof(T) * C * lda > sizeof(float) * Geo<T>::NT ? sizeof(T) * C * lda
-                                                                                   : sizeof(float) * Geo<T>::NT;
+    static constexpr int ldn = M + PAD, ldt = C + PAD;
+    static constexpr size_t oVn = 0;                                  // Vn [C][ldn]
+    static constexpr size_t oUd = oVn + sizeof(T) * C * ldn;          // Ud [M][ldt]
+    static constexpr size_t oUp = oUd + sizeof(T) * M * ldt;          // Up [M][ldt]
+    static constexpr size_t oRb = oUp + sizeof(T) * M * ldt;          // Rb, Rd, Rr, dGam totals: [C/16][M] fp32 each
+    static constexpr size_t end = oRb + 4 * sizeof(float) * (C / 16) * M;
     static constexpr int kRpr = 2;        // row blocks per round of the reduction
     static constexpr size_t szRed = sizeof(f32x4) * kWave * (C / 16) *
-                                    reduce_fragments<C / 16, C / 16 + M / 16, C / 16, kRpr>();   // from offset 0: every tile is written after it
-    static constexpr size_t oCarry = (oAT + szAT > szRed) ? oAT + szAT : szRed;
+                                    reduce_fragments<C / 16, C / 16 + M / 16, C / 16, kRpr, true>();   // from offset 0: dead before the tiles are written
+    static constexpr size_t oCarry = end > szRed ? end : szRed;
     static constexpr size_t bytes = oCarry + sizeof(float) * (C / 16) * M;   // per-wave partial carries
 };
 
@@ -199,7 +203,7 @@ template <typename T> struct IntraArgs {
     const float *g, *z, *dz, *dgf;
     const T *S, *SF, *E;
     StateLayout lay;
-    const T *tAvT;
+    const T *tAvT, *tAvLo;   // bf16: product and rest
     float *dg;
     T *tB, *tBT, *tA2T, *tDZe, *tSbe;
     const float *sin;   // general form: write intensities, or NULL
@@ -213,17 +217,13 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
                                                                  IntraArgs<T> a)
 {
     using L = IntraLds<T, M>;
-    constexpr int C = Geo<T>::C, NT = Geo<T>::NT, NW = Geo<T>::NW;
+    constexpr int C = Geo<T>::C, NW = Geo<T>::NW;
     constexpr int MI = M / 16, CI = C / 16, KM = L::KM;
     constexpr int NB = CI + MI;
     extern __shared__ __align__(16) unsigned char smem[];
-    float *Gs = reinterpret_cast<float *>(smem + L::oG);
-    float *Ss = reinterpret_cast<float *>(smem + L::oS);
-    float *Pf = reinterpret_cast<float *>(smem + L::oPf);    // p, later exp(g)*ds
-    float *Df = reinterpret_cast<float *>(smem + L::oDf);    // dz, later dGam
-    float *tot = reinterpret_cast<float *>(smem + L::oTot);
+    T *Vn = reinterpret_cast<T *>(smem + L::oVn), *Ud = reinterpret_cast<T *>(smem + L::oUd), *Up = reinterpret_cast<T *>(smem + L::oUp);
+    float *Rb = reinterpret_cast<float *>(smem + L::oRb), *Rd = Rb + CI * M, *Rr = Rd + CI * M, *Tot = Rr + CI * M;
     float *carry = reinterpret_cast<float *>(smem + L::oCarry);   // [NW][M]
-    T *ATs = reinterpret_cast<T *>(smem + L::oAT);           // [r][t] (q_t . k_r) for t >= r; later Bm [t][r]
 
     ChunkInfo ci;
     int cid, h;
@@ -252,15 +252,19 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
 
     // ---- phase 1: contractions over the head dimension, operands straight from global memory
     //   A[t][r] = q_t . k_r (r <= t),  X[r][i] = <E[i], [k_r | v_r]>,  carry[i] = <E[i], S_end[i]>
-    // Split over the waves in steps of 64 columns (see gated_scores): every wave covers all row
-    // blocks over its share of the columns, the partial sums meet in LDS.
-    f32x4 accA[CI], accX[MI];
-    GatePrep<M, NT, C, GEN> gp;
-    SoftmaxRows<M, C> sr;
+    // Split over the waves in steps of 64 columns (see contract_heads): every wave covers all row
+    // blocks over its share of the columns, the partial sums meet in LDS.  Wave w keeps the tiles of its
+    // own tokens as r: A as D[t][r] for the row blocks of t from w on, X as D[slot][r].
+    const int t = rowb + r;                                  // this lane's token
+    const bool live = t < ci.len;
+    const size_t row = (tokh + (size_t)min(t, ci.len - 1) * H) * M + g4;   // clamped; nothing is stored past len
+    f32x4 ds[MI], p[MI], wd[MI];                             // X, later ds; z, later p; dz, later scale*dz
+    typename Atom<T>::Frag16 fa[CI], fav[CI], favlo[CI];                // (q_t . k_r) and (dO_t . v_r), masked: operands of contractions over t
+    BlockGates<M, GEN> bg;
     const bool given = GEN && a.sin != nullptr;   // write intensities are an input of their own
     {
         typedef typename Atom<T>::Frag Frag;
-        f32x4 acc[NW][NB];   // [row block][k blocks (causal) | slot blocks]
+        f32x4 acc[NW][NB];   // [row block of r][row blocks of t (causal) | slot blocks]
 #pragma unroll
         for (int rb = 0; rb < NW; ++rb)
 #pragma unroll
@@ -297,7 +301,7 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
             for (int hh = 0; hh < 2; ++hh)
 #pragma unroll
                 for (int ni = 0; ni < CI; ++ni) fk[hh][ni] = Atom<T>::load(kb + tk[ni] + kk + 32 * hh);
-            __builtin_amdgcn_sched_barrier(0);   // all loads of the step before its multiplies (see gated_scores)
+            __builtin_amdgcn_sched_barrier(0);   // all loads of the step before its multiplies (see contract_heads)
             if (PHI) {
 #pragma unroll
                 for (int hh = 0; hh < 2; ++hh)
@@ -309,7 +313,7 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
 #pragma unroll
                 for (int rb = 0; rb < NW; ++rb)
 #pragma unroll
-                    for (int cb = 0; cb <= rb; ++cb) Atom<T>::mma(acc[rb][cb], fq[hh][rb], fk[hh][cb]);
+                    for (int cb = rb; cb < CI; ++cb) Atom<T>::mma(acc[rb][cb], fq[hh][cb], fk[hh][rb]);
         }
         for (int kk = 64 * w; kk < d_k; kk += 64 * NW) {
             Frag fk[2][CI], fe[2][MI], fs[2][MI];
@@ -337,13 +341,13 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
 #pragma unroll
                 for (int rb = 0; rb < NW; ++rb)
 #pragma unroll
-                    for (int ni = 0; ni < MI; ++ni) Atom<T>::mma(acc[rb][CI + ni], fk[hh][rb], fe[hh][ni]);
+                    for (int ni = 0; ni < MI; ++ni) Atom<T>::mma(acc[rb][CI + ni], fe[hh][ni], fk[hh][rb]);
 #pragma unroll
                 for (int ni = 0; ni < MI; ++ni) cpart[ni] += frag_dot<T>(fe[hh][ni], fs[hh][ni]);
             }
         }
         // value half: X += V E_v^T
-        // (64 columns per wave and step here, as in gated_scores: the registers allow it in this half)
+        // (64 columns per wave and step here, as in contract_heads: the registers allow it in this half)
         for (int kk = 64 * w; kk < d_v; kk += 64 * NW) {
             Frag fv[2][CI], fe[2][MI], fs[2][MI];
 #pragma unroll
@@ -370,7 +374,7 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
 #pragma unroll
                 for (int rb = 0; rb < NW; ++rb)
 #pragma unroll
-                    for (int ni = 0; ni < MI; ++ni) Atom<T>::mma(acc[rb][CI + ni], fv[hh][rb], fe[hh][ni]);
+                    for (int ni = 0; ni < MI; ++ni) Atom<T>::mma(acc[rb][CI + ni], fe[hh][ni], fv[hh][rb]);
 #pragma unroll
                 for (int ni = 0; ni < MI; ++ni) cpart[ni] += frag_dot<T>(fe[hh][ni], fs[hh][ni]);
             }
@@ -383,216 +387,208 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
             if (lane < 16) carry[w * M + ni * 16 + lane] = x;   // read after the barriers of the reduction
         }
         // the loads of everything phase 2 needs from global memory land during the reduction
-        gp.load(a.g + tokh * M, (size_t)H * M, ci.len, tid, given ? a.sin + tokh * M : nullptr, GEN ? a.gate_tau : 0.f);
-        sr.load(a.z + tokh * M, a.dz + tokh * M, (size_t)H * M, ci.len, tid);
-        f32x4 own[NB];
-        reduce_row_blocks<NW, NB, CI, L::kRpr>(own, acc, reinterpret_cast<f32x4 *>(smem), lane, w);
-#pragma unroll
-        for (int ni = 0; ni < CI; ++ni) accA[ni] = own[ni];
-#pragma unroll
-        for (int ni = 0; ni < MI; ++ni) accX[ni] = own[CI + ni];
-    }
-    // gate tiles; p and dz tiles (they overwrite the reduction buffer, which every wave has left by now)
-    gp.finish(Gs, Ss, L::ldg, tot, ci.len, tid);
-    if (!GEN || a.readout == kReadSoftmax) sr.finish(Pf, Df, L::ldg, ci.len, tid);
-    else sr.finish_elementwise(a.readout, Pf, Df, L::ldg, ci.len, tid);
-    // ---- phase 2a: transposed masked A into LDS; the slot-side operand tiles of the apply kernel
-#pragma unroll
-    for (int ni = 0; ni < CI; ++ni)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int t = rowb + g4 + j, rr = ni * 16 + r;
-            ATs[rr * L::lda + t] = from_f32<T>((ni <= w && rr <= t) ? accA[ni][j] : 0.f);
-        }
-    __syncthreads();   // Pf, Df, ATs visible to every wave
-    {
-        T *dD = a.tDZe + ch * C * KM, *dS = a.tSbe + ch * C * KM;
-        for (int idx = tid; idx < C * KM / 8; idx += NT) {
-            const int t = idx / (KM / 8), i8 = (idx - t * (KM / 8)) * 8;
-            float x[8], y[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int i = i8 + e;
-                x[e] = y[e] = 0.f;
-                if (i < M) {
-                    const float G = Gs[t * L::ldg + i];
-                    x[e] = scale * Df[t * L::ldg + i] * __expf(G);
-                    y[e] = Ss[t * L::ldg + i] * __expf(Gs[(C - 1) * L::ldg + i] - G);
-                }
-            }
-            store8<T>(dD + t * KM + i8, x);
-            store8<T>(dS + t * KM + i8, y);
-        }
-    }
-    const bool unsafe = block_unsafe<M>(Gs, L::ldg, rowb, lane);
-    // ---- phase 2b: write-intensity gradient ds for rows r of block w, then dGam and exp(g)*ds
-    float dGam[MI][4], ads[MI][4];
-    {
-        f32x4 accW[MI];
-#pragma unroll
-        for (int ni = 0; ni < MI; ++ni) accW[ni] = f32x4{0.f, 0.f, 0.f, 0.f};
-        const int tstart = unsafe ? rowb + 16 : rowb;
-        float gend[MI];
-#pragma unroll
-        for (int ni = 0; ni < MI; ++ni) gend[ni] = Gs[(rowb + 15) * L::ldg + ni * 16 + r];
-        // LDS reads are unconditional (every token of the tile exists); masking is a register select
-        for (int k0 = (tstart & ~31); k0 < C; k0 += 32) {
-            const typename Atom<T>::Frag aA = Atom<T>::load(ATs + (rowb + r) * L::lda + k0 + g8);
-            const typename Atom<T>::Frag aAv = Atom<T>::load(AvT + (rowb + r) * C + k0 + g8);
-#pragma unroll
-            for (int ni = 0; ni < MI; ++ni) {
-                const int i = ni * 16 + r;
-                float gv[8], dv[8], pv[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const int t = k0 + g8 + e;
-                    gv[e] = Gs[t * L::ldg + i];
-                    dv[e] = Df[t * L::ldg + i];
-                    pv[e] = Pf[t * L::ldg + i];
-                }
-                typename Atom<T>::Frag bdz, bp;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const bool on = k0 + g8 + e >= tstart;
-                    const float f = __expf(fminf(gv[e] - gend[ni], kExpClamp));
-                    bdz[e] = from_f32<T>(on ? scale * dv[e] * f : 0.f);
-                    bp[e] = from_f32<T>(on ? pv[e] * f : 0.f);
-                }
-                Atom<T>::mma(accW[ni], aA, bdz);
-                Atom<T>::mma(accW[ni], aAv, bp);
-            }
-        }
+        bg.load(a.g + tokh * M, (size_t)H * M, ci.len, rowb, lane, given ? a.sin + tokh * M : nullptr, GEN ? a.gate_tau : 0.f);
 #pragma unroll
         for (int ni = 0; ni < MI; ++ni) {
-            const int i = ni * 16 + r;
-            const float gend = Gs[(rowb + 15) * L::ldg + i], GC = Gs[(C - 1) * L::ldg + i];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int rr = rowb + g4 + j;
-                const float Gr = Gs[rr * L::ldg + i];
-                float ds = __expf(GC - Gr) * accX[ni][j] + __expf(gend - Gr) * accW[ni][j];
-                if (unsafe) {
-                    float sum = 0.f;
-                    for (int t = rr; t < rowb + 16; ++t)
-                        sum += (to_f32(ATs[rr * L::lda + t]) * scale * Df[t * L::ldg + i] +
-                                to_f32(AvT[rr * C + t]) * Pf[t * L::ldg + i]) *
-                               __expf(Gs[t * L::ldg + i] - Gr);
-                    ds += sum;
-                }
-                const float sv = Ss[rr * L::ldg + i];
-                const float fl = a.dgf[(tokh + (size_t)min(rr, ci.len - 1) * H) * M + i];
-                const float f = (rr < ci.len) ? fl : 0.f;
-                dGam[ni][j] = f - sv * ds;
-                ads[ni][j] = given ? ds : (1.f - sv) * ds;   // tied: d(1 - e^g)/dg = -e^g = -(1 - s)
-            }
+            p[ni] = *reinterpret_cast<const f32x4 *>(a.z + row + ni * 16);
+            wd[ni] = *reinterpret_cast<const f32x4 *>(a.dz + row + ni * 16);
         }
+#pragma unroll
+        for (int b = 0; b < CI; ++b) {
+            const size_t off = (size_t)t * C + max(b, w) * 16 + g4;
+            fav[b] = Atom<T>::load16(AvT + off);
+            if (sizeof(T) == 2) favlo[b] = Atom<T>::load16(a.tAvLo + ch * C * C + off);
+        }
+        f32x4 own[NB];
+        reduce_row_blocks<NW, NB, CI, L::kRpr, true>(own, acc, reinterpret_cast<f32x4 *>(smem), lane, w);
+#pragma unroll
+        for (int b = 0; b < CI; ++b) {
+            f32x4 x = own[b];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) x[j] = (b > w || (b == w && g4 + j >= r)) ? x[j] : 0.f;
+            fa[b] = to_frag16<T>(x);
+        }
+#pragma unroll
+        for (int ni = 0; ni < MI; ++ni) ds[ni] = own[CI + ni];
     }
-    // ---- phase 2c: Bm and A2 for row block w
-    f32x4 accB[CI], acc2[CI];
-    {
+    f32x4 dgl[MI];   // z*dz + p*dp of this lane's token
 #pragma unroll
-        for (int ni = 0; ni < CI; ++ni) { accB[ni] = f32x4{0.f, 0.f, 0.f, 0.f}; acc2[ni] = f32x4{0.f, 0.f, 0.f, 0.f}; }
-        for (int k0 = 0; k0 < KM; k0 += 32) {
-            const SlotSpan<M, KM> sp(k0 + g8);
-            float gref[8];
-            gate_ref8(gref, Gs, L::ldg, rowb, sp.i0);
-            typename Atom<T>::Frag adz, ap;
-            {
-                float gv[8], dv[8], pv[8];
-                lds_row8(gv, Gs + (rowb + r) * L::ldg + sp.i0);
-                lds_row8(dv, Df + (rowb + r) * L::ldg + sp.i0);
-                lds_row8(pv, Pf + (rowb + r) * L::ldg + sp.i0);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const float f = __expf(gv[e] - gref[e]);
-                    adz[e] = from_f32<T>(sp.live ? dv[e] * f : 0.f);
-                    ap[e] = from_f32<T>(sp.live ? pv[e] * f : 0.f);
-                }
-            }
-#pragma unroll
-            for (int ni = 0; ni < CI; ++ni) {
-                if (ni > w || (unsafe && ni == w)) continue;   // wave-uniform
-                const typename Atom<T>::Frag b = write_frag<T>(Gs, Ss, L::ldg, ni * 16 + r, sp.i0, sp.live, gref);
-                Atom<T>::mma(accB[ni], adz, b);
-                Atom<T>::mma(acc2[ni], ap, b);
-            }
-        }
-        if (unsafe) {
-            const f32x4 eb = pair_weights_exact<M, float>(Df, L::ldg, Gs, Ss, L::ldg, lane, rowb);
-            const f32x4 e2 = pair_weights_exact<M, float>(Pf, L::ldg, Gs, Ss, L::ldg, lane, rowb);
-#pragma unroll
-            for (int ni = 0; ni < CI; ++ni)
-                if (ni == w) { accB[ni] = eb; acc2[ni] = e2; }
-        }
-    }
-    __syncthreads();   // every wave is done reading p, dz and the transposed A
-    {
-        T *dBT = a.tBT + ch * C * C, *dA2T = a.tA2T + ch * C * C;
-#pragma unroll
-        for (int ni = 0; ni < CI; ++ni) {
-            const int rr = ni * 16 + r;
-            float bv[4], av[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int t = rowb + g4 + j;
-                const bool keep = (ni <= w) && (rr <= t);
-                bv[j] = keep ? scale * accB[ni][j] : 0.f;
-                av[j] = keep ? acc2[ni][j] : 0.f;
-                ATs[t * L::lda + rr] = from_f32<T>(bv[j]);     // Bm in natural orientation, staged for a row-wise copy
-            }
-            store4(dBT + rr * C + rowb + g4, bv[0], bv[1], bv[2], bv[3]);
-            store4(dA2T + rr * C + rowb + g4, av[0], av[1], av[2], av[3]);
-        }
+    for (int ni = 0; ni < MI; ++ni) dgl[ni] = *reinterpret_cast<const f32x4 *>(a.dgf + row + ni * 16);
+    // ---- phase 2 (register tiles and one barrier in place of fp32 LDS tiles and seven: with m = 128, H = 4, d = 512, 4 x 1000
+    // tokens 84 -> 72 us; with m = 64 the launch is bound by its loads): gates, p and scale*dz in D[slot][token] tiles of this wave's block.  What the other waves
+    // need goes to LDS (it overwrites the reduction buffer, which every wave has left by now): the
+    // write-intensity tile Vn for the pair weights, and the tiles U = (scale*dz | p) * exp(L_t - ref) for ds.
+    // ref lies halfway down the block's decay, so that neither U nor exp(ref - L_r) leaves fp32's range by
+    // more than e^40; a block too wide for that is referenced to its start, which serves the earlier blocks,
+    // and its own pairs are evaluated one by one.
+    const bool unsafe = bg.finish(ci.len, rowb, lane);
+    bg.template write_tiles<T>(Vn, L::ldn, nullptr, 0, Rb, rowb, lane);
+    if (!GEN || a.readout == kReadSoftmax) {
+        softmax_slots<M>(p);
+    } else {
 #pragma unroll
         for (int ni = 0; ni < MI; ++ni)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int rr = rowb + g4 + j, i = ni * 16 + r;
-                Df[rr * L::ldg + i] = dGam[ni][j];
-                Pf[rr * L::ldg + i] = ads[ni][j];
-            }
+            for (int j = 0; j < 4; ++j) p[ni][j] = readout_value(a.readout, p[ni][j]);
     }
-    __syncthreads();
-    {
-        T *dB = a.tB + ch * C * C;
-        for (int idx = tid; idx < C * C / 8; idx += NT) {
-            const int t = idx / (C / 8), c8 = (idx - t * (C / 8)) * 8;
-            Raw8<T> x;
-            x.load(ATs + t * L::lda + c8);
-            x.store(dB + t * C + c8);
-        }
-    }
-    __syncthreads();   // ATs is about to be reused as the suffix sum's scratch
-    // ---- phase 2d: dg = (suffix sum of dGam inside the chunk) + carry - exp(g) ds
-    {
-        constexpr int P = NT / M, TP = C / P;
-        const int i = tid % M, part = tid / M;
-        float run = 0.f;
-        for (int tt = TP - 1; tt >= 0; --tt) {
-            const int t = part * TP + tt;
-            run += Df[t * L::ldg + i];
-            Df[t * L::ldg + i] = run;
-        }
-        tot[part * M + i] = run;
-        __syncthreads();
-        float off = 0.f;
+    const float half = unsafe ? 0.f : 0.5f;   // ref = half * tot
 #pragma unroll
-        for (int u = 0; u < NW; ++u) off += carry[u * M + i];
-        for (int pp = part + 1; pp < P; ++pp) off += tot[pp * M + i];
-        for (int tt = 0; tt < TP; ++tt) {
-            const int t = part * TP + tt;
-            if (t < ci.len) {
-                const size_t o = (tokh + (size_t)t * H) * M + i;
-                // gate logits in g: the gradient goes on to the logit, d logsigmoid(u)/tau / du
-                const float chain = (GEN && a.gate_tau > 0.f) ? log_gate_slope(a.g[o], a.gate_tau) : 1.f;
-                if (given) {
-                    a.dg[o] = chain * (Df[t * L::ldg + i] + off);
-                    a.ds[o] = Pf[t * L::ldg + i];
-                } else {
-                    a.dg[o] = chain * (Df[t * L::ldg + i] + off - Pf[t * L::ldg + i]);
+    for (int ni = 0; ni < MI; ++ni) {
+        f32x4 rd, rr;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            p[ni][j] = live ? p[ni][j] : 0.f;
+            wd[ni][j] = live ? scale * wd[ni][j] : 0.f;
+            const float ref = half * bg.tot[ni][j], e = __expf(bg.L[ni][j] - ref);
+            const int i = ni * 16 + g4 + j;
+            Ud[i * L::ldt + t] = from_f32<T>(wd[ni][j] * e);
+            Up[i * L::ldt + t] = from_f32<T>(p[ni][j] * e);
+            rd[j] = __expf(bg.tot[ni][j] - ref);
+            rr[j] = __expf(ref);
+        }
+        if (r == 0) {
+            *reinterpret_cast<f32x4 *>(Rd + w * M + ni * 16 + g4) = rd;
+            *reinterpret_cast<f32x4 *>(Rr + w * M + ni * 16 + g4) = rr;
+        }
+    }
+    // (the rests of the products lie where Bm^T goes below: every wave has its own before any wave writes)
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+    __syncthreads();
+    // ---- phase 2a: ds for the tokens r of block w: the sum over later tokens walks from the chunk's end (where
+    // it is the inter-chunk term) to the start of each block, ds <- ds * exp(tot) + U_b A_b
+#pragma unroll
+    for (int b = CI - 1; b >= 0; --b) {
+        if (b < w || (b == w && unsafe)) continue;   // wave-uniform
+#pragma unroll
+        for (int ni = 0; ni < MI; ++ni) {
+            ds[ni] *= *reinterpret_cast<const f32x4 *>(Rd + b * M + ni * 16 + g4);
+            Atom<T>::mma16(ds[ni], Atom<T>::load16(Ud + (ni * 16 + r) * L::ldt + b * 16 + g4), fa[b]);
+            const typename Atom<T>::Frag16 up = Atom<T>::load16(Up + (ni * 16 + r) * L::ldt + b * 16 + g4);
+            Atom<T>::mma16(ds[ni], up, fav[b]);
+            if (sizeof(T) == 2) Atom<T>::mma16(ds[ni], up, favlo[b]);
+            if (b > w) ds[ni] *= *reinterpret_cast<const f32x4 *>(Rr + b * M + ni * 16 + g4);
+        }
+    }
+#pragma unroll
+    for (int ni = 0; ni < MI; ++ni)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) ds[ni][j] *= __expf((unsafe ? 1.f : 0.5f) * bg.tot[ni][j] - bg.L[ni][j]);
+    f32x4 exb = {0.f, 0.f, 0.f, 0.f}, exa = {0.f, 0.f, 0.f, 0.f};   // diagonal pair weights, unfactored
+    if (unsafe) {
+        typename Atom<T>::Frag16 ownA = fa[0], ownAv = fav[0], ownLo = favlo[0];
+#pragma unroll
+        for (int b = 0; b < CI; ++b)
+            if (b == w) { ownA = fa[b]; ownAv = fav[b]; ownLo = favlo[b]; }
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const int tt = 4 * q + c, src = (lane & 48) | tt;
+                const float x = __shfl(to_f32(ownA[c]), 16 * q + r, 64), y = __shfl(sizeof(T) == 2 ? to_f32(ownAv[c]) + to_f32(ownLo[c]) : to_f32(ownAv[c]), 16 * q + r, 64);   // zero for t < r
+#pragma unroll
+                for (int ni = 0; ni < MI; ++ni)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const float Lt = __shfl(bg.L[ni][j], src, 64);
+                        const float d = __shfl(wd[ni][j], src, 64), pt = __shfl(p[ni][j], src, 64);
+                        ds[ni][j] += (x * d + y * pt) * __expf(fminf(Lt - bg.L[ni][j], 0.f));
+                    }
+            }
+        exb = pair_tile_exact<M, GEN>(wd, bg, lane);
+        exa = pair_tile_exact<M, GEN>(p, bg, lane);
+    }
+    // ---- phase 2b: the gate gradient inside the block, and the block's total for the earlier ones
+    f32x4 dg[MI];
+#pragma unroll
+    for (int ni = 0; ni < MI; ++ni) {
+        f32x4 sum;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float x = live ? dgl[ni][j] - bg.s[ni][j] * ds[ni][j] : 0.f;
+            sum[j] = row16_suffix_sum(x);
+            // tied: d(1 - e^g)/dg = -e^g = -(1 - s)
+            dg[ni][j] = given ? sum[j] : sum[j] - (1.f - bg.s[ni][j]) * ds[ni][j];
+        }
+        if (r == 0) *reinterpret_cast<f32x4 *>(Tot + w * M + ni * 16 + g4) = sum;
+        if (GEN && given && live) *reinterpret_cast<f32x4 *>(a.ds + row + ni * 16) = ds[ni];
+    }
+    // ---- phase 2c: the slot-side operand of dk and dv, s*exp(G_C - G)
+    T *dS = a.tSbe + ch * C * KM + (size_t)t * KM, *dD = a.tDZe + ch * C * KM + (size_t)t * KM;
+#pragma unroll
+    for (int ni = 0; ni < MI; ++ni) {
+        f32x4 y;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) y[j] = bg.s[ni][j] * __expf(bg.tot[ni][j] - bg.L[ni][j]);
+#pragma unroll
+        for (int b = 1; b < CI; ++b)
+            if (b > w) y *= *reinterpret_cast<const f32x4 *>(Rb + b * M + ni * 16 + g4);
+        store_frag16<T>(dS + ni * 16 + g4, y);
+    }
+    if (M < KM) store_frag16<T>(dS + M + g4, f32x4{0.f, 0.f, 0.f, 0.f});   // the padded slot columns
+    // ---- phase 2d: Bm (both orientations) and A2^T, row t of this wave's block, one column block after the
+    // other as in the forward; `wd` ends as the slot-side operand of dq, scale*dz*exp(G)
+#pragma unroll
+    for (int ni = 0; ni < MI; ++ni)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float e = __expf(unsafe ? bg.L[ni][j] : bg.L[ni][j] - bg.tot[ni][j]);
+            wd[ni][j] *= e;
+            p[ni][j] *= e;
+        }
+    T *dB = a.tB + ch * C * C + (size_t)t * C, *dBT = a.tBT + ch * C * C + rowb, *dA2T = a.tA2T + ch * C * C + rowb;
+#pragma unroll
+    for (int b = CI - 1; b >= 0; --b) {
+        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+        f32x4 xb = zero, xbt = zero, xat = zero;   // D[r][t]; D[t][r]
+        if (b == w && unsafe) {   // weights are already at the start of the block
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                dBT[(size_t)(b * 16 + g4 + j) * C + r] = from_f32<T>(exb[j]);
+                dA2T[(size_t)(b * 16 + g4 + j) * C + r] = from_f32<T>(exa[j]);
+            }
+            store_frag16<T>(dB + b * 16 + g4, exb);
+            continue;
+        }
+        if (b <= w) {   // wave-uniform
+            pair_tiles<T, M>(wd, p, Vn, L::ldn, b, lane, xb, xbt, xat);
+#pragma unroll
+            for (int ni = 0; ni < MI; ++ni) {
+                const f32x4 e = *reinterpret_cast<const f32x4 *>(Rb + b * M + ni * 16 + g4);
+                wd[ni] *= e;
+                p[ni] *= e;
+            }
+            if (b == w) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    xb[j] = g4 + j <= r ? xb[j] : 0.f;
+                    xbt[j] = g4 + j >= r ? xbt[j] : 0.f;
+                    xat[j] = g4 + j >= r ? xat[j] : 0.f;
                 }
             }
         }
+        store_frag16<T>(dB + b * 16 + g4, xb);
+        store_frag16<T>(dBT + (size_t)(b * 16 + r) * C + g4, xbt);
+        store_frag16<T>(dA2T + (size_t)(b * 16 + r) * C + g4, xat);
+    }
+#pragma unroll
+    for (int ni = 0; ni < MI; ++ni) store_frag16<T>(dD + ni * 16 + g4, wd[ni]);
+    if (M < KM) store_frag16<T>(dD + M + g4, f32x4{0.f, 0.f, 0.f, 0.f});
+    // ---- phase 2e: dg = (suffix sum of dGam inside the chunk) + carry - exp(g) ds
+    __syncthreads();   // the other blocks' totals
+#pragma unroll
+    for (int ni = 0; ni < MI; ++ni) {
+        f32x4 off = *reinterpret_cast<const f32x4 *>(carry + ni * 16 + g4);
+#pragma unroll
+        for (int u = 1; u < NW; ++u) off += *reinterpret_cast<const f32x4 *>(carry + u * M + ni * 16 + g4);
+#pragma unroll
+        for (int b = 1; b < CI; ++b)
+            if (b > w) off += *reinterpret_cast<const f32x4 *>(Tot + b * M + ni * 16 + g4);
+        f32x4 x = dg[ni] + off;
+        if (GEN && a.gate_tau > 0.f) {   // gate logits in g: the gradient goes on to the logit
+            const f32x4 u = *reinterpret_cast<const f32x4 *>(a.g + row + ni * 16);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) x[j] *= log_gate_slope(u[j], a.gate_tau);
+        }
+        if (live) *reinterpret_cast<f32x4 *>(a.dg + row + ni * 16) = x;
     }
 }
 
@@ -623,7 +619,8 @@ static hipError_t launch_bwd_tm(const Plan &pl, const Work &w, const void *q, co
         GSA_HIP_TRY(allow_lds(kern, lds));
         KernelTimer kt(kSlotChunkDz, st);
         hipLaunchKernelGGL(kern, grid, dim3(Geo<T>::NT), lds, st, cm, pl.H, pl.d_v, pl.scale, (const T *)v,
-                           (const T *)dO, g, z, (const T *)w.S, pl.lay, w.dz, w.dgf, (T *)w.Wr, (T *)w.tAvT, pl.s_in,
+                           (const T *)dO, g, z, (const T *)w.S, pl.lay, w.dz, w.dgf, (T *)w.Wr, (T *)w.tAvT,
+                           (T *)w.tBT, pl.s_in,
                            pl.opts(), pl.gate_tau);
         GSA_HIP_TRY(hipGetLastError());
     }
@@ -645,6 +642,7 @@ static hipError_t launch_bwd_tm(const Plan &pl, const Work &w, const void *q, co
         a.S = (const T *)w.S; a.SF = (const T *)w.SF; a.E = (const T *)w.E;
         a.lay = pl.lay;
         a.tAvT = (const T *)w.tAvT;
+        a.tAvLo = (const T *)w.tBT;
         a.dg = dg;
         a.tB = (T *)w.tA; a.tBT = (T *)w.tBT; a.tA2T = (T *)w.tA2T; a.tDZe = (T *)w.tP; a.tSbe = (T *)w.tSbe;
         a.sin = pl.s_in; a.ds = pl.ds_out; a.readout = pl.readout; a.gate_tau = pl.gate_tau;

@@ -22,26 +22,6 @@
 
 namespace gsa {
 
-__device__ __forceinline__ float wave_max(float x)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x = fmaxf(x, __shfl_xor(x, o, 64));
-    return x;
-}
-
-// True when the factored form is not safe for the 16-token block starting at row rowb:
-// some slot decays by more than e^kExpClamp across the block.  Wave-uniform.
-template <int M>
-__device__ __forceinline__ bool block_unsafe(const float *Gs, int ldg, int rowb, int lane)
-{
-    float drop = 0.f;
-    for (int i = lane; i < M; i += kWave) {
-        const float gref = rowb ? Gs[(rowb - 1) * ldg + i] : 0.f;
-        drop = fmaxf(drop, gref - Gs[(rowb + 15) * ldg + i]);
-    }
-    return wave_max(drop) > kExpClamp;
-}
-
 // Split-contraction bookkeeping.  The chunk kernels contract over the head dimension with
 // every wave taking a slice of that dimension for ALL row blocks of the chunk (so each
 // operand byte is loaded by exactly one wave, in whole 128-byte lines), and then sum the
@@ -52,20 +32,25 @@ __device__ __forceinline__ bool block_unsafe(const float *Gs, int ldg, int rowb,
 // workgroup must call it.
 // RPR row blocks are exchanged per round (RPR divides NW): fewer, fuller rounds need fewer barriers
 // and keep more waves busy adding, at the price of a larger buffer, reduce_fragments<..>() * NW * 64 f32x4.
-template <int NW, int NB, int CAUSAL, int RPR> constexpr int reduce_fragments()
+// UPPER: the causal column blocks are needed for cb >= rb instead.
+template <int NW, int NB, int CAUSAL, bool UPPER> constexpr bool reduce_skips(int rb, int cb)
+{
+    return cb < CAUSAL && (UPPER ? cb < rb : cb > rb);
+}
+template <int NW, int NB, int CAUSAL, int RPR, bool UPPER = false> constexpr int reduce_fragments()
 {
     int worst = 0;
     for (int rb0 = 0; rb0 < NW; rb0 += RPR) {
         int n = 0;
         for (int rb = rb0; rb < rb0 + RPR; ++rb)
             for (int cb = 0; cb < NB; ++cb)
-                if (!(cb < CAUSAL && cb > rb)) ++n;
+                if (!reduce_skips<NW, NB, CAUSAL, UPPER>(rb, cb)) ++n;
         worst = n > worst ? n : worst;
     }
     return worst;
 }
 
-template <int NW, int NB, int CAUSAL, int RPR = 1>
+template <int NW, int NB, int CAUSAL, int RPR = 1, bool UPPER = false>
 __device__ __forceinline__ void reduce_row_blocks(f32x4 (&own)[NB], const f32x4 (&acc)[NW][NB], f32x4 *Red, int lane,
                                                   int w)
 {
@@ -82,14 +67,14 @@ __device__ __forceinline__ void reduce_row_blocks(f32x4 (&own)[NB], const f32x4 
         for (int rb = rb0; rb < rb0 + RPR; ++rb)
 #pragma unroll
             for (int cb = 0; cb < NB; ++cb)
-                if (!(cb < CAUSAL && cb > rb)) { Red[(slot * NW + w) * kWave + lane] = acc[rb][cb]; ++slot; }
+                if (!reduce_skips<NW, NB, CAUSAL, UPPER>(rb, cb)) { Red[(slot * NW + w) * kWave + lane] = acc[rb][cb]; ++slot; }
         __syncthreads();
         slot = 0;
 #pragma unroll
         for (int rb = rb0; rb < rb0 + RPR; ++rb)
 #pragma unroll
             for (int cb = 0; cb < NB; ++cb) {
-                if (cb < CAUSAL && cb > rb) continue;
+                if (reduce_skips<NW, NB, CAUSAL, UPPER>(rb, cb)) continue;
                 if (w == rb) {
                     f32x4 x = Red[(slot * NW) * kWave + lane];
 #pragma unroll
@@ -117,6 +102,14 @@ __device__ __forceinline__ float row16_prefix_sum(float x)   // inclusive, over 
     x += dpp_or_zero<0x118>(x);
     return x;
 }
+__device__ __forceinline__ float row16_suffix_sum(float x)   // inclusive, over lanes own .. l%16 = 15
+{
+    x += dpp_or_zero<0x101>(x);   // row_shl:1, 2, 4, 8
+    x += dpp_or_zero<0x102>(x);
+    x += dpp_or_zero<0x104>(x);
+    x += dpp_or_zero<0x108>(x);
+    return x;
+}
 __device__ __forceinline__ float row16_last(float x) { return dpp_or_zero<0x15f>(x); }   // row_newbcast:15
 
 // Sum / maximum over the slots of a token: over the four lanes that share l%16, after the lane's own registers.
@@ -134,7 +127,8 @@ __device__ __forceinline__ float slots_max(float x)
 // Softmax over the slots of every token of the block, in place (D[slot][token] tiles).
 template <int M> __device__ __forceinline__ void softmax_slots(f32x4 (&p)[M / 16])
 {
-    float mx = p[0][0], sum = 0.f;
+    float mx = p[0][0];
+    f32x4 sum = {0.f, 0.f, 0.f, 0.f};   // four short chains
 #pragma unroll
     for (int ni = 0; ni < M / 16; ++ni)
 #pragma unroll
@@ -143,8 +137,8 @@ template <int M> __device__ __forceinline__ void softmax_slots(f32x4 (&p)[M / 16
 #pragma unroll
     for (int ni = 0; ni < M / 16; ++ni)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) { p[ni][j] = __expf(p[ni][j] - mx); sum += p[ni][j]; }
-    const float inv = 1.f / slots_sum(sum);
+        for (int j = 0; j < 4; ++j) { p[ni][j] = __expf(p[ni][j] - mx); sum[j] += p[ni][j]; }
+    const float inv = 1.f / slots_sum((sum[0] + sum[1]) + (sum[2] + sum[3]));
 #pragma unroll
     for (int ni = 0; ni < M / 16; ++ni) p[ni] *= inv;
 }
@@ -393,22 +387,35 @@ __device__ __forceinline__ void gated_rows(f32x4 (&run)[M / 16], const typename 
 }
 
 // Pair weights of this wave's row block w against row block b <= w, with the slots contracted in registers:
-//   out[j] = sum_i wt[i] V[r][i],   D[r][t] (T_FIRST = false) or D[t][r] (T_FIRST = true)
+//   out[j] = sum_i wt[i] V[r][i],   D[r][t]
 // wt: D[slot][t] tiles referenced to the END of block b.  Entries with r > t are returned as computed.
-template <typename T, int M, bool T_FIRST>
+template <typename T, int M>
 __device__ __forceinline__ f32x4 pair_tile(const f32x4 (&wt)[M / 16], const T *Vn, int ldn, int b, int lane)
 {
     constexpr int MI = M / 16;
     const int r = lane & 15, g4 = (lane >> 4) * 4;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
+    for (int ni = 0; ni < MI; ++ni)
+        Atom<T>::mma16(acc, Atom<T>::load16(Vn + (b * 16 + r) * ldn + ni * 16 + g4), to_frag16<T>(wt[ni]));
+    return acc;
+}
+
+// The same for two sets of weights: x1 in D[r][t]; x1t, x2t in D[t][r].
+template <typename T, int M>
+__device__ __forceinline__ void pair_tiles(const f32x4 (&w1)[M / 16], const f32x4 (&w2)[M / 16], const T *Vn, int ldn,
+                                           int b, int lane, f32x4 &x1, f32x4 &x1t, f32x4 &x2t)
+{
+    constexpr int MI = M / 16;
+    const int r = lane & 15, g4 = (lane >> 4) * 4;
+#pragma unroll
     for (int ni = 0; ni < MI; ++ni) {
         const typename Atom<T>::Frag16 v = Atom<T>::load16(Vn + (b * 16 + r) * ldn + ni * 16 + g4);
-        const typename Atom<T>::Frag16 p = to_frag16<T>(wt[ni]);
-        if (T_FIRST) Atom<T>::mma16(acc, p, v);
-        else Atom<T>::mma16(acc, v, p);
+        const typename Atom<T>::Frag16 f = to_frag16<T>(w1[ni]);
+        Atom<T>::mma16(x1, v, f);
+        Atom<T>::mma16(x1t, f, v);
+        Atom<T>::mma16(x2t, to_frag16<T>(w2[ni]), v);
     }
-    return acc;
 }
 
 // The diagonal tile D[r][t] of the pair weights without factoring: sum_i wt[i] s_r[i] exp(L_t[i] - L_r[i]) for
@@ -437,15 +444,6 @@ __device__ __forceinline__ f32x4 pair_tile_exact(const f32x4 (&wt)[M / 16], cons
     return out;
 }
 
-// Eight consecutive floats of an LDS row (16-byte aligned).
-__device__ __forceinline__ void lds_row8(float (&x)[8], const float *p)
-{
-    const f32x4 lo = *reinterpret_cast<const f32x4 *>(p);
-    const f32x4 hi = *reinterpret_cast<const f32x4 *>(p + 4);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) { x[e] = lo[e]; x[4 + e] = hi[e]; }
-}
-
 // The eight slots i0 .. i0+7 a lane contributes to a contraction over the (padded) slot axis,
 // and whether they exist: with M < KM the padding lanes re-read the last eight real slots and
 // are masked, so that no LDS read sits under a per-lane branch.
@@ -454,82 +452,6 @@ template <int M, int KM> struct SlotSpan {
     bool live;
     __device__ __forceinline__ SlotSpan(int k) : i0((M < KM) ? min(k, M - 8) : k), live((M >= KM) || (k < M)) {}
 };
-
-// Gate reference of row block rowb (cumulative log gate just before it) for slots i0 .. i0+7.
-__device__ __forceinline__ void gate_ref8(float (&gref)[8], const float *Gs, int ldg, int rowb, int i0)
-{
-    lds_row8(gref, Gs + (rowb ? rowb - 1 : 0) * ldg + i0);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) gref[e] = rowb ? gref[e] : 0.f;
-}
-
-// B fragment  b[e] = s_rr[i0+e] * exp(gref[e] - G_rr[i0+e])  (clamped; zero where !live).
-template <typename T>
-__device__ __forceinline__ typename Atom<T>::Frag write_frag(const float *Gs, const float *Ss, int ldg, int rr, int i0,
-                                                             bool live, const float (&gref)[8])
-{
-    float sv[8], gv[8];
-    lds_row8(sv, Ss + rr * ldg + i0);
-    lds_row8(gv, Gs + rr * ldg + i0);
-    typename Atom<T>::Frag b;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const float x = sv[e] * __expf(fminf(gref[e] - gv[e], kExpClamp));
-        b[e] = from_f32<T>(live ? x : 0.f);
-    }
-    return b;
-}
-
-// Row block w of the pair-weight matrix, for column blocks ni <= w:
-//   acc[ni][j] = sum_i Wa[t][i] s_r[i] exp(G_t[i] - G_r[i]),  t = rowb + 4*(lane/16) + j, r = 16*ni + lane%16
-// where the caller supplies Wa pre-multiplied by exp(G_t - Gref_w) as an LDS tile of T
-// ([C][ldp], slots padded with zeros to KM).  Entries with r > t are returned as computed
-// (the caller masks).  When the block is unsafe the diagonal atom is left at zero and the
-// caller adds pair_weights_exact.
-template <typename T, int M, int C, int KM>
-__device__ __forceinline__ void pair_weights(f32x4 (&acc)[C / 16], const T *Wa, int ldp, const float *Gs,
-                                             const float *Ss, int ldg, bool unsafe, int lane, int w)
-{
-    constexpr int CI = C / 16;
-    const int r = lane & 15, g8 = (lane >> 4) * 8;
-    const int rowb = 16 * w;
-#pragma unroll
-    for (int ni = 0; ni < CI; ++ni) acc[ni] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int k0 = 0; k0 < KM; k0 += 32) {
-        const typename Atom<T>::Frag a = Atom<T>::load(Wa + (rowb + r) * ldp + k0 + g8);
-        const SlotSpan<M, KM> sp(k0 + g8);
-        float gref[8];
-        gate_ref8(gref, Gs, ldg, rowb, sp.i0);
-#pragma unroll
-        for (int ni = 0; ni < CI; ++ni) {
-            if (ni > w || (unsafe && ni == w)) continue;   // wave-uniform
-            const typename Atom<T>::Frag b = write_frag<T>(Gs, Ss, ldg, ni * 16 + r, sp.i0, sp.live, gref);
-            Atom<T>::mma(acc[ni], a, b);
-        }
-    }
-}
-
-// Diagonal atom of the pair-weight matrix without factoring:
-//   out[j] = sum_i Wf[t][i] s_r[i] exp(G_t[i] - G_r[i])   for r = rowb + lane%16 <= t, else 0
-// Wf: LDS tile [C][ldw] of the ungated weights (fp32 or T).
-template <int M, typename TW>
-__device__ __forceinline__ f32x4 pair_weights_exact(const TW *Wf, int ldw, const float *Gs, const float *Ss, int ldg,
-                                                    int lane, int rowb)
-{
-    const int r = lane & 15, g4 = (lane >> 4) * 4;
-    const int rr = rowb + r;
-    f32x4 out = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int t = rowb + g4 + j;
-        if (rr > t) continue;
-        float sum = 0.f;
-        for (int i = 0; i < M; ++i)
-            sum += to_f32(Wf[t * ldw + i]) * Ss[rr * ldg + i] * __expf(Gs[t * ldg + i] - Gs[rr * ldg + i]);
-        out[j] = sum;
-    }
-    return out;
-}
 
 // Stores a C x ncols tile held in LDS (Os, row stride ldo) to global rows of `ld` elements,
 // 8 elements per thread, rows >= len skipped.  NTS: with the non-temporal hint (final outputs).
@@ -552,51 +474,5 @@ __device__ __forceinline__ void store_tile(T *dst, size_t ld, const T *Os, int l
         }
     }
 }
-
-// Softmax over the M slots of each chunk row, from scores in global memory into an fp32
-// LDS tile Pf[C][ld]; four threads per row.  Rows >= len get zeros.  Also copies a second
-// [len][M] array (same global layout) into Df.  Needs NT = 4*C threads.  load() only issues
-// the (clamped, unconditional) loads, so that it can be called ahead of other work.
-template <int M, int C> struct SoftmaxRows {
-    static constexpr int Q = M / 4;
-    float zv[Q], dv[Q];
-    __device__ __forceinline__ void load(const float *z, const float *dz, size_t gld, int len, int tid)
-    {
-        const int t = tid >> 2, sub = tid & 3;
-        const size_t row = (size_t)min(t, len - 1) * gld;
-#pragma unroll
-        for (int u = 0; u < Q; ++u) zv[u] = z[row + sub + 4 * u];
-#pragma unroll
-        for (int u = 0; u < Q; ++u) dv[u] = dz[row + sub + 4 * u];
-    }
-    __device__ __forceinline__ void finish(float *Pf, float *Df, int ld, int len, int tid)
-    {
-        const int t = tid >> 2, sub = tid & 3;
-        float mx = -INFINITY;
-#pragma unroll
-        for (int u = 0; u < Q; ++u) mx = fmaxf(mx, zv[u]);
-        mx = fmaxf(mx, __shfl_xor(mx, 1, 64));
-        mx = fmaxf(mx, __shfl_xor(mx, 2, 64));
-        float sum = 0.f;
-#pragma unroll
-        for (int u = 0; u < Q; ++u) { zv[u] = __expf(zv[u] - mx); sum += zv[u]; }
-        sum += __shfl_xor(sum, 1, 64);
-        sum += __shfl_xor(sum, 2, 64);
-        const float inv = (t < len) ? 1.f / sum : 0.f;
-#pragma unroll
-        for (int u = 0; u < Q; ++u) Pf[t * ld + sub + 4 * u] = zv[u] * inv;
-#pragma unroll
-        for (int u = 0; u < Q; ++u) Df[t * ld + sub + 4 * u] = (t < len) ? dv[u] : 0.f;
-    }
-    // The same with an element-wise read-out p = f(z) in place of the softmax.
-    __device__ __forceinline__ void finish_elementwise(int readout, float *Pf, float *Df, int ld, int len, int tid)
-    {
-        const int t = tid >> 2, sub = tid & 3;
-#pragma unroll
-        for (int u = 0; u < Q; ++u) Pf[t * ld + sub + 4 * u] = (t < len) ? readout_value(readout, zv[u]) : 0.f;
-#pragma unroll
-        for (int u = 0; u < Q; ++u) Df[t * ld + sub + 4 * u] = (t < len) ? dv[u] : 0.f;
-    }
-};
 
 }  // namespace gsa

@@ -341,12 +341,7 @@ __device__ __forceinline__ void seq_lookup(const ChunkMap &cm, int s, int &chunk
 }
 
 // ----------------------------------------------------------------------------
-// Gate preparation for one chunk (Algorithm 1, chunk_cumsum, plus the write
-// intensity): from g[len][M] (global, row stride gld) fill
-//   Gs[t][i] = sum_{j<=t} max(g_j[i], floor)      chunk-local inclusive cumulative log gate
-//   Ss[t][i] = 1 - exp(g_t[i])                    write intensity (0 on padded rows)
-// Rows t >= len are padded with g = 0.  Needs blockDim.x = NT threads, NT % M == 0,
-// C % (NT/M) == 0, and `tot` scratch of NT floats.  Ends with a __syncthreads().
+// Gates (Algorithm 1, chunk_cumsum, plus the write intensity).
 // ----------------------------------------------------------------------------
 // log gate from a gate logit: logsigmoid(u) / tau = -(log(1 + exp(-|u|)) + max(-u, 0)) / tau, and its slope
 __device__ __forceinline__ float log_gate_from_logit(float u, float tau)
@@ -372,6 +367,8 @@ __device__ __forceinline__ float write_intensity(float x)
     return x > -0.5f ? -x * p : 1.f - __expf(x);
 }
 
+// Gates of one slot's run of tokens in a chunk-wide layout: thread tid owns slot tid % M and the C / P tokens
+// from (tid / M) * C / P on.  Log gates are floored at kGateFloor, rows past the end of the chunk are g = 0, s = 0.
 // GEN: the general form, in which the write intensity may come from an array of its own
 // (sin: [len][M] fp32, same layout as g; NULL = 1 - exp(g) as above), and the array g may hold gate
 // LOGITS u instead of log gates: with tau > 0 the log gate is logsigmoid(u) / tau, the layer's gate
@@ -399,43 +396,17 @@ template <int M, int NT, int C, bool GEN = false> struct GatePrep {
             for (int tt = 0; tt < (GEN ? TP : 1); ++tt) sv[tt] = sin[(size_t)min(part * TP + tt, len - 1) * gld + i];
         }
     }
-    // Fills Gs, Ss.  Contains barriers (all threads must call it) and ends with one.
-    __device__ __forceinline__ void finish(float *Gs, float *Ss, int ldg, float *tot, int len, int tid) const
+    // Log gate and write intensity of this thread's token tt (0 and 0 past the end of the chunk).
+    __device__ __forceinline__ void token(float &x, float &sx, int tt, bool live) const
     {
-        const int i = tid % M, part = tid / M;
-        float run = 0.f;
-#pragma unroll
-        for (int tt = 0; tt < TP; ++tt) {
-            const int t = part * TP + tt;
-            float graw = gv[tt];
-            if (GEN && tau > 0.f) graw = log_gate_from_logit(graw, tau);
-            const float x = (t < len) ? fmaxf(graw, kGateFloor) : 0.f;
-            run += x;
-            Gs[t * ldg + i] = run;
-            float sx = write_intensity(x);
-            if (GEN && given) sx = sv[GEN ? tt : 0];
-            Ss[t * ldg + i] = (t < len) ? sx : 0.f;
-        }
-        tot[part * M + i] = run;
-        __syncthreads();
-        float off = 0.f;
-        for (int pp = 0; pp < part; ++pp) off += tot[pp * M + i];
-        if (part > 0) {
-#pragma unroll 4
-            for (int tt = 0; tt < TP; ++tt) Gs[(part * TP + tt) * ldg + i] += off;
-        }
-        __syncthreads();
+        float graw = gv[tt];
+        if (GEN && tau > 0.f) graw = log_gate_from_logit(graw, tau);
+        x = live ? fmaxf(graw, kGateFloor) : 0.f;
+        sx = write_intensity(x);
+        if (GEN && given) sx = sv[GEN ? tt : 0];
+        sx = live ? sx : 0.f;
     }
 };
-
-template <int M, int NT, int C, bool GEN = false>
-__device__ __forceinline__ void gate_prep(float *Gs, float *Ss, int ldg, float *tot, const float *g, size_t gld,
-                                          int len, int tid, const float *sin = nullptr, float gate_tau = 0.f)
-{
-    GatePrep<M, NT, C, GEN> gp;
-    gp.load(g, gld, len, tid, sin, gate_tau);
-    gp.finish(Gs, Ss, ldg, tot, len, tid);
-}
 
 // ----------------------------------------------------------------------------
 // Read-outs: how the slot scores z become the read weights p.  Softmax over the slots is the
@@ -575,19 +546,5 @@ template <typename T, int C, int NCOLS, int NT> struct TokTile {
         }
     }
 };
-
-// Reduce over the 16 lanes that share l/16 (the 16 columns of one D-tile row).
-__device__ __forceinline__ float row16_max(float x)
-{
-#pragma unroll
-    for (int o = 1; o < 16; o <<= 1) x = fmaxf(x, __shfl_xor(x, o, 64));
-    return x;
-}
-__device__ __forceinline__ float row16_sum(float x)
-{
-#pragma unroll
-    for (int o = 1; o < 16; o <<= 1) x += __shfl_xor(x, o, 64);
-    return x;
-}
 
 }  // namespace gsa

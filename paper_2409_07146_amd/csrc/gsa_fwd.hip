@@ -176,7 +176,7 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_fwd_kernel
             if (b == w && unsafe) {
                 x = exact;   // p is already at the start of the block
             } else {
-                x = pair_tile<T, M, false>(p, Vn, L::ldn, b, lane);
+                x = pair_tile<T, M>(p, Vn, L::ldn, b, lane);
 #pragma unroll
                 for (int ni = 0; ni < MI; ++ni) p[ni] *= *reinterpret_cast<const f32x4 *>(Rb + b * M + ni * 16 + g4);
             }

@@ -51,7 +51,7 @@ struct Work {
     void *SF;         // per (sequence, head): memory after the last token (Plan::lay)
     void *Wr;         // [2][m][C]   reverse scan weights
     void *E;          // gradient of the memory at the end of the chunk (Plan::lay)
-    void *tBT;        // [C][C]      scale*Bm^T
+    void *tBT;       // [C][C]      first the rest of tAvT's rounding (bf16), then scale*Bm^T
     void *tA2T;       // [C][C]      A2^T
     void *tAvT;       // [C][C]      (dO_t . v_r)^T, causally masked
     void *tSbe;       // [C][KM]     s*exp(G_C-G)

@@ -25,6 +25,10 @@ namespace gsa {
 
 // ---------------------------------------------------------------------------------------
 // Gate weights of the forward scan (chunk-parallel).
+//
+// Everything stays in the registers of the thread that owns a slot's tokens; only the partial sums of the
+// partitions meet in LDS.  (A form with gate and intensity tiles in LDS took as long at m = 64, 11 us with the
+// launch around it, and 20 us against 19 at m = 128.)
 // ---------------------------------------------------------------------------------------
 template <typename T, int M, bool GEN>
 __global__ __launch_bounds__(Geo<T>::NT) void gate_kernel(ChunkMap cm, int H, const float *__restrict__ g,
@@ -32,27 +36,44 @@ __global__ __launch_bounds__(Geo<T>::NT) void gate_kernel(ChunkMap cm, int H, co
                                                           T *__restrict__ Wf, float *__restrict__ dec)
 {
     constexpr int C = Geo<T>::C, NT = Geo<T>::NT;
-    constexpr int ldg = M + 1;   // odd row stride: the column reads below spread over all banks
-    __shared__ float Gs[C * ldg];
-    __shared__ float Ss[C * ldg];
+    typedef GatePrep<M, NT, C, GEN> Gates;
+    constexpr int P = Gates::P, TP = Gates::TP;   // a thread owns one slot and TP consecutive tokens
     __shared__ float tot[NT];
     ChunkInfo ci;
     if (!chunk_lookup(cm, blockIdx.x, ci)) return;
-    const int h = blockIdx.y, tid = threadIdx.x;
+    const int h = blockIdx.y, tid = threadIdx.x, i = tid % M, part = tid / M;
     const size_t ch = (size_t)blockIdx.x * H + h;
     const size_t goff = ((size_t)ci.tok0 * H + h) * M;
-    gate_prep<M, NT, C, GEN>(Gs, Ss, ldg, tot, g + goff, (size_t)H * M, ci.len, tid, (GEN && sin) ? sin + goff : nullptr,
-                             gate_tau);
-    T *W = Wf + ch * M * C;
-    for (int idx = tid; idx < M * C / 8; idx += NT) {   // eight consecutive tokens of one slot per thread
-        const int i = idx / (C / 8), t8 = (idx - i * (C / 8)) * 8;
-        const float gc = Gs[(C - 1) * ldg + i];
-        float x[8];
+    Gates gp;
+    gp.load(g + goff, (size_t)H * M, ci.len, tid, (GEN && sin) ? sin + goff : nullptr, gate_tau);
+    float x[TP], w[TP], own = 0.f;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] = Ss[(t8 + e) * ldg + i] * __expf(gc - Gs[(t8 + e) * ldg + i]);
-        store8<T>(W + i * C + t8, x);
+    for (int tt = TP - 1; tt >= 0; --tt) {
+        gp.token(x[tt], w[tt], tt, part * TP + tt < ci.len);
+        own += x[tt];
     }
-    if (tid < M) dec[ch * M + tid] = __expf(Gs[(C - 1) * ldg + tid]);
+    tot[part * M + i] = own;
+    __syncthreads();
+    float after = 0.f;   // decay of the chunk behind the token: G_C - G_t
+#pragma unroll
+    for (int pp = P - 1; pp > 0; --pp) after += pp > part ? tot[pp * M + i] : 0.f;
+#pragma unroll
+    for (int tt = TP - 1; tt >= 0; --tt) {
+        w[tt] *= __expf(after);
+        after += x[tt];
+    }
+    T *W = Wf + ch * M * C + (size_t)i * C + part * TP;
+    if constexpr (TP % 8 == 0) {
+#pragma unroll
+        for (int t8 = 0; t8 < TP; t8 += 8) {
+            const float y[8] = {w[t8], w[t8 + 1], w[t8 + 2], w[t8 + 3], w[t8 + 4], w[t8 + 5], w[t8 + 6], w[t8 + 7]};
+            store8<T>(W + t8, y);
+        }
+    } else {
+        static_assert(TP == 4, "tokens per thread");
+        store4(W, w[0], w[1], w[2], w[3]);
+    }
+    if (part == 0) dec[ch * M + i] = __expf(after);
 }
 
 // ---------------------------------------------------------------------------------------
