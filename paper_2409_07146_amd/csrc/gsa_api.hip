@@ -19,7 +19,8 @@ bool valid_m(int m, bool sequence_kernels)
     return m == 16 || m == 32 || m == 64 || m == 128;
 }
 
-gsa_status make_plan(const gsa_problem *p, Plan *pl)
+// fine_segments: see the segment rule below.
+gsa_status make_plan(const gsa_problem *p, Plan *pl, bool fine_segments = true)
 {
     if (!p) return GSA_ERR_NULL;
     if (p->B < 1 || p->T < 0 || p->H < 1 || p->d_k < 1 || p->d_v < 1 || p->m < 1) return GSA_ERR_SHAPE;
@@ -57,23 +58,35 @@ gsa_status make_plan(const gsa_problem *p, Plan *pl)
     pl->off_dec = off;    off += align_up(ch * M * sizeof(float));
     pl->off_tA = off;     off += align_up(ch * C * C * esz);
     pl->off_tP = off;     off += align_up(ch * C * KM * esz);
-    // Long sequences: the scans cut them into segments (gsa_scan.hip).  The host knows the longest a
-    // sequence can be (T tokens, also in packed form) and provides for that many segments per sequence;
-    // this is only done while the sequences alone do not fill the chip.
+    // The scans cut sequences into segments (gsa_scan.hip) while the sequences alone do not fill the chip: the
+    // launch then waits on the chain over the chunks, and two launches with a short chain each are faster.
+    // The host knows the longest a sequence can be (T tokens, also in packed form) and provides for that many
+    // segments per sequence.
     {
         const int64_t max_nch = ((int64_t)p->T + pl->chunk - 1) / pl->chunk;
-        const int64_t nseg = (max_nch + gsa::kSegChunks - 1) / gsa::kSegChunks;
         const int64_t base = (int64_t)pl->n_seqs * p->H * ((dk + dv) / 64);   // workgroups of an unsegmented scan
-        const bool on = max_nch > gsa::kSegChunks + gsa::kSegChunks / 2 && base < 512 && base * nseg <= 8192;
+        auto segs = [&](int64_t c) { return (max_nch + c - 1) / c; };
+        bool on = max_nch > gsa::kSegChunks + gsa::kSegChunks / 2 && base < 512 && base * segs(gsa::kSegChunks) <= 8192;
         pl->seg_chunks = gsa::kSegChunks;
-        pl->max_seg = on ? (int32_t)nseg : 1;
+        pl->fine = false;
+        // Batch form (every sequence really is T long): the shortest segments that still leave the chip one
+        // round of workgroups (one per CU), and a chain that gets at least a third shorter -- both launches
+        // walk seg_chunks chunks.  B=1, T=2048, H=4, d=512 (64 workgroups): 34 us in
+        // one walk, 13 + 17 us in four segments of eight; with 128 workgroups (512 of segments) 36 us against 16 + 24.
+        if (fine_segments && !p->cu_seqlens)
+            for (int32_t c : {8, 16})
+                if (!pl->fine && max_nch >= 3 * c && base * segs(c) <= 256) {
+                    on = pl->fine = true;
+                    pl->seg_chunks = c;
+                }
+        pl->max_seg = on ? (int32_t)segs(pl->seg_chunks) : 1;
     }
     const size_t nsum = pl->max_seg > 1 ? (size_t)pl->n_seqs * pl->max_seg * p->H : 0;
-    pl->off_sumY = off;   off += align_up(nsum * M * D * sizeof(float));
-    pl->off_sumD = off;   off += align_up(nsum * (D / 64) * M * sizeof(float));
+    const size_t szY = align_up(nsum * M * D * sizeof(float)), szD = align_up(nsum * (D / 64) * M * sizeof(float));
     pl->off_S = off;
-    pl->total_fwd = off + align_up(ch * M * D * esz);
     off += align_up(ch * M * D * esz);
+    pl->off_sum_fwd = off;   // the segment summaries come last, so that nothing else depends on their size
+    pl->total_fwd = off + szY + szD;
     pl->off_SF = off;     off += align_up((size_t)pl->n_seqs * p->H * M * D * esz);
     pl->off_Wr = off;     off += align_up(ch * 2 * M * C * esz);
     pl->off_E = off;      off += align_up(ch * M * D * esz);
@@ -83,12 +96,15 @@ gsa_status make_plan(const gsa_problem *p, Plan *pl)
     pl->off_tSbe = off;   off += align_up(ch * C * KM * esz);
     pl->off_dz = off;     off += align_up(tokm);
     pl->off_dgf = off;    off += align_up(tokm);
-    pl->total_bwd = off;
+    pl->off_sum_bwd = off;
+    pl->size_sumY = szY;
+    pl->total_bwd = off + szY + szD;
     if (pl->keep) pl->total_fwd = pl->total_bwd;   // one workspace goes through both calls
     return GSA_OK;
 }
 
-Work make_work(const Plan &pl, void *ws)
+// bwd: the backward's layout (also the forward's when it keeps the memories for the backward)
+Work make_work(const Plan &pl, void *ws, bool bwd)
 {
     unsigned char *b = static_cast<unsigned char *>(ws);
     Work w;
@@ -97,8 +113,9 @@ Work make_work(const Plan &pl, void *ws)
     w.segbase = reinterpret_cast<int32_t *>(b + pl.off_segbase);
     w.Wf = b + pl.off_Wf;
     w.dec = reinterpret_cast<float *>(b + pl.off_dec);
-    w.sumY = reinterpret_cast<float *>(b + pl.off_sumY);
-    w.sumD = reinterpret_cast<float *>(b + pl.off_sumD);
+    const size_t sum = bwd ? pl.off_sum_bwd : pl.off_sum_fwd;
+    w.sumY = reinterpret_cast<float *>(b + sum);
+    w.sumD = reinterpret_cast<float *>(b + sum + pl.size_sumY);
     w.S = b + pl.off_S;
     w.tA = b + pl.off_tA;
     w.tP = b + pl.off_tP;
@@ -143,6 +160,15 @@ gsa_status check_workspace(void *ws, size_t have, size_t need)
     if (reinterpret_cast<uintptr_t>(ws) % kAlign) return GSA_ERR_WORKSPACE;
     if (have < need) return GSA_ERR_WORKSPACE;
     return GSA_OK;
+}
+
+// The plan of one call: a workspace that holds everything but the summaries of short segments is still good for
+// the scans without them (the rest of the layout is the same).
+gsa_status plan_call(const gsa_problem *p, bool want_bwd, size_t workspace_bytes, Plan *pl)
+{
+    gsa_status st = make_plan(p, pl);
+    if (st == GSA_OK && pl->fine && workspace_bytes < (want_bwd ? pl->total_bwd : pl->total_fwd)) st = make_plan(p, pl, false);
+    return st;
 }
 
 gsa_status decode_checks(int32_t B, int32_t H, int32_t d_k, int32_t d_v, int32_t m, int32_t dtype, float scale)
@@ -221,7 +247,7 @@ gsa_status fwd_any(const gsa_problem *p, int32_t readout, float gate_tau, int32_
                    void *stream, void *act = nullptr, float *ssq = nullptr, bool with_act = false)
 {
     Plan pl;
-    gsa_status st = make_plan(p, &pl);
+    gsa_status st = plan_call(p, false, workspace_bytes, &pl);
     if (st != GSA_OK) return st;
     if (readout < GSA_READOUT_SOFTMAX || readout > GSA_READOUT_RELU2) return GSA_ERR_SHAPE;
     if (!(gate_tau >= 0.f)) return GSA_ERR_SHAPE;
@@ -252,7 +278,7 @@ gsa_status fwd_any(const gsa_problem *p, int32_t readout, float gate_tau, int32_
     pl.readout = readout;
     pl.gate_tau = gate_tau;
     pl.phi = feature_map;
-    const Work w = make_work(pl, workspace);
+    const Work w = make_work(pl, workspace, pl.keep);
     const hipError_t e = gsa::launch_fwd(pl, w, q, k, v, g, K0, V0, o, z_saved, KT, VT,
                                          static_cast<hipStream_t>(stream));
     return e == hipSuccess ? GSA_OK : GSA_ERR_HIP;
@@ -265,7 +291,7 @@ gsa_status bwd_any(const gsa_problem *p, int32_t readout, float gate_tau, int32_
                    void *stream)
 {
     Plan pl;
-    gsa_status st = make_plan(p, &pl);
+    gsa_status st = plan_call(p, true, workspace_bytes, &pl);
     if (st != GSA_OK) return st;
     if (readout < GSA_READOUT_SOFTMAX || readout > GSA_READOUT_RELU2) return GSA_ERR_SHAPE;
     if (!(gate_tau >= 0.f)) return GSA_ERR_SHAPE;
@@ -294,7 +320,7 @@ gsa_status bwd_any(const gsa_problem *p, int32_t readout, float gate_tau, int32_
     pl.readout = readout;
     pl.gate_tau = gate_tau;
     pl.phi = feature_map;
-    const Work w = make_work(pl, workspace);
+    const Work w = make_work(pl, workspace, true);
     const hipError_t e = gsa::launch_bwd(pl, w, q, k, v, g, K0, V0, z_saved, dO, dKT, dVT, dq, dk, dv, dg, dK0, dV0,
                                          static_cast<hipStream_t>(stream));
     return e == hipSuccess ? GSA_OK : GSA_ERR_HIP;

@@ -18,9 +18,10 @@ struct Plan {
     int32_t chunk;              // tokens per chunk for this dtype
     int32_t chunk_slots;        // upper bound on chunks (exact in batch form)
     int32_t seg_chunks, max_seg;   // long sequences: chunks per scan segment, segments provided per sequence (1 = off)
+    bool fine;                  // segments shorter than kSegChunks
     // workspace offsets in bytes (256-byte aligned); 0-sized parts share an offset
-    size_t off_table, off_seqtab, off_segbase, off_Wf, off_dec, off_S, off_tA, off_tP, off_sumY, off_sumD, total_fwd;
-    size_t off_SF, off_Wr, off_E, off_dz, off_dgf, off_tB, off_tBT, off_tA2T, off_tAvT, off_tSbe, total_bwd;
+    size_t off_table, off_seqtab, off_segbase, off_Wf, off_dec, off_S, off_tA, off_tP, off_sum_fwd, total_fwd;
+    size_t off_SF, off_Wr, off_E, off_dz, off_dgf, off_tB, off_tBT, off_tA2T, off_tAvT, off_tSbe, off_sum_bwd, size_sumY, total_bwd;
     // layout of every memory snapshot record (elements); see gsa_layout.h
     StateLayout lay;
     // variants (gsa_fwd_ex / gsa_bwd_ex): write intensity as an input of its own, element-wise read-outs
@@ -51,7 +52,7 @@ struct Work {
     void *SF;         // per (sequence, head): memory after the last token (Plan::lay)
     void *Wr;         // [2][m][C]   reverse scan weights
     void *E;          // gradient of the memory at the end of the chunk (Plan::lay)
-    void *tBT;       // [C][C]      first the rest of tAvT's rounding (bf16), then scale*Bm^T
+    void *tBT;        // [C][C]      scale*Bm^T
     void *tA2T;       // [C][C]      A2^T
     void *tAvT;       // [C][C]      (dO_t . v_r)^T, causally masked
     void *tSbe;       // [C][KM]     s*exp(G_C-G)
