@@ -14,8 +14,9 @@
 //   * one workgroup per (sequence, head, column slice); the slice of acc lives in MFMA
 //     accumulators for the whole sequence;
 //   * the tiles of chunk n+1 are prefetched into registers while chunk n is multiplied;
-//   * snapshots leave through an LDS tile, as one contiguous block per workgroup (the records are
-//     tiled by column slice for this);
+//   * snapshots leave by 16-byte pieces: the accumulator tiles are D[column][slot], with the columns dealt to
+//     the matrix rows so that a lane holds runs of consecutive columns of one slot, and a workgroup's tile of
+//     the record is one contiguous block (the records are tiled by column slice for this);
 //   * workgroups that share (sequence, head) — and therefore W and dec — are mapped to
 //     the same XCD so those re-reads hit its L2.
 #include "gsa_chunk.h"
@@ -101,21 +102,25 @@ template <typename T, int M, int NS> struct ScanLds {
     static constexpr int C = Geo<T>::C;
     static constexpr int PAD = Atom<T>::kPad;
     static constexpr int ldw = C + PAD;      // XT [NS][ldw]
-    static constexpr int lds = NS + PAD;     // snapshot tile [M][lds]
+    // a workgroup's waves share out the slots first, then the columns
+    static constexpr int NW = Geo<T>::NW;
+    static constexpr int WS = M / 16 < NW ? M / 16 : NW, WC = NW / WS;
+    static constexpr int MI = M / (16 * WS), NI = NS / (16 * WC);   // slot and column tiles of a wave
     // We [M][C] has no padding: its 8-element groups are XOR-swizzled by the row instead (we_off), which
-    // keeps the fragment reads of 16 rows off each other's banks just as well and, with the decays at
-    // one word per slot, brings a workgroup under a third of a CU's LDS: three are resident instead of
-    // two, which is what lets 640 scan workgroups (d = 640, or five heads) run as one round.
+    // keeps the fragment reads of 16 rows off each other's banks just as well.
     static constexpr int GW = C / 8;         // groups per row
     __device__ static __forceinline__ int we_off(int i, int t8) { return i * C + (((t8 >> 3) ^ (i & (GW - 1))) << 3); }
     // one set per parity of the chunk's position in the walk: a set is written while the other is read
-    static constexpr size_t szW = sizeof(T) * M * C, szX = sizeof(T) * NS * ldw, szS = sizeof(T) * M * lds;
+    static constexpr size_t szW = sizeof(T) * M * C, szX = sizeof(T) * NS * ldw;
     static constexpr size_t oW = 0;
     static constexpr size_t oX = oW + szW;
-    static constexpr size_t oSn = oX + szX;
-    static constexpr size_t oDec = oSn + szS;             // chunk decays, fp32 [M]
+    static constexpr size_t oDec = oX + szX;              // chunk decays, fp32 [M]
     static constexpr size_t set = oDec + sizeof(float) * M;
-    static constexpr size_t bytes = 2 * set;
+    // where a wave owns whole rows of the snapshot tile: its 16 slots meet here, so that they leave in full lines
+    static constexpr bool kRows = NI * 16 == NS;
+    static constexpr int ldx = NS + PAD;
+    static constexpr size_t oEx = 2 * set, szEx = kRows ? sizeof(T) * 16 * ldx : 0;   // per wave
+    static constexpr size_t bytes = oEx + NW * szEx;
 };
 
 // MODE 0: one workgroup walks a whole sequence.  A sequence of many chunks leaves the chip waiting on
@@ -129,18 +134,16 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void scan_kernel(Chun
                                                           ScanArgs<T> a)
 {
     using L = ScanLds<T, M, NS>;
-    constexpr int C = Geo<T>::C, NT = Geo<T>::NT, NW = Geo<T>::NW;
-    constexpr int MI = M / 16, NI = NS / (16 * NW);
-    constexpr int WVEC = M * C / 8, SVEC = M * NS / 8;
-    constexpr int WV = (WVEC + NT - 1) / NT, SV = (SVEC + NT - 1) / NT;
+    constexpr int C = Geo<T>::C, NT = Geo<T>::NT;
+    constexpr int MI = L::MI, NI = L::NI;
+    constexpr int WVEC = M * C / 8, WV = (WVEC + NT - 1) / NT;
     extern __shared__ __align__(16) unsigned char smem[];
     auto We = [&](int b) { return reinterpret_cast<T *>(smem + b * L::set + L::oW); };
     auto XT = [&](int b) { return reinterpret_cast<T *>(smem + b * L::set + L::oX); };
-    auto Sn = [&](int b) { return reinterpret_cast<T *>(smem + b * L::set + L::oSn); };
     auto Dec = [&](int b) { return reinterpret_cast<float *>(smem + b * L::set + L::oDec); };
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int r = lane & 15, g4 = (lane >> 4) * 4, g8 = (lane >> 4) * 8;
+    const int r = lane & 15, g8 = (lane >> 4) * 8;
     const int D = d_k + d_v;
     const int nsl = D / NS;
     // XCD-aware placement: consecutive workgroup ids go round-robin over the 8 XCDs.  The slices of one
@@ -187,7 +190,13 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void scan_kernel(Chun
 
     int chunk0, nch_seq, tok0, ntok;
     seq_lookup(cm, s, chunk0, nch_seq, tok0, ntok);
-    const int wcol = wave * 16 * NI;
+    // acc[mi][ni][j]: slot slot0 + 16*mi, column lcol + tcol(ni) + j of the slice.  Matrix row rho of column tile ni is
+    // column wcol + (rho/4)*4*NP + tcol(ni) + rho%4: a lane's registers are runs of 4*NP consecutive columns, and
+    // the four lanes that share a slot cover 16*NP of them in a row with each store.
+    constexpr int NP = NI < 2 ? 1 : 2;
+    const int slot0 = (wave % L::WS) * MI * 16 + r, wcol = (wave / L::WS) * 16 * NI;
+    const int lcol = wcol + (lane >> 4) * 4 * NP, xrow = wcol + (r >> 2) * 4 * NP + (r & 3);
+    auto tcol = [](int ni) { return (ni / NP) * 16 * NP + (ni % NP) * 4; };
     // the chunks this workgroup walks: [first, first + nch) of the sequence
     int first = 0, nch = nch_seq, nseg = 1;
     if (MODE != 0) {
@@ -207,16 +216,17 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void scan_kernel(Chun
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-            for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int i = mi * 16 + g4 + j, c = c0 + wcol + ni * 16 + r;
-                    acc[mi][ni][j] = (MODE != 1 && S0) ? S0[(((size_t)s * H + h) * M + i) * dsrc + c] : 0.f;
-                }
+            for (int ni = 0; ni < NI; ++ni) {
+                const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+                acc[mi][ni] = (MODE != 1 && S0) ? *reinterpret_cast<const f32x4 *>(
+                                                      S0 + (((size_t)s * H + h) * M + slot0 + 16 * mi) * dsrc + c0 + lcol + tcol(ni))
+                                                : zero;
+            }
         if (MODE == 2 && !starts_walk) {
             // the memory at the start of this segment: the recurrence over the summaries of the segments
             // walked before it, acc <- Diag(sumD) acc + sumY, in walk order
             const int npre = REVERSE ? nseg - 1 - seg : seg;
+#pragma unroll 2
             for (int u = 0; u < npre; ++u) {
                 const int sg = REVERSE ? nseg - 1 - u : u;
                 const size_t rec = ((size_t)s * a.max_seg + sg) * H + h;
@@ -224,12 +234,10 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void scan_kernel(Chun
                 const float *Dd = a.sumD + (rec * nsl + slice) * M;
 #pragma unroll
                 for (int mi = 0; mi < MI; ++mi) {
-                    const f32x4 dd = *reinterpret_cast<const f32x4 *>(Dd + mi * 16 + g4);
+                    const float dd = Dd[slot0 + 16 * mi];
 #pragma unroll
                     for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            acc[mi][ni][j] = dd[j] * acc[mi][ni][j] + Y[(size_t)(mi * 16 + g4 + j) * D + wcol + ni * 16 + r];
+                        acc[mi][ni] = dd * acc[mi][ni] + *reinterpret_cast<const f32x4 *>(Y + (size_t)(slot0 + 16 * mi) * D + lcol + tcol(ni));
                 }
             }
         }
@@ -238,9 +246,9 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void scan_kernel(Chun
         // express as "everything", and that would drain the prefetches in every iteration.
         __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0) only
     }
-    f32x4 dprod[MI];   // MODE 1: product of the chunk decays, rows as in acc
+    float dprod[MI];   // MODE 1: product of the chunk decays, slots as in acc
 #pragma unroll
-    for (int mi = 0; mi < MI; ++mi) dprod[mi] = f32x4{1.f, 1.f, 1.f, 1.f};
+    for (int mi = 0; mi < MI; ++mi) dprod[mi] = 1.f;
 
     // Operands of one chunk, staged in registers: the loads of the next two chunks are in flight
     // while the current one multiplies (one chunk ahead does not cover the memory latency of a
@@ -263,32 +271,41 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void scan_kernel(Chun
         const T *Xg = src + ((size_t)(tok0 + n * C) * H + h) * dsrc + c0;
         st.xt.template load<true>(Xg, (size_t)H * dsrc, len, NS, tid);
     };
-    // accumulator -> LDS tile [m][cols] -> whole rows of the record's key or value part
-    auto snapshot_to_lds = [&](int b) {
-        T *dstl = Sn(b);
-#pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-            for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    dstl[(mi * 16 + g4 + j) * L::lds + wcol + ni * 16 + r] = from_f32<T>(acc[mi][ni][j]);
-    };
-    auto snapshot_to_global = [&](T *rec, int b) {   // rec: start of the record
+    // accumulator -> this workgroup's tile of a record (rec: its start); read back by the next kernel: cached
+    auto snapshot = [&](T *rec) {
         static_assert(NS == kSnapTile, "one workgroup owns one tile of the record");
-        T *dst = rec + (isK ? a.lay.oK : a.lay.oV) + (size_t)(c0 / kSnapTile) * (M * kSnapTile);   // contiguous [M][NS]
-        const T *srcl = Sn(b);
-        // LDS reads first (clamped, unconditional), then the stores: no read sits under a branch
-        Raw8<T> x[SV];
+        T *dst = rec + (isK ? a.lay.oK : a.lay.oV) + (size_t)(c0 / kSnapTile) * (M * kSnapTile) + slot0 * kSnapTile + lcol;
 #pragma unroll
-        for (int u = 0; u < SV; ++u) {
-            const int idx = min(tid + NT * u, SVEC - 1), i = idx / (NS / 8), cg = idx - i * (NS / 8);
-            x[u].load(srcl + i * L::lds + cg * 8);
-        }
+        for (int mi = 0; mi < MI; ++mi) {
+            T *d = dst + mi * 16 * kSnapTile;
+            if constexpr (L::kRows) {
+                T *X = reinterpret_cast<T *>(smem + L::oEx + wave * L::szEx);
 #pragma unroll
-        for (int u = 0; u < SV; ++u) {
-            const int idx = tid + NT * u;
-            if (SVEC % NT == 0 || idx < SVEC) x[u].store(dst + (size_t)idx * 8);   // read back by the next kernel: cached
+                for (int ni = 0; ni < NI; ni += 2) {
+                    const f32x4 x = acc[mi][ni], y = acc[mi][ni + 1];
+                    const float v[8] = {x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]};
+                    store8<T>(X + r * L::ldx + lcol + tcol(ni), v);
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                T *rows = dst - r * kSnapTile - lcol + mi * 16 * kSnapTile;
+#pragma unroll
+                for (int u = 0; u < 16 * NS / 8 / kWave; ++u) {
+                    const int idx = lane + kWave * u;
+                    Raw8<T> x;
+                    x.load(X + (idx / (NS / 8)) * L::ldx + (idx % (NS / 8)) * 8);
+                    x.store(rows + (size_t)idx * 8);
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            } else if constexpr (NI == 1) {
+                store4(d, acc[mi][0][0], acc[mi][0][1], acc[mi][0][2], acc[mi][0][3]);
+            } else {
+#pragma unroll
+                for (int ni = 0; ni < NI; ni += 2) {
+                    const f32x4 x = acc[mi][ni], y = acc[mi][ni + 1];
+                    const float v[8] = {x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]};
+                    store8<T>(d + tcol(ni), v);
+                }
+            }
         }
     };
     // staged registers -> LDS set b (W as is, X transposed)
@@ -312,34 +329,32 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void scan_kernel(Chun
     auto chunk_of = [&](int it) { it = min(it, nch - 1); return first + (REVERSE ? nch - 1 - it : it); };
 
     // The walk, software-pipelined with ONE barrier per chunk.  At the top of step `it` LDS set it%2
-    // holds the operands of chunk `it` (written during the previous step) and the snapshot tile of
-    // the other set holds the memory the previous chunk started from.  The step
-    //   - sends that previous snapshot to global memory,
-    //   - snapshots the accumulator (the memory chunk `it` starts from) into its own set,
+    // holds the operands of chunk `it` (written during the previous step).  The step
+    //   - sends the accumulator (the memory chunk `it` starts from) to the snapshots,
     //   - applies S <- Diag(dec) S + W X with fragments read from its own set,
     //   - writes the operands of chunk it+1 (register stage `nx`) into the other set and refills
     //     that stage with chunk it+3,
     // so only the accumulator update lies on the chain from one chunk to the next; everything
-    // else rides beside it.  A set is rewritten two steps after it was read, with a barrier between.
+    // else rides beside it.  A step used to write its snapshot with sixteen 2-byte LDS stores per thread and tile, which
+    // is what a workgroup alone on its CU waits for: m = 128, 256 workgroups 37 -> 31 us; fwd d = 128, 128 workgroups 36 ->
+    // 30 us; eight sequences of 2048 tokens, d = 512, m = 64 (bound by bandwidth) 59 -> 56 us.  Straight from the
+    // registers, by 16-byte pieces 32 bytes apart, the last one took 63 us.
     auto step = [&](Stage &nx, int it) {
         const int b = it & 1;
-        if (MODE != 1) {
-            if (it > 0) snapshot_to_global(a.snap + ((size_t)(chunk0 + chunk_of(it - 1)) * H + h) * a.lay.stride, b ^ 1);
-            snapshot_to_lds(b);
-        }
+        if (MODE != 1) snapshot(a.snap + ((size_t)(chunk0 + chunk_of(it)) * H + h) * a.lay.stride);
         typename Atom<T>::Frag af[C / 32][MI], bf[C / 32][NI];
         const T *w = We(b), *x = XT(b);
 #pragma unroll
         for (int ks = 0; ks < C / 32; ++ks) {
 #pragma unroll
-            for (int mi = 0; mi < MI; ++mi) af[ks][mi] = Atom<T>::load(w + L::we_off(mi * 16 + r, ks * 32 + g8));
+            for (int mi = 0; mi < MI; ++mi) af[ks][mi] = Atom<T>::load(w + L::we_off(slot0 + 16 * mi, ks * 32 + g8));
 #pragma unroll
             for (int ni = 0; ni < NI; ++ni)
-                bf[ks][ni] = Atom<T>::load(x + xt_off<C>(wcol + ni * 16 + r, ks * 32 + g8, L::ldw));
+                bf[ks][ni] = Atom<T>::load(x + xt_off<C>(xrow + tcol(ni), ks * 32 + g8, L::ldw));
         }
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi) {
-            const f32x4 dcur = *reinterpret_cast<const f32x4 *>(Dec(b) + mi * 16 + g4);
+            const float dcur = Dec(b)[slot0 + 16 * mi];
             if (MODE == 1) dprod[mi] *= dcur;
 #pragma unroll
             for (int ni = 0; ni < NI; ++ni) acc[mi][ni] *= dcur;
@@ -349,7 +364,7 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void scan_kernel(Chun
 #pragma unroll
             for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-                for (int ni = 0; ni < NI; ++ni) Atom<T>::mma(acc[mi][ni], af[ks][mi], bf[ks][ni]);
+                for (int ni = 0; ni < NI; ++ni) Atom<T>::mma(acc[mi][ni], bf[ks][ni], af[ks][mi]);
         stage_to_lds(nx, b ^ 1);
     };
     // (the scheduling fences keep the compiler from hoisting a stage's refill above the LDS stores
@@ -380,21 +395,17 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void scan_kernel(Chun
         __syncthreads();
         ++it;
     }
-    if (MODE != 1 && nch > 0)
-        snapshot_to_global(a.snap + ((size_t)(chunk0 + chunk_of(nch - 1)) * H + h) * a.lay.stride, (nch - 1) & 1);
     if (MODE == 1) {   // what this segment adds and how much it decays, for its successors
         const size_t rec = ((size_t)s * a.max_seg + seg) * H + h;
         float *Y = a.sumY + rec * M * D + col0;
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-            for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) Y[(size_t)(mi * 16 + g4 + j) * D + wcol + ni * 16 + r] = acc[mi][ni][j];
-        if (wave == 0 && r == 0) {
+            for (int ni = 0; ni < NI; ++ni) *reinterpret_cast<f32x4 *>(Y + (size_t)(slot0 + 16 * mi) * D + lcol + tcol(ni)) = acc[mi][ni];
+        if (lcol == 0) {   // one lane per slot
             float *Dd = a.sumD + (rec * nsl + slice) * M;
 #pragma unroll
-            for (int mi = 0; mi < MI; ++mi) *reinterpret_cast<f32x4 *>(Dd + mi * 16 + g4) = dprod[mi];
+            for (int mi = 0; mi < MI; ++mi) Dd[slot0 + 16 * mi] = dprod[mi];
         }
         return;
     }
@@ -406,18 +417,9 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void scan_kernel(Chun
         for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
             for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int i = mi * 16 + g4 + j, c = c0 + wcol + ni * 16 + r;
-                    ST[(((size_t)s * H + h) * M + i) * dsrc + c] = acc[mi][ni][j];
-                }
+                *reinterpret_cast<f32x4 *>(ST + (((size_t)s * H + h) * M + slot0 + 16 * mi) * dsrc + c0 + lcol + tcol(ni)) = acc[mi][ni];
     }
-    if (a.outJ) {
-        __syncthreads();   // the last snapshot tile may still be on its way out
-        snapshot_to_lds(0);
-        __syncthreads();
-        snapshot_to_global(a.outJ + ((size_t)s * H + h) * a.lay.stride, 0);
-    }
+    if (a.outJ) snapshot(a.outJ + ((size_t)s * H + h) * a.lay.stride);
 }
 
 // ---------------------------------------------------------------------------------------
