@@ -307,6 +307,11 @@ def main():
         "chunk_intra_kernel": H * ((2 * dk + dv) * esz + 12 * m),
         "apply_bwd_kernel": H * 2 * (2 * dk + dv) * esz,
     }
+    # kernels that evaluate the wide contractions themselves touch the apply kernel's tensors as well
+    if "apply_fwd_kernel" not in kern_ms:
+        per_tok["chunk_fwd_kernel"] += per_tok["apply_fwd_kernel"]
+    if "apply_bwd_kernel" not in kern_ms:
+        per_tok["chunk_intra_kernel"] += H * 2 * (dk + dv) * esz   # dO in, dq, dk, dv out
     alg_bytes = {n: b * tokens for n, b in per_tok.items()}
     dom = max((n for n in kern_ms if n in alg_bytes), key=lambda n: kern_ms[n])
     achieved = alg_bytes[dom] / (kern_ms[dom] * 1e-3) / 1e9

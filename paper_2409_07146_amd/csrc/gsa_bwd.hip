@@ -28,6 +28,7 @@
 // Bm, A2, ds, dg and the small operand matrices), apply (gsa_apply.hip: dq, dk, dv).
 #include "gsa_chunk.h"
 #include "gsa_launch.h"
+#include "gsa_wide.h"
 
 namespace gsa {
 
@@ -181,7 +182,11 @@ template <typename T> __device__ __forceinline__ float frag_dot(const typename A
     return d;
 }
 
-template <typename T, int M> struct IntraLds {
+// By value: a conditional expression over variables selects their addresses, which keeps them in memory.
+template <typename P> __device__ __forceinline__ P pick(bool c, P x, P y) { return c ? x : y; }
+
+// WIDE: the wide contractions follow in the same kernel, small matrices in LDS.
+template <typename T, int M, bool WIDE> struct IntraLds {
     static constexpr int C = Geo<T>::C;
     static constexpr int PAD = Atom<T>::kPad;
     static constexpr int KM = (M < 32) ? 32 : M;
@@ -189,8 +194,13 @@ template <typename T, int M> struct IntraLds {
     static constexpr size_t oVn = 0;                                  // Vn [C][ldn]
     static constexpr size_t oUd = oVn + sizeof(T) * C * ldn;          // Ud [M][ldt]
     static constexpr size_t oUp = oUd + sizeof(T) * M * ldt;          // Up [M][ldt]
-    static constexpr size_t oRb = oUp + sizeof(T) * M * ldt;          // Rb, Rd, Rr, dGam totals: [C/16][M] fp32 each
-    static constexpr size_t end = oRb + 4 * sizeof(float) * (C / 16) * M;
+    static constexpr size_t tiles = oUp + sizeof(T) * M * ldt;
+    // Rb, Rd, Rr, dGam totals: [C/16][M] fp32 each, behind the first buffer of the wide contractions (they are read
+    // until that buffer has been written)
+    static constexpr size_t oRb = (WIDE && tiles < Wide<M>::szBuf) ? Wide<M>::szBuf : tiles;
+    static constexpr size_t endR = oRb + 4 * sizeof(float) * (C / 16) * M;
+    static constexpr size_t oMat = (WIDE && endR < 2 * Wide<M>::szBuf) ? 2 * Wide<M>::szBuf : endR;   // Bm, Bm^T, A2^T, scale*dz*exp(G), s*exp(G_C-G)
+    static constexpr size_t end = oMat + (WIDE ? 3 * Wide<M>::szTok + 2 * Wide<M>::szSlot : 0);
     static constexpr int kRpr = 2;        // row blocks per round of the reduction
     static constexpr size_t szRed = sizeof(f32x4) * kWave * (C / 16) *
                                     reduce_fragments<C / 16, C / 16 + M / 16, C / 16, kRpr, true>();   // from offset 0: dead before the tiles are written
@@ -205,18 +215,20 @@ template <typename T> struct IntraArgs {
     StateLayout lay;
     const T *tAvT, *tAvLo;   // bf16: product and rest
     float *dg;
-    T *tB, *tBT, *tA2T, *tDZe, *tSbe;
+    T *tB, *tBT, *tA2T, *tDZe, *tSbe;   // for the apply kernel (not WIDE)
+    const T *dO;                        // WIDE
+    T *dq, *dk, *dv;                    // WIDE
     const float *sin;   // general form: write intensities, or NULL
     float *ds;          // general form: their gradient (with sin)
     int readout;
     float gate_tau;     // general form: > 0 when g holds gate logits
 };
 
-template <typename T, int M, bool GEN, bool PHI>
+template <typename T, int M, bool GEN, bool PHI, bool WIDE>
 __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kernel(ChunkMap cm, int H, int d_k, int d_v, float scale,
                                                                  IntraArgs<T> a)
 {
-    using L = IntraLds<T, M>;
+    using L = IntraLds<T, M, WIDE>;
     constexpr int C = Geo<T>::C, NW = Geo<T>::NW;
     constexpr int MI = M / 16, CI = C / 16, KM = L::KM;
     constexpr int NB = CI + MI;
@@ -296,7 +308,7 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
 #pragma unroll
             for (int hh = 0; hh < 2; ++hh)
 #pragma unroll
-                for (int ni = 0; ni < CI; ++ni) fq[hh][ni] = Atom<T>::load_nt(qb + tk[ni] + kk + 32 * hh);
+                for (int ni = 0; ni < CI; ++ni) fq[hh][ni] = WIDE ? Atom<T>::load(qb + tk[ni] + kk + 32 * hh) : Atom<T>::load_nt(qb + tk[ni] + kk + 32 * hh);
 #pragma unroll
             for (int hh = 0; hh < 2; ++hh)
 #pragma unroll
@@ -512,7 +524,17 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
         if (GEN && given && live) *reinterpret_cast<f32x4 *>(a.ds + row + ni * 16) = ds[ni];
     }
     // ---- phase 2c: the slot-side operand of dk and dv, s*exp(G_C - G)
-    T *dS = a.tSbe + ch * C * KM + (size_t)t * KM, *dD = a.tDZe + ch * C * KM + (size_t)t * KM;
+    // (the five small matrices stay in LDS when the wide contractions follow here)
+    constexpr int lda = WIDE ? Wide<M>::lda : C, lds = WIDE ? Wide<M>::lds : KM;
+    T *mB = a.tB + ch * C * C, *mBT = a.tBT + ch * C * C, *mA2T = a.tA2T + ch * C * C, *mD = a.tDZe + ch * C * KM, *mS = a.tSbe + ch * C * KM;
+    if constexpr (WIDE) {
+        mB = reinterpret_cast<T *>(smem + L::oMat);
+        mBT = mB + C * lda;
+        mA2T = mBT + C * lda;
+        mD = mA2T + C * lda;
+        mS = mD + C * lds;
+    }
+    T *dS = mS + (size_t)t * lds, *dD = mD + (size_t)t * lds;
 #pragma unroll
     for (int ni = 0; ni < MI; ++ni) {
         f32x4 y;
@@ -524,6 +546,24 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
         store_frag16<T>(dS + ni * 16 + g4, y);
     }
     if (M < KM) store_frag16<T>(dS + M + g4, f32x4{0.f, 0.f, 0.f, 0.f});   // the padded slot columns
+    typedef Wide<M> W;
+    typename W::Stage sa, sb;
+    const int nk = d_k / 64, units = 2 * nk + d_v / 64;
+    const T *const SK = a.S + ch * a.lay.stride + a.lay.oK;
+    const T *const tk0 = a.k + tokh * d_k, *const tk1 = a.q + tokh * d_k, *const tk2 = a.dO + tokh * d_v;
+    T *const to0 = a.dq + tokh * d_k, *const to1 = a.dk + tokh * d_k, *const to2 = a.dv + tokh * d_v;
+    auto unit = [=](int i) {   // i is uniform over the workgroup
+        const bool isq = i < nk, isv = i >= 2 * nk;
+        const int c = 64 * (isq ? i : isv ? i - 2 * nk : i - nk), d = isv ? d_v : d_k;
+        const T *slot = pick(isq, SK, pick(isv, EV, EK)), *tok = pick(isq, tk0, pick(isv, tk2, tk1));
+        T *out = pick(isq, to0, pick(isv, to2, to1));
+        return typename W::Unit{(const bf16_t *)(slot + (size_t)c * M), (const bf16_t *)(tok + c), (bf16_t *)(out + c), (size_t)H * d,
+                                (const bf16_t *)pick(isq, mB, pick(isv, mA2T, mBT)), (const bf16_t *)pick(isq, mD, mS)};
+    };
+    if constexpr (WIDE) {   // the first two units' tiles land during the rest of phase 2
+        W::fetch(sa, unit(0), ci.len, tid);
+        W::fetch(sb, unit(1), ci.len, tid);
+    }
     // ---- phase 2d: Bm (both orientations) and A2^T, row t of this wave's block, one column block after the
     // other as in the forward; `wd` ends as the slot-side operand of dq, scale*dz*exp(G)
 #pragma unroll
@@ -534,7 +574,7 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
             wd[ni][j] *= e;
             p[ni][j] *= e;
         }
-    T *dB = a.tB + ch * C * C + (size_t)t * C, *dBT = a.tBT + ch * C * C + rowb, *dA2T = a.tA2T + ch * C * C + rowb;
+    T *dB = mB + (size_t)t * lda, *dBT = mBT + rowb, *dA2T = mA2T + rowb;
 #pragma unroll
     for (int b = CI - 1; b >= 0; --b) {
         const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
@@ -542,8 +582,8 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
         if (b == w && unsafe) {   // weights are already at the start of the block
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                dBT[(size_t)(b * 16 + g4 + j) * C + r] = from_f32<T>(exb[j]);
-                dA2T[(size_t)(b * 16 + g4 + j) * C + r] = from_f32<T>(exa[j]);
+                dBT[(size_t)(b * 16 + g4 + j) * lda + r] = from_f32<T>(exb[j]);
+                dA2T[(size_t)(b * 16 + g4 + j) * lda + r] = from_f32<T>(exa[j]);
             }
             store_frag16<T>(dB + b * 16 + g4, exb);
             continue;
@@ -566,8 +606,8 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
             }
         }
         store_frag16<T>(dB + b * 16 + g4, xb);
-        store_frag16<T>(dBT + (size_t)(b * 16 + r) * C + g4, xbt);
-        store_frag16<T>(dA2T + (size_t)(b * 16 + r) * C + g4, xat);
+        store_frag16<T>(dBT + (size_t)(b * 16 + r) * lda + g4, xbt);
+        store_frag16<T>(dA2T + (size_t)(b * 16 + r) * lda + g4, xat);
     }
 #pragma unroll
     for (int ni = 0; ni < MI; ++ni) store_frag16<T>(dD + ni * 16 + g4, wd[ni]);
@@ -589,6 +629,11 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
             for (int j = 0; j < 4; ++j) x[j] *= log_gate_slope(u[j], a.gate_tau);
         }
         if (live) *reinterpret_cast<f32x4 *>(a.dg + row + ni * 16) = x;
+    }
+    // ---- phase 3: dq, dk, dv (B=8, T=2048, H=4, d=512, m=64: 131 us and a kernel of its own of 102 us -> 200 us)
+    if constexpr (WIDE) {
+        if (ci.len == C) W::template walk<true>(unit, units, sa, sb, smem, ci.len, tid);
+        else W::template walk<false>(unit, units, sa, sb, smem, ci.len, tid);
     }
 }
 
@@ -629,12 +674,19 @@ static hipError_t launch_bwd_tm(const Plan &pl, const Work &w, const void *q, co
         const ScanIo io = {q, dO, dKT, dVT, dK0, dV0, nullptr, true, pl.phi != 0, false};
         GSA_HIP_TRY(launch_scan(pl, w, io, st));
     }
-    // 4. everything chunk-local except the wide contractions
+    // 4. everything chunk-local, and in bf16 without the feature map the wide contractions as well.  One workgroup
+    // then walks all 64-column units of its (chunk, head), which takes longer than a kernel of its own where few
+    // pairs are left to fill the chip: without / with them inside (backward call, m = 64): 64 pairs of d = 512 (24
+    // units) 92 / 98 us, 96 pairs 110 / 111, 128 pairs 119 / 117, 512 pairs 214 / 193, 1024 pairs 411 / 373; d = 1024 (48
+    // units) 128 pairs 153 / 159, 192 pairs 188 / 185; d = 128 (6 units) 32 pairs 56 / 54.
+    const int64_t pairs = (int64_t)pl.chunk_slots * pl.H;
+    const bool wide = sizeof(T) == 2 && !pl.phi && pairs >= 4 * (2 * pl.d_k + pl.d_v) / 64;
     {
-        auto kern = !pl.general() ? chunk_intra_kernel<T, M, false, false>
-                    : pl.phi     ? chunk_intra_kernel<T, M, true, true>
-                                 : chunk_intra_kernel<T, M, true, false>;
-        const size_t lds = IntraLds<T, M>::bytes;
+        constexpr bool kWide = sizeof(T) == 2;
+        auto kern = pl.phi          ? chunk_intra_kernel<T, M, true, true, false>
+                    : pl.general() ? (wide ? chunk_intra_kernel<T, M, true, false, kWide> : chunk_intra_kernel<T, M, true, false, false>)
+                                   : (wide ? chunk_intra_kernel<T, M, false, false, kWide> : chunk_intra_kernel<T, M, false, false, false>);
+        const size_t lds = wide ? IntraLds<T, M, sizeof(T) == 2>::bytes : IntraLds<T, M, false>::bytes;
         GSA_HIP_TRY(allow_lds(kern, lds));
         IntraArgs<T> a;
         a.q = (const T *)q; a.k = (const T *)k; a.v = (const T *)v;
@@ -643,6 +695,8 @@ static hipError_t launch_bwd_tm(const Plan &pl, const Work &w, const void *q, co
         a.lay = pl.lay;
         a.tAvT = (const T *)w.tAvT;
         a.tAvLo = (const T *)w.tBT;
+        a.dO = (const T *)dO;
+        a.dq = (T *)dq; a.dk = (T *)dk; a.dv = (T *)dv;
         a.dg = dg;
         a.tB = (T *)w.tA; a.tBT = (T *)w.tBT; a.tA2T = (T *)w.tA2T; a.tDZe = (T *)w.tP; a.tSbe = (T *)w.tSbe;
         a.sin = pl.s_in; a.ds = pl.ds_out; a.readout = pl.readout; a.gate_tau = pl.gate_tau;
@@ -650,6 +704,7 @@ static hipError_t launch_bwd_tm(const Plan &pl, const Work &w, const void *q, co
         hipLaunchKernelGGL(kern, grid, dim3(Geo<T>::NT), lds, st, cm, pl.H, pl.d_k, pl.d_v, pl.scale, a);
         GSA_HIP_TRY(hipGetLastError());
     }
+    if (wide) return hipSuccess;
     // 5. dq, dk, dv (with the feature map: through its slope at the raw q, k, v)
     const bool phi = pl.phi != 0;
     const ApplyIo io[3] = {

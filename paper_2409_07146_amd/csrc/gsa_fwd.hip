@@ -17,6 +17,7 @@
 //   apply_kernel      (gsa_apply.hip) o = (p e^G) Vt_start + A2 V, the wide contraction.
 #include "gsa_chunk.h"
 #include "gsa_launch.h"
+#include "gsa_wide.h"
 
 namespace gsa {
 
@@ -85,7 +86,8 @@ hipError_t launch_prepare(const Plan &pl, const Work &w, hipStream_t st)
 // instructions per wave): B=8, T=2048, H=4, m=64, bf16: d=512 66 -> 56 us, d=128 43 -> 31 us; one sequence of 2048
 // tokens, d=512: 21.6 -> 16.6 us; T=256, d=64, m=16, fp32: 9 -> 5.4 us.
 // ---------------------------------------------------------------------------------------
-template <typename T, int M> struct ChunkFwdLds {
+// WIDE: the wide contraction follows in the same kernel, small matrices in LDS.
+template <typename T, int M, bool WIDE> struct ChunkFwdLds {
     static constexpr int C = Geo<T>::C;
     static constexpr int PAD = Atom<T>::kPad;
     static constexpr int KM = (M < 32) ? 32 : M;   // slots padded to the contraction depth of the apply kernel
@@ -93,7 +95,9 @@ template <typename T, int M> struct ChunkFwdLds {
     static constexpr size_t oVn = 0;                                  // Vn [C][ldn]
     static constexpr size_t oVt = oVn + sizeof(T) * C * ldn;          // Vt [M][ldt]
     static constexpr size_t oRb = oVt + sizeof(T) * M * ldt;          // Rb [C/16][M] fp32
-    static constexpr size_t end = oRb + sizeof(float) * (C / 16) * M;
+    static constexpr size_t endR = oRb + sizeof(float) * (C / 16) * M;
+    static constexpr size_t oMat = (WIDE && endR < 2 * Wide<M>::szBuf) ? 2 * Wide<M>::szBuf : endR;   // A2, p*exp(G)
+    static constexpr size_t end = oMat + (WIDE ? Wide<M>::szTok + Wide<M>::szSlot : 0);
     static constexpr int kRpr = 2;                 // row blocks per round of the reduction
     static constexpr size_t szRed = sizeof(f32x4) * kWave * (C / 16) *
                                     reduce_fragments<C / 16, C / 16 + M / 16, C / 16, kRpr>();   // from offset 0: dead before the tiles are written
@@ -102,16 +106,17 @@ template <typename T, int M> struct ChunkFwdLds {
 
 // GEN: the general form (write intensities from `sin` when it is not NULL; opts: read-out in the low
 // byte).  PHI (with GEN): the feature map on q and k.
-template <typename T, int M, bool GEN, bool PHI>
+template <typename T, int M, bool GEN, bool PHI, bool WIDE>
 __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_fwd_kernel(ChunkMap cm, int H, int d_k, float scale,
                                                                const T *__restrict__ q, const T *__restrict__ k,
                                                                const float *__restrict__ g,
                                                                const T *__restrict__ S, StateLayout lay,
                                                                float *__restrict__ z_saved, T *__restrict__ tA,
                                                                T *__restrict__ tP, const float *__restrict__ sin,
-                                                               int opts, float gate_tau)
+                                                               int opts, float gate_tau, int d_v,
+                                                               const T *__restrict__ v, T *__restrict__ o)
 {
-    using L = ChunkFwdLds<T, M>;
+    using L = ChunkFwdLds<T, M, WIDE>;
     const int readout = opts & kReadoutMask;
     constexpr int C = Geo<T>::C;
     constexpr int MI = M / 16, CI = C / 16, KM = L::KM;
@@ -162,7 +167,24 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_fwd_kernel
     // ---- pass-2 pair weights A2[t][r] = sum_i p_t[i] s_r[i] exp(G_t[i] - G_r[i]), r <= t: row t of this wave's
     // block, one column block after the other, nearest first; `p` walks its reference backwards with them and
     // ends as the inter-chunk weights p * exp(G)
-    T *dA = tA + ch * C * C + (size_t)t * C, *dP = tP + ch * C * KM + (size_t)t * KM;
+    constexpr int lda = WIDE ? Wide<M>::lda : C, lds = WIDE ? Wide<M>::lds : KM;
+    T *mA = tA + ch * C * C, *mP = tP + ch * C * KM;
+    typedef Wide<M> W;
+    typename W::Stage sa, sb;
+    const T *const Vs = S + ch * lay.stride + lay.oV, *const vt = v + tokh * d_v;
+    T *const ot = o + tokh * d_v;
+    auto unit = [=](int i) {   // columns 64*i .. of o; i is uniform over the workgroup
+        return typename W::Unit{(const bf16_t *)(Vs + (size_t)64 * i * M), (const bf16_t *)(vt + 64 * i), (bf16_t *)(ot + 64 * i), (size_t)H * d_v,
+                                (const bf16_t *)(smem + L::oMat), (const bf16_t *)(smem + L::oMat + W::szTok)};
+    };
+    const int units = d_v / 64;
+    if constexpr (WIDE) {   // the first two units' tiles land during what follows
+        mA = reinterpret_cast<T *>(smem + L::oMat);
+        mP = reinterpret_cast<T *>(smem + L::oMat + W::szTok);
+        W::fetch(sa, unit(0), ci.len, tid);
+        W::fetch(sb, unit(min(1, units - 1)), ci.len, tid);
+    }
+    T *dA = mA + (size_t)t * lda, *dP = mP + (size_t)t * lds;
     f32x4 exact = {0.f, 0.f, 0.f, 0.f};
     if (unsafe) exact = pair_tile_exact<M, GEN>(p, bg, lane);
 #pragma unroll
@@ -190,6 +212,12 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_fwd_kernel
 #pragma unroll
     for (int ni = 0; ni < MI; ++ni) store_frag16<T>(dP + ni * 16 + g4, p[ni]);
     if (M < KM) store_frag16<T>(dP + M + g4, f32x4{0.f, 0.f, 0.f, 0.f});   // the padded slot columns
+    // ---- pass 2: o = A2 V + (p * exp(G)) Vt_start (B=8, T=2048, H=4, d=512, m=64: 57 us and a kernel of its own of 40 us -> 86 us)
+    if constexpr (WIDE) {
+        __syncthreads();   // the small matrices are whole, and the tiles they were made from are dead
+        if (ci.len == C) W::template walk<true>(unit, units, sa, sb, smem, ci.len, tid);
+        else W::template walk<false>(unit, units, sa, sb, smem, ci.len, tid);
+    }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -207,19 +235,26 @@ static hipError_t launch_fwd_tm(const Plan &pl, const Work &w, const void *q, co
         const ScanIo io = {k, v, K0, V0, KT, VT, pl.keep ? w.SF : nullptr, false, pl.phi != 0, pl.phi != 0};
         GSA_HIP_TRY(launch_scan(pl, w, io, st));
     }
+    // bf16 without the feature map and the output epilogue: the wide contraction follows in the chunk kernel.  Forward
+    // call with a kernel of its own / inside, m = 64: d = 512, 64 (chunk, head) pairs 43.0 / 43.3 us, 512 pairs 90 / 79, 1024
+    // pairs 156 / 146; d = 128, 1024 pairs 80 / 73; but d = 1024 with 1536 pairs 410 / 428 (512 pairs: 148 / 143).
+    const bool wide = sizeof(T) == 2 && !pl.phi && !pl.act_out && !pl.act_ssq &&
+                      (pl.d_v <= 768 || (int64_t)pl.chunk_slots * pl.H <= 512);
     {
-        auto kern = !pl.general() ? chunk_fwd_kernel<T, M, false, false>
-                    : pl.phi     ? chunk_fwd_kernel<T, M, true, true>
-                                 : chunk_fwd_kernel<T, M, true, false>;
-        const size_t lds = ChunkFwdLds<T, M>::bytes;
+        constexpr bool kWide = sizeof(T) == 2;
+        auto kern = pl.phi          ? chunk_fwd_kernel<T, M, true, true, false>
+                    : pl.general() ? (wide ? chunk_fwd_kernel<T, M, true, false, kWide> : chunk_fwd_kernel<T, M, true, false, false>)
+                                   : (wide ? chunk_fwd_kernel<T, M, false, false, kWide> : chunk_fwd_kernel<T, M, false, false, false>);
+        const size_t lds = wide ? ChunkFwdLds<T, M, kWide>::bytes : ChunkFwdLds<T, M, false>::bytes;
         GSA_HIP_TRY(allow_lds(kern, lds));
         dim3 grid(pl.chunk_slots, pl.H);
         KernelTimer kt(kSlotChunkFwd, st);
         hipLaunchKernelGGL(kern, grid, dim3(Geo<T>::NT), lds, st, cm, pl.H, pl.d_k, pl.scale, (const T *)q,
                            (const T *)k, g, (const T *)w.S, pl.lay, z_saved, (T *)w.tA, (T *)w.tP, pl.s_in,
-                           pl.opts(), pl.gate_tau);
+                           pl.opts(), pl.gate_tau, pl.d_v, (const T *)v, (T *)o);
         GSA_HIP_TRY(hipGetLastError());
     }
+    if (wide) return hipSuccess;
     ApplyIo io = {w.tA, w.tP, v, w.S, pl.lay.oV, pl.lay.stride, o, pl.d_v, pl.phi != 0, nullptr};
     io.act = pl.act_out;
     io.ssq = pl.act_ssq;
