@@ -22,7 +22,7 @@ class GsaError(RuntimeError):
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()   # the argument types make it a pointer
 
 
 def _check(t, name, dtype=None, shape=None, optional=False):
@@ -30,6 +30,9 @@ def _check(t, name, dtype=None, shape=None, optional=False):
         if optional:
             return
         raise ValueError("%s is required" % name)
+    # the usual case first: a decode step makes seven of these checks in the time its kernels run
+    if t.shape == shape and t.dtype == dtype and t.is_cuda and t.is_contiguous():
+        return
     if not t.is_cuda:
         raise ValueError("%s must live on the GPU" % name)
     if not t.is_contiguous():
@@ -41,7 +44,7 @@ def _check(t, name, dtype=None, shape=None, optional=False):
 
 
 def _stream(t: torch.Tensor):
-    return ctypes.c_void_p(torch.cuda.current_stream(t.device).cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(t.device.index)   # without building a Stream object per call
 
 
 def make_problem(q, v, g, scale=1.0, cu_seqlens=None, keep_states=False):
