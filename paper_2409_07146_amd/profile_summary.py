@@ -139,8 +139,8 @@ def main():
         dur = kernel_trace(args.kernel_trace)
         total = sum(sum(v) for v in dur.values())
         note = args.trace_note or (
-            "Per step the forward launches gate, scan(forward), chunk_fwd, apply; the backward launches gate,\n"
-            "scan(forward), chunk_dz, scan(reverse), chunk_intra, apply (dq, dk, dv in one launch).  scan(forward)\n"
+            "Per step the forward launches gate, scan(forward), chunk_fwd; the backward launches gate,\n"
+            "scan(forward), chunk_dz, scan(reverse), chunk_intra (the wide contractions inside).  scan(forward)\n"
             "therefore appears twice per step; its average mixes the forward's and the backward's launch.  The run\n"
             "also times the steps without recomputation, the decode steps and the 256 MiB copy probe.")
         with open(os.path.join(args.out, args.trace_name or "%s_fwd_bwd_kernel_trace.txt" % wl), "w") as f:
