@@ -25,7 +25,8 @@
 // Kernels of one backward call: gate + forward scan (gsa_scan.hip; recompute the chunk-start
 // memories, since nothing but z was saved by the forward), chunk_dz (chunk-parallel: dp, dz,
 // weights of the reverse scan), reverse scan (gsa_scan.hip: E), chunk_intra (chunk-parallel:
-// Bm, A2, ds, dg and the small operand matrices), apply (gsa_apply.hip: dq, dk, dv).
+// Bm, A2, ds, dg and, in bf16, dq, dk, dv from them: gsa_wide.h), or apply (gsa_apply.hip: dq,
+// dk, dv from matrices in memory; the rule stands at the launch).
 #include "gsa_chunk.h"
 #include "gsa_launch.h"
 #include "gsa_wide.h"

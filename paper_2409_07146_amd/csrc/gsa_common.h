@@ -376,7 +376,7 @@ __device__ __forceinline__ float write_intensity(float x)
 template <int M, int NT, int C, bool GEN = false> struct GatePrep {
     static constexpr int P = NT / M;     // token partitions
     static constexpr int TP = C / P;     // tokens per partition
-    static_assert(NT % M == 0 && C % P == 0, "gate_prep partitioning");
+    static_assert(NT % M == 0 && C % P == 0, "slots and tokens split evenly over the threads");
     float gv[TP];
     float sv[GEN ? TP : 1];
     bool given = false;

@@ -14,7 +14,10 @@
 //                     registers, and the two small matrices of pass 2: p*exp(G) [C x m] and
 //                     the pair weights A2 [C x C].  z and p never round-trip HBM except for
 //                     the z the backward needs.
-//   apply_kernel      (gsa_apply.hip) o = (p e^G) Vt_start + A2 V, the wide contraction.
+//                     In bf16 o = (p e^G) Vt_start + A2 V, the wide contraction, follows in the
+//                     same kernel (gsa_wide.h).
+//   apply_kernel      (gsa_apply.hip) the wide contraction where it does not (fp32, feature map,
+//                     output epilogue).
 #include "gsa_chunk.h"
 #include "gsa_launch.h"
 #include "gsa_wide.h"
