@@ -210,7 +210,7 @@ template <int M, bool GEN> struct BlockGates {
                 float x = L[ni][j];
                 if (GEN && tau > 0.f) x = log_gate_from_logit(x, tau);
                 x = live ? fmaxf(x, kGateFloor) : 0.f;
-                const float sx = (GEN && given) ? s[ni][j] : write_intensity(x);
+                const float sx = (GEN && given) ? s[ni][j] : -expm1f(x);
                 s[ni][j] = live ? sx : 0.f;
                 x = row16_prefix_sum(x);
                 L[ni][j] = x;

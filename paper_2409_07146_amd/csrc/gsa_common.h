@@ -350,23 +350,6 @@ __device__ __forceinline__ float log_gate_from_logit(float u, float tau)
 }
 __device__ __forceinline__ float log_gate_slope(float u, float tau) { return 1.f / ((1.f + __expf(u)) * tau); }
 
-// Write intensity 1 - exp(x) of a log gate x in [kGateFloor, 0]: the Taylor series of expm1 to x^9 above -0.5 (its
-// remainder is below 1e-9 there), the plain difference below (at most 1 + exp(x) half units in the last place lost).
-// About 14 vector instructions; the library's expm1f is about 25.
-__device__ __forceinline__ float write_intensity(float x)
-{
-    float p = 1.f / 362880.f;
-    p = fmaf(p, x, 1.f / 40320.f);
-    p = fmaf(p, x, 1.f / 5040.f);
-    p = fmaf(p, x, 1.f / 720.f);
-    p = fmaf(p, x, 1.f / 120.f);
-    p = fmaf(p, x, 1.f / 24.f);
-    p = fmaf(p, x, 1.f / 6.f);
-    p = fmaf(p, x, 0.5f);
-    p = fmaf(p, x, 1.f);
-    return x > -0.5f ? -x * p : 1.f - __expf(x);
-}
-
 // Gates of one slot's run of tokens in a chunk-wide layout: thread tid owns slot tid % M and the C / P tokens
 // from (tid / M) * C / P on.  Log gates are floored at kGateFloor, rows past the end of the chunk are g = 0, s = 0.
 // GEN: the general form, in which the write intensity may come from an array of its own
@@ -402,7 +385,7 @@ template <int M, int NT, int C, bool GEN = false> struct GatePrep {
         float graw = gv[tt];
         if (GEN && tau > 0.f) graw = log_gate_from_logit(graw, tau);
         x = live ? fmaxf(graw, kGateFloor) : 0.f;
-        sx = write_intensity(x);
+        sx = -expm1f(x);   // as in the decode step: a memory is handed from one to the other
         if (GEN && given) sx = sv[GEN ? tt : 0];
         sx = live ? sx : 0.f;
     }
