@@ -46,6 +46,7 @@ template <typename T, int M> struct DzLds {
     static constexpr size_t oX = oRb + sizeof(float) * (C / 16) * M;  // per wave: [kRows][ldx], transposing scratch
     static constexpr int kRows = 2 * M + (sizeof(T) == 2 ? 2 : 1) * C;   // the products' roundings leave a rest in bf16
     static constexpr size_t szX = sizeof(T) * kRows * ldx;
+    static_assert(kRows * ldx >= kPrivate<T, M>, "gated_rows' scratch");
     static constexpr size_t end = oX + szX * (C / 16);
     static constexpr int kRpr = 2;                 // row blocks per round of the reduction
     static constexpr size_t szRed = sizeof(f32x4) * kWave * (C / 16) *
@@ -97,10 +98,11 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_dz_kernel(
 #pragma unroll
             for (int ni = 0; ni < MI; ++ni) zv[ni] = *reinterpret_cast<const f32x4 *>(z + row + ni * 16);
         });
-    const bool unsafe = bg.finish(ci.len, rowb, lane);
+    bg.finish(ci.len, rowb, lane);
     bg.template write_tiles<T>(nullptr, 0, Vt, L::ldt, Rb, rowb, lane);
+    T *X = reinterpret_cast<T *>(smem + L::oX + (size_t)w * L::szX);   // this wave's scratch
     __syncthreads();
-    gated_rows<T, M, C, GEN>(dp, a, alo, bg, unsafe, Vt, L::ldt, Rb, lane, w);
+    gated_rows<T, M, C, GEN>(dp, a, alo, bg, Vt, L::ldt, Rb, X, lane, w);
     // slope*(dp - pdp) is dz: p and <p,dp> for the softmax, f'(z) and 0 for an element-wise read-out
     f32x4 p[MI], slope[MI];
     float pdp = 0.f;
@@ -128,7 +130,7 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_dz_kernel(
     // dz, dgf for the intra kernel; gate-weighted transposes (scale*dz*exp G, p*exp G) for the reverse scan and
     // the causally masked (dO_t . v_r), transposed, for the intra kernel's ds contraction.  The three are
     // token-fastest in memory: this wave's 16 tokens of every row meet in its own piece of LDS first.
-    T *X = reinterpret_cast<T *>(smem + L::oX + (size_t)w * L::szX);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // gated_rows has read what it kept there
 #pragma unroll
     for (int ni = 0; ni < MI; ++ni) {
         f32x4 pre = {1.f, 1.f, 1.f, 1.f};   // exp of the cumulative log gate before the block
@@ -432,9 +434,10 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
     // need goes to LDS (it overwrites the reduction buffer, which every wave has left by now): the
     // write-intensity tile Vn for the pair weights, and the tiles U = (scale*dz | p) * exp(L_t - ref) for ds.
     // ref lies halfway down the block's decay, so that neither U nor exp(ref - L_r) leaves fp32's range by
-    // more than e^40; a block too wide for that is referenced to its start, which serves the earlier blocks,
-    // and its own pairs are evaluated one by one.
-    const bool unsafe = bg.finish(ci.len, rowb, lane);
+    // more than e^40; a kPairs block is referenced to its start, which serves the earlier blocks, and its own pairs are
+    // evaluated one by one.
+    bg.finish(ci.len, rowb, lane);
+    const bool unsafe = bg.kind == kPairs;
     bg.template write_tiles<T>(Vn, L::ldn, nullptr, 0, Rb, rowb, lane);
     if (!GEN || a.readout == kReadSoftmax) {
         softmax_slots<M>(p);
@@ -486,7 +489,7 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
     for (int ni = 0; ni < MI; ++ni)
 #pragma unroll
         for (int j = 0; j < 4; ++j) ds[ni][j] *= __expf((unsafe ? 1.f : 0.5f) * bg.tot[ni][j] - bg.L[ni][j]);
-    f32x4 exb = {0.f, 0.f, 0.f, 0.f}, exa = {0.f, 0.f, 0.f, 0.f};   // diagonal pair weights, unfactored
+    f32x4 exb = {0.f, 0.f, 0.f, 0.f}, exa = {0.f, 0.f, 0.f, 0.f};   // diagonal pair weights of a block that is not kNarrow
     if (unsafe) {
         typename Atom<T>::Frag16 ownA = fa[0], ownAv = fav[0], ownLo = favlo[0];
 #pragma unroll
@@ -508,6 +511,10 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
             }
         exb = pair_tile_exact<M, GEN>(wd, bg, lane);
         exa = pair_tile_exact<M, GEN>(p, bg, lane);
+    }
+    if (bg.kind == kHalf) {
+        exb = pair_tile_half<T, M, GEN>(wd, bg, lane);
+        exa = pair_tile_half<T, M, GEN>(p, bg, lane);
     }
     // ---- phase 2b: the gate gradient inside the block, and the block's total for the earlier ones
     f32x4 dg[MI];
@@ -571,7 +578,7 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
     for (int ni = 0; ni < MI; ++ni)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const float e = __expf(unsafe ? bg.L[ni][j] : bg.L[ni][j] - bg.tot[ni][j]);
+            const float e = bg.walk_gate(ni, j);
             wd[ni][j] *= e;
             p[ni][j] *= e;
         }
@@ -580,7 +587,7 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
     for (int b = CI - 1; b >= 0; --b) {
         const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
         f32x4 xb = zero, xbt = zero, xat = zero;   // D[r][t]; D[t][r]
-        if (b == w && unsafe) {   // weights are already at the start of the block
+        if (b == w && bg.kind != kNarrow) {   // weights are already at the start of the block
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 dBT[(size_t)(b * 16 + g4 + j) * lda + r] = from_f32<T>(exb[j]);

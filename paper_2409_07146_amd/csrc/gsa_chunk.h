@@ -169,6 +169,7 @@ template <typename T> __device__ __forceinline__ void store_frag16(T *p, const f
 // Gates of one wave's row block (16 tokens, all slots), in D[slot][token] registers.
 //   L[ni][j]   = sum over the block's tokens up to and including t of g       (block-local, inclusive)
 //   tot[ni][j] = the same over the whole block (equal in the 16 lanes of a row)
+//   kind       = how far the block's widest slot decays (wave-uniform), which decides how its own pairs are weighted
 //   s[ni][j]   = write intensity, 0 on rows past the end of the chunk
 // What other waves need of them goes to LDS once (write_tiles): the write-intensity tile referenced to
 // the END of its block,
@@ -177,11 +178,19 @@ template <typename T> __device__ __forceinline__ void store_frag16(T *p, const f
 // exp(tot[i]).  The weight between a token t of block w and a token r of block b <= w is then
 //   exp(G_t - G_r) s_r = exp(L_t - tot_w) * (product of Rb over the blocks b+1 .. w) * V[r]
 // for the diagonal block as well: no operand of a gated contraction needs an exponential of its own, and
-// no exponential is evaluated twice.
+// no exponential is evaluated twice.  Of the diagonal block that holds while it is
+//   kNarrow (down to e^-40).  The two factors grow and shrink with the decay, and in
+//   kHalf (down to e^-80) blocks weights above 6e3 overflowed and products below 1e-4 underflowed: the wave that owns one
+//   references its diagonal halfway, exp(L_t - tot/2) * s_r exp(tot/2 - L_r), with operands of its own.  Neither factor
+//   leaves e^+-40 then, and what they multiply may lie anywhere in fp32's range but its outer 17 orders of magnitude.
+//   (Tokens of later blocks are all behind the decay: what underflows there is far below their own block's terms.)
+//   kPairs (wider): the block's own pairs are evaluated one by one with the unfactored exponent.
 // ----------------------------------------------------------------------------
+enum BlockKind { kNarrow = 0, kHalf = 1, kPairs = 2 };
 template <int M, bool GEN> struct BlockGates {
     static constexpr int MI = M / 16;
     f32x4 L[MI], s[MI], tot[MI];
+    int kind = kNarrow;
     bool given = false;
     float tau = 0.f;
     // Issues the loads (rows clamped into the chunk); may be called well before finish().
@@ -198,8 +207,7 @@ template <int M, bool GEN> struct BlockGates {
             for (int ni = 0; ni < MI; ++ni) s[ni] = *reinterpret_cast<const f32x4 *>(sin + off + ni * 16);
         }
     }
-    // Returns whether the factored form is unsafe for this block (wave-uniform).
-    __device__ __forceinline__ bool finish(int len, int rowb, int lane)
+    __device__ __forceinline__ void finish(int len, int rowb, int lane)
     {
         const bool live = rowb + (lane & 15) < len;
         float least = 0.f;
@@ -217,8 +225,13 @@ template <int M, bool GEN> struct BlockGates {
                 tot[ni][j] = row16_last(x);
                 least = fminf(least, tot[ni][j]);
             }
-        return __any(least < -kExpClamp);
+        kind = __any(least < -kExpClamp) ? kPairs : __any(least < -0.5f * kExpClamp) ? kHalf : kNarrow;
     }
+    // exp(L_t - ref) with ref the block's end where its diagonal uses the shared tile, else its start
+    __device__ __forceinline__ float walk_gate(int ni, int j) const { return __expf(kind == kNarrow ? L[ni][j] - tot[ni][j] : L[ni][j]); }
+    // kHalf: the two factors of the diagonal
+    __device__ __forceinline__ float half_read(int ni, int j) const { return __expf(L[ni][j] - 0.5f * tot[ni][j]); }
+    __device__ __forceinline__ float half_write(int ni, int j) const { return s[ni][j] * __expf(0.5f * tot[ni][j] - L[ni][j]); }
     template <typename T>
     __device__ __forceinline__ void write_tiles(T *Vn, int ldn, T *Vt, int ldt, float *Rb, int rowb, int lane) const
     {
@@ -339,24 +352,26 @@ __device__ __forceinline__ void contract_heads(f32x4 (&run)[M / 16], typename At
 }
 
 // Second part: the gated sum itself, from the tiles of contract_heads and of BlockGates::write_tiles (which
-// must be visible to all waves):
+// must be visible to all waves).  Vp: LDS, kPrivate<T, M> elements of this wave's own.
 //   run[ni][j] <- exp(G_t[i]) * <X_t, St[i]>  +  sum_{r<=t} <X_t, Y_r> s_r[i] exp(G_t[i]-G_r[i])
 // `run` walks its reference from the chunk start (where it is the inter-chunk term) to the end of this
-// wave's block, one block at a time: run <- run * Rb[b] + V_b^T a_b.
+// wave's block, one block at a time: run <- run * Rb[b] + V_b^T a_b.  (To its start where the diagonal is not kNarrow.)
+template <typename T, int M> constexpr int kPrivate = M * (16 + Atom<T>::kPad);
 template <typename T, int M, int C, bool GEN>
 __device__ __forceinline__ void gated_rows(f32x4 (&run)[M / 16], const typename Atom<T>::Frag16 (&a)[C / 16],
                                            const typename Atom<T>::Frag16 (&alo)[C / 16],
-                                           const BlockGates<M, GEN> &bg, bool unsafe, const T *Vt, int ldt,
-                                           const float *Rb, int lane, int w)
+                                           const BlockGates<M, GEN> &bg, const T *Vt, int ldt,
+                                           const float *Rb, T *Vp, int lane, int w)
 {
     constexpr int MI = M / 16, CI = C / 16;
     const int r = lane & 15, g4 = (lane >> 4) * 4;
-    typename Atom<T>::Frag16 own = a[0];
+    typename Atom<T>::Frag16 own = a[0], rest = alo[0];
 #pragma unroll
     for (int b = 0; b < CI; ++b) {
         if (b > w) continue;   // wave-uniform
         own = a[b];
-        if (b == w && unsafe) continue;
+        rest = alo[b];
+        if (b == w && bg.kind != kNarrow) continue;
 #pragma unroll
         for (int ni = 0; ni < MI; ++ni) {
             run[ni] *= *reinterpret_cast<const f32x4 *>(Rb + b * M + ni * 16 + g4);
@@ -368,8 +383,25 @@ __device__ __forceinline__ void gated_rows(f32x4 (&run)[M / 16], const typename 
 #pragma unroll
     for (int ni = 0; ni < MI; ++ni)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) run[ni][j] *= __expf(unsafe ? bg.L[ni][j] : bg.L[ni][j] - bg.tot[ni][j]);
-    if (unsafe) {   // the diagonal block pair by pair
+        for (int j = 0; j < 4; ++j) run[ni][j] *= bg.walk_gate(ni, j);
+    if (bg.kind == kHalf) {
+        constexpr int ldp = 16 + Atom<T>::kPad;
+#pragma unroll
+        for (int ni = 0; ni < MI; ++ni)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) Vp[(ni * 16 + g4 + j) * ldp + r] = from_f32<T>(bg.half_write(ni, j));
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+        for (int ni = 0; ni < MI; ++ni) {
+            f32x4 x = {0.f, 0.f, 0.f, 0.f};
+            const typename Atom<T>::Frag16 v = Atom<T>::load16(Vp + (ni * 16 + r) * ldp + g4);
+            Atom<T>::mma16(x, v, own);
+            if (sizeof(T) == 2) Atom<T>::mma16(x, v, rest);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) run[ni][j] += x[j] * bg.half_read(ni, j);
+        }
+    }
+    if (bg.kind == kPairs) {   // the diagonal block pair by pair
         for (int q = 0; q < 4; ++q)
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
@@ -416,6 +448,24 @@ __device__ __forceinline__ void pair_tiles(const f32x4 (&w1)[M / 16], const f32x
         Atom<T>::mma16(x1t, f, v);
         Atom<T>::mma16(x2t, to_frag16<T>(w2[ni]), v);
     }
+}
+
+// The diagonal tile D[r][t] of the pair weights of a kHalf block, zero for r > t.  wt: ungated D[slot][t] weights.
+template <typename T, int M, bool GEN>
+__device__ __forceinline__ f32x4 pair_tile_half(const f32x4 (&wt)[M / 16], const BlockGates<M, GEN> &bg, int lane)
+{
+    const int r = lane & 15, g4 = (lane >> 4) * 4;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ni = 0; ni < M / 16; ++ni) {
+        f32x4 v, x;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { v[j] = bg.half_write(ni, j); x[j] = wt[ni][j] * bg.half_read(ni, j); }
+        Atom<T>::mma16(acc, to_frag16<T>(v), to_frag16<T>(x));
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[j] = g4 + j <= r ? acc[j] : 0.f;
+    return acc;
 }
 
 // The diagonal tile D[r][t] of the pair weights without factoring: sum_i wt[i] s_r[i] exp(L_t[i] - L_r[i]) for

@@ -100,7 +100,8 @@ template <typename T, int M, bool WIDE> struct ChunkFwdLds {
     static constexpr size_t oRb = oVt + sizeof(T) * M * ldt;          // Rb [C/16][M] fp32
     static constexpr size_t endR = oRb + sizeof(float) * (C / 16) * M;
     static constexpr size_t oMat = (WIDE && endR < 2 * Wide<M>::szBuf) ? 2 * Wide<M>::szBuf : endR;   // A2, p*exp(G)
-    static constexpr size_t end = oMat + (WIDE ? Wide<M>::szTok + Wide<M>::szSlot : 0);
+    static constexpr size_t oVp = oMat + (WIDE ? Wide<M>::szTok + Wide<M>::szSlot : 0);   // per wave: see gated_rows
+    static constexpr size_t end = oVp + sizeof(T) * kPrivate<T, M> * (C / 16);
     static constexpr int kRpr = 2;                 // row blocks per round of the reduction
     static constexpr size_t szRed = sizeof(f32x4) * kWave * (C / 16) *
                                     reduce_fragments<C / 16, C / 16 + M / 16, C / 16, kRpr>();   // from offset 0: dead before the tiles are written
@@ -147,10 +148,10 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_fwd_kernel
         p, a, alo, reinterpret_cast<f32x4 *>(smem), q + tokh * d_k, k + tokh * d_k, (size_t)H * d_k, d_k, Kn, ci.len, lane, w,
         PHI ? (kHintX | kHintY) : 0,
         [&] { bg.load(g + tokh * M, (size_t)H * M, ci.len, rowb, lane, (GEN && sin) ? sin + tokh * M : nullptr, gate_tau); });
-    const bool unsafe = bg.finish(ci.len, rowb, lane);
+    bg.finish(ci.len, rowb, lane);
     bg.template write_tiles<T>(Vn, L::ldn, Vt, L::ldt, Rb, rowb, lane);
     __syncthreads();
-    gated_rows<T, M, C, GEN>(p, a, alo, bg, unsafe, Vt, L::ldt, Rb, lane, w);
+    gated_rows<T, M, C, GEN>(p, a, alo, bg, Vt, L::ldt, Rb, reinterpret_cast<T *>(smem + L::oVp) + w * kPrivate<T, M>, lane, w);
     // ---- softmax over the slots, in registers
 #pragma unroll
     for (int ni = 0; ni < MI; ++ni) p[ni] *= scale;
@@ -188,18 +189,19 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_fwd_kernel
         W::fetch(sb, unit(min(1, units - 1)), ci.len, tid);
     }
     T *dA = mA + (size_t)t * lda, *dP = mP + (size_t)t * lds;
-    f32x4 exact = {0.f, 0.f, 0.f, 0.f};
-    if (unsafe) exact = pair_tile_exact<M, GEN>(p, bg, lane);
+    f32x4 diag = {0.f, 0.f, 0.f, 0.f};
+    if (bg.kind == kPairs) diag = pair_tile_exact<M, GEN>(p, bg, lane);
+    if (bg.kind == kHalf) diag = pair_tile_half<T, M, GEN>(p, bg, lane);
 #pragma unroll
     for (int ni = 0; ni < MI; ++ni)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) p[ni][j] *= __expf(unsafe ? bg.L[ni][j] : bg.L[ni][j] - bg.tot[ni][j]);
+        for (int j = 0; j < 4; ++j) p[ni][j] *= bg.walk_gate(ni, j);
 #pragma unroll
     for (int b = CI - 1; b >= 0; --b) {
         f32x4 x = {0.f, 0.f, 0.f, 0.f};
         if (b <= w) {   // wave-uniform
-            if (b == w && unsafe) {
-                x = exact;   // p is already at the start of the block
+            if (b == w && bg.kind != kNarrow) {
+                x = diag;   // p is already at the start of the block
             } else {
                 x = pair_tile<T, M>(p, Vn, L::ldn, b, lane);
 #pragma unroll
