@@ -406,7 +406,8 @@ __device__ __forceinline__ void gated_rows(f32x4 (&run)[M / 16], const typename 
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 const int rr = 4 * q + c;
-                const float av = __shfl(to_f32(own[c]), 16 * q + r, 64);   // zero for rr > t
+                const float x = sizeof(T) == 2 ? to_f32(own[c]) + to_f32(rest[c]) : to_f32(own[c]);
+                const float av = __shfl(x, 16 * q + r, 64);   // zero for rr > t
 #pragma unroll
                 for (int ni = 0; ni < MI; ++ni)
 #pragma unroll

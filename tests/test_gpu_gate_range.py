@@ -1,6 +1,6 @@
 """Row blocks whose gates decay by close to e^80, the widest that are factored, next to ordinary slots: results are linear in
 q (forward, identity read-out) and in dO (backward) over many powers of two, because neither factor of a gate may leave
-fp32's range first."""
+fp32's range first; and wider blocks, evaluated pair by pair, keep the precision of the factored ones."""
 import pytest
 import torch
 
@@ -54,3 +54,16 @@ def test_identity_readout_is_linear_in_q(m, dtype, power):
     for n, t, b in zip(("o", "z"), run(d["q"] * 2.0 ** power), run(d["q"])):
         assert torch.isfinite(t).all(), n
         assert rel_l2(to_np64(t) * 2.0 ** -power, to_np64(b)) <= BAR[dtype], n
+
+
+@pytest.mark.parametrize("m", [16, 32, 64, 128])
+def test_pair_by_pair_blocks_keep_the_rest_of_the_products(oracle, m):
+    """One block, every slot wiped at every token, no initial memory: z is a sum of products of bf16 numbers, exact in fp32,
+    with fp32 weights.  Product and rest together hold 16 bits of it; the product alone would hold 8 (error about 1e-3)."""
+    import paper_2409_07146_amd as gsa
+    from paper_2409_07146_amd import synth
+    x = synth.make_inputs(synth.GsaConfig("wiped", B=1, T=16, H=2, d_k=128, d_v=64, m=m, dtype="bf16", seed=43))
+    g = x["g"] * 4.0 - 6.0
+    _, z, _, _ = gsa.gsa_fwd(x["q"].cuda(), x["k"].cuda(), x["v"].cuda(), g.cuda())
+    ref = oracle.fwd(*(to_np64(t) for t in (x["q"], x["k"], x["v"], g)))["z"]
+    assert rel_l2(to_np64(z), ref) <= 2.0 ** -15
