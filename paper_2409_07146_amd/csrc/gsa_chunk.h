@@ -157,7 +157,10 @@ template <typename T> __device__ __forceinline__ typename Atom<T>::Frag16 rest_f
 {
     f32x4 y;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) y[j] = x[j] - to_f32(f[j]);
+    for (int j = 0; j < 4; ++j) {   // of an infinity nothing: its sum with a NaN would lose the sign
+        const float h = to_f32(f[j]);
+        y[j] = fabsf(h) < __builtin_inff() ? x[j] - h : 0.f;
+    }
     return to_frag16<T>(y);
 }
 template <typename T> __device__ __forceinline__ void store_frag16(T *p, const f32x4 &x)
