@@ -220,7 +220,7 @@ template <int M, bool GEN> struct BlockGates {
             for (int j = 0; j < 4; ++j) {
                 float x = L[ni][j];
                 if (GEN && tau > 0.f) x = log_gate_from_logit(x, tau);
-                x = live ? fmaxf(x, kGateFloor) : 0.f;
+                x = live ? floor_gate(x) : 0.f;
                 const float sx = (GEN && given) ? s[ni][j] : -expm1f(x);
                 s[ni][j] = live ? sx : 0.f;
                 x = row16_prefix_sum(x);

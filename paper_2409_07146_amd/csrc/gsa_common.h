@@ -343,6 +343,9 @@ __device__ __forceinline__ void seq_lookup(const ChunkMap &cm, int s, int &chunk
 // ----------------------------------------------------------------------------
 // Gates (Algorithm 1, chunk_cumsum, plus the write intensity).
 // ----------------------------------------------------------------------------
+// (the maximum that keeps a NaN; fmaxf would turn it into the floor)
+__device__ __forceinline__ float floor_gate(float x) { return __builtin_elementwise_maximum(x, kGateFloor); }
+
 // log gate from a gate logit: logsigmoid(u) / tau = -(log(1 + exp(-|u|)) + max(-u, 0)) / tau, and its slope
 __device__ __forceinline__ float log_gate_from_logit(float u, float tau)
 {
@@ -384,7 +387,7 @@ template <int M, int NT, int C, bool GEN = false> struct GatePrep {
     {
         float graw = gv[tt];
         if (GEN && tau > 0.f) graw = log_gate_from_logit(graw, tau);
-        x = live ? fmaxf(graw, kGateFloor) : 0.f;
+        x = live ? floor_gate(graw) : 0.f;
         sx = -expm1f(x);   // as in the decode step: a memory is handed from one to the other
         if (GEN && given) sx = sv[GEN ? tt : 0];
         sx = live ? sx : 0.f;

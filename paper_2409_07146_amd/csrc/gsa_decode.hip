@@ -147,7 +147,7 @@ __global__ __launch_bounds__(NWAVES * kWave) void decode_kernel(int d_k, int d_v
     float a[R], s[R];
 #pragma unroll
     for (int rr = 0; rr < R; ++rr) {
-        const float gv = fmaxf((GEN && gate_tau > 0.f) ? log_gate_from_logit(graw[rr], gate_tau) : graw[rr], kGateFloor);
+        const float gv = floor_gate((GEN && gate_tau > 0.f) ? log_gate_from_logit(graw[rr], gate_tau) : graw[rr]);
         a[rr] = __expf(gv);
         s[rr] = (GEN && sin) ? sraw[rr] : -expm1f(gv);
     }
