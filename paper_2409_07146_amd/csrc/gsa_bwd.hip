@@ -98,7 +98,7 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_dz_kernel(
 #pragma unroll
             for (int ni = 0; ni < MI; ++ni) zv[ni] = *reinterpret_cast<const f32x4 *>(z + row + ni * 16);
         });
-    bg.finish(ci.len, rowb, lane);
+    bg.template finish<T>(ci.len, rowb, lane);
     bg.template write_tiles<T>(nullptr, 0, Vt, L::ldt, Rb, rowb, lane);
     T *X = reinterpret_cast<T *>(smem + L::oX + (size_t)w * L::szX);   // this wave's scratch
     __syncthreads();
@@ -436,7 +436,7 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
     // ref lies halfway down the block's decay, so that neither U nor exp(ref - L_r) leaves fp32's range by
     // more than e^40; a kPairs block is referenced to its start, which serves the earlier blocks, and its own pairs are
     // evaluated one by one.
-    bg.finish(ci.len, rowb, lane);
+    bg.template finish<T>(ci.len, rowb, lane);
     const bool unsafe = bg.kind == kPairs;
     bg.template write_tiles<T>(Vn, L::ldn, nullptr, 0, Rb, rowb, lane);
     if (!GEN || a.readout == kReadSoftmax) {

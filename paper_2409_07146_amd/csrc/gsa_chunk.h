@@ -180,13 +180,15 @@ template <typename T> __device__ __forceinline__ void store_frag16(T *p, const f
 // in both orientations (Vn[token][slot], Vt[slot][token]), and the decay across the block Rb[b][i] =
 // exp(tot[i]).  The weight between a token t of block w and a token r of block b <= w is then
 //   exp(G_t - G_r) s_r = exp(L_t - tot_w) * (product of Rb over the blocks b+1 .. w) * V[r]
-// for the diagonal block as well: no operand of a gated contraction needs an exponential of its own, and
-// no exponential is evaluated twice.  Of the diagonal block that holds while it is
-//   kNarrow (down to e^-40).  The two factors grow and shrink with the decay, and in
-//   kHalf (down to e^-80) blocks weights above 6e3 overflowed and products below 1e-4 underflowed: the wave that owns one
-//   references its diagonal halfway, exp(L_t - tot/2) * s_r exp(tot/2 - L_r), with operands of its own.  Neither factor
-//   leaves e^+-40 then, and what they multiply may lie anywhere in fp32's range but its outer 17 orders of magnitude.
-//   (Tokens of later blocks are all behind the decay: what underflows there is far below their own block's terms.)
+// no operand of a gated contraction needs an exponential of its own, and no exponential is evaluated twice.  The
+// diagonal block (b = w) depends on its kind:
+//   kNarrow (bf16, down to e^-40): as above, exp(L_t - tot) * V[r].
+//   kHalf (down to e^-80; fp32: always): referenced halfway by the wave that owns it, exp(L_t - tot/2) * s_r exp(tot/2 - L_r),
+//   with operands of its own.  Neither factor leaves e^+-40 then, and what they multiply may lie anywhere in fp32's range
+//   but its outer 17 orders of magnitude; referenced to the end, weights above 6e3 overflowed at e^-80 and products below
+//   1e-4 underflowed.  (Tokens of later blocks are all behind the decay: what underflows there is far below their own
+//   block's terms.)  fp32 takes it for the smaller exponents: the error of dq is 2.56e-7 instead of 2.94e-7 (m = 32, 700
+//   tokens, d_k = 192).
 //   kPairs (wider): the block's own pairs are evaluated one by one with the unfactored exponent.
 // ----------------------------------------------------------------------------
 enum BlockKind { kNarrow = 0, kHalf = 1, kPairs = 2 };
@@ -210,7 +212,7 @@ template <int M, bool GEN> struct BlockGates {
             for (int ni = 0; ni < MI; ++ni) s[ni] = *reinterpret_cast<const f32x4 *>(sin + off + ni * 16);
         }
     }
-    __device__ __forceinline__ void finish(int len, int rowb, int lane)
+    template <typename T> __device__ __forceinline__ void finish(int len, int rowb, int lane)
     {
         const bool live = rowb + (lane & 15) < len;
         float least = 0.f;
@@ -228,7 +230,7 @@ template <int M, bool GEN> struct BlockGates {
                 tot[ni][j] = row16_last(x);
                 least = fminf(least, tot[ni][j]);
             }
-        kind = __any(least < -kExpClamp) ? kPairs : __any(least < -0.5f * kExpClamp) ? kHalf : kNarrow;
+        kind = __any(least < -kExpClamp) ? kPairs : (sizeof(T) == 4 || __any(least < -0.5f * kExpClamp)) ? kHalf : kNarrow;
     }
     // exp(L_t - ref) with ref the block's end where its diagonal uses the shared tile, else its start
     __device__ __forceinline__ float walk_gate(int ni, int j) const { return __expf(kind == kNarrow ? L[ni][j] - tot[ni][j] : L[ni][j]); }

@@ -148,7 +148,7 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_fwd_kernel
         p, a, alo, reinterpret_cast<f32x4 *>(smem), q + tokh * d_k, k + tokh * d_k, (size_t)H * d_k, d_k, Kn, ci.len, lane, w,
         PHI ? (kHintX | kHintY) : 0,
         [&] { bg.load(g + tokh * M, (size_t)H * M, ci.len, rowb, lane, (GEN && sin) ? sin + tokh * M : nullptr, gate_tau); });
-    bg.finish(ci.len, rowb, lane);
+    bg.template finish<T>(ci.len, rowb, lane);
     bg.template write_tiles<T>(Vn, L::ldn, Vt, L::ldt, Rb, rowb, lane);
     __syncthreads();
     gated_rows<T, M, C, GEN>(p, a, alo, bg, Vt, L::ldt, Rb, reinterpret_cast<T *>(smem + L::oVp) + w * kPrivate<T, M>, lane, w);
