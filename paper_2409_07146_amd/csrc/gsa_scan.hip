@@ -98,7 +98,7 @@ template <typename T> struct ScanArgs {
     float *sumD;           // [n_seqs][max_seg][H][slices][M]    its total decay
 };
 
-template <typename T, int M, int NS> struct ScanLds {
+template <typename T, int M, int NS, bool TILE> struct ScanLds {
     static constexpr int C = Geo<T>::C;
     static constexpr int PAD = Atom<T>::kPad;
     static constexpr int ldw = C + PAD;      // XT [NS][ldw]
@@ -115,10 +115,13 @@ template <typename T, int M, int NS> struct ScanLds {
     static constexpr size_t oW = 0;
     static constexpr size_t oX = oW + szW;
     static constexpr size_t oDec = oX + szX;              // chunk decays, fp32 [M]
-    static constexpr size_t set = oDec + sizeof(float) * M;
-    // where a wave owns whole rows of the snapshot tile: its 16 slots meet here, so that they leave in full lines
-    static constexpr bool kRows = NI * 16 == NS;
+    // Where a wave owns whole rows of the snapshot tile (kRows) its 16 slots meet in LDS of its own, so that they leave in
+    // full lines.  Where it owns less than a line of each (kTile: bf16 with 16 and 32 slots) the whole tile can meet in the
+    // set and leave one step later, behind the step's barrier; the rule stands at the launch.
+    static constexpr bool kRows = NI * 16 == NS, kTile = TILE && NI * 16 * sizeof(T) < 128;
     static constexpr int ldx = NS + PAD;
+    static constexpr size_t oSn = oDec + sizeof(float) * M, szSn = kTile ? sizeof(T) * M * ldx : 0;
+    static constexpr size_t set = oSn + szSn;
     static constexpr size_t oEx = 2 * set, szEx = kRows ? sizeof(T) * 16 * ldx : 0;   // per wave
     static constexpr size_t bytes = oEx + NW * szEx;
 };
@@ -129,11 +132,11 @@ template <typename T, int M, int NS> struct ScanLds {
 // and leaves what the segment adds (sumY) and its total decay (sumD); MODE 2 walks every segment for
 // real, starting from the memory its predecessors leave behind, which it gets by running the
 // recurrence over their summaries (at most max_seg - 1 steps of an element-wise update).
-template <typename T, int M, int NS, bool REVERSE, int MODE>
+template <typename T, int M, int NS, bool REVERSE, int MODE, bool TILE>
 __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void scan_kernel(ChunkMap cm, int H, int d_k, int d_v, int n_seqs,
                                                           ScanArgs<T> a)
 {
-    using L = ScanLds<T, M, NS>;
+    using L = ScanLds<T, M, NS, TILE>;
     constexpr int C = Geo<T>::C, NT = Geo<T>::NT;
     constexpr int MI = L::MI, NI = L::NI;
     constexpr int WVEC = M * C / 8, WV = (WVEC + NT - 1) / NT;
@@ -308,6 +311,36 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void scan_kernel(Chun
             }
         }
     };
+    // position in the walk -> chunk; positions past the end repeat the last chunk, so that refills can be
+    // issued unconditionally (a refill under a branch makes the number of loads in flight unknown to the
+    // compiler, which then waits for all of them wherever it needs one)
+    auto chunk_of = [&](int it) { it = min(it, nch - 1); return first + (REVERSE ? nch - 1 - it : it); };
+    // kTile: accumulator -> tile of set b, and (behind a barrier) that tile -> this workgroup's tile of a record
+    auto gather = [&](int b) {
+        T *X = reinterpret_cast<T *>(smem + b * L::set + L::oSn) + slot0 * L::ldx + lcol;
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+            if constexpr (NI == 1) {
+                store4(X + mi * 16 * L::ldx, acc[mi][0][0], acc[mi][0][1], acc[mi][0][2], acc[mi][0][3]);
+            } else {
+#pragma unroll
+                for (int ni = 0; ni < NI; ni += 2) {
+                    const f32x4 x = acc[mi][ni], y = acc[mi][ni + 1];
+                    const float v[8] = {x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]};
+                    store8<T>(X + mi * 16 * L::ldx + tcol(ni), v);
+                }
+            }
+    };
+    auto send = [&](T *rec, int b) {
+        const T *X = reinterpret_cast<const T *>(smem + b * L::set + L::oSn);
+        T *dst = rec + (isK ? a.lay.oK : a.lay.oV) + (size_t)(c0 / kSnapTile) * (M * kSnapTile);   // contiguous [M][NS]
+        static_assert(!L::kTile || M * NS / 8 <= NT, "one 16-byte piece per thread at most");
+        const int idx = min(tid, M * NS / 8 - 1);
+        Raw8<T> x;
+        x.load(X + (idx / (NS / 8)) * L::ldx + (idx % (NS / 8)) * 8);   // clamped: the read is not under the branch
+        if (tid < M * NS / 8) x.store(dst + (size_t)tid * 8);
+    };
+    auto snap_of = [&](int it) { return a.snap + ((size_t)(chunk0 + chunk_of(it)) * H + h) * a.lay.stride; };
     // staged registers -> LDS set b (W as is, X transposed)
     auto stage_to_lds = [&](const Stage &st, int b) {
         T *w = We(b);
@@ -323,14 +356,10 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void scan_kernel(Chun
         else st.xt.store_transposed(XT(b), L::ldw, NS, tid);
         Dec(b)[tid & (M - 1)] = st.dec;   // every thread stores (slots have NT/M writers of the same value): no branch around a loaded value
     };
-    // position in the walk -> chunk; positions past the end repeat the last chunk, so that refills can be
-    // issued unconditionally (a refill under a branch makes the number of loads in flight unknown to the
-    // compiler, which then waits for all of them wherever it needs one)
-    auto chunk_of = [&](int it) { it = min(it, nch - 1); return first + (REVERSE ? nch - 1 - it : it); };
-
     // The walk, software-pipelined with ONE barrier per chunk.  At the top of step `it` LDS set it%2
     // holds the operands of chunk `it` (written during the previous step).  The step
-    //   - sends the accumulator (the memory chunk `it` starts from) to the snapshots,
+    //   - sends the accumulator (the memory chunk `it` starts from) to the snapshots (kTile: to its set, and the previous one's
+    //     from the other set to the snapshots),
     //   - applies S <- Diag(dec) S + W X with fragments read from its own set,
     //   - writes the operands of chunk it+1 (register stage `nx`) into the other set and refills
     //     that stage with chunk it+3,
@@ -341,7 +370,12 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void scan_kernel(Chun
     // registers, by 16-byte pieces 32 bytes apart, the last one took 63 us.
     auto step = [&](Stage &nx, int it) {
         const int b = it & 1;
-        if (MODE != 1) snapshot(a.snap + ((size_t)(chunk0 + chunk_of(it)) * H + h) * a.lay.stride);
+        if constexpr (MODE != 1 && L::kTile) {
+            if (it > 0) send(snap_of(it - 1), b ^ 1);
+            gather(b);
+        } else if constexpr (MODE != 1) {
+            snapshot(snap_of(it));
+        }
         typename Atom<T>::Frag af[C / 32][MI], bf[C / 32][NI];
         const T *w = We(b), *x = XT(b);
 #pragma unroll
@@ -395,6 +429,9 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void scan_kernel(Chun
         __syncthreads();
         ++it;
     }
+    if constexpr (MODE != 1 && L::kTile) {
+        if (nch > 0) send(snap_of(nch - 1), (nch - 1) & 1);
+    }
     if (MODE == 1) {   // what this segment adds and how much it decays, for its successors
         const size_t rec = ((size_t)s * a.max_seg + seg) * H + h;
         float *Y = a.sumY + rec * M * D + col0;
@@ -419,7 +456,17 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void scan_kernel(Chun
             for (int ni = 0; ni < NI; ++ni)
                 *reinterpret_cast<f32x4 *>(ST + (((size_t)s * H + h) * M + slot0 + 16 * mi) * dsrc + c0 + lcol + tcol(ni)) = acc[mi][ni];
     }
-    if (a.outJ) snapshot(a.outJ + ((size_t)s * H + h) * a.lay.stride);
+    if (a.outJ) {
+        T *rec = a.outJ + ((size_t)s * H + h) * a.lay.stride;
+        if constexpr (L::kTile) {
+            __syncthreads();   // the last snapshot may still be on its way out of the set
+            gather(0);
+            __syncthreads();
+            send(rec, 0);
+        } else {
+            snapshot(rec);
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -457,10 +504,17 @@ hipError_t launch_gates(const Plan &pl, const Work &w, const float *g, const flo
 template <typename T, int M, int NS, bool REVERSE, int MODE>
 static hipError_t run_scan_mode(const Plan &pl, const ChunkMap &cm, const ScanArgs<T> &a, int slot, hipStream_t st)
 {
-    auto kern = scan_kernel<T, M, NS, REVERSE, MODE>;
-    const size_t lds = ScanLds<T, M, NS>::bytes;
-    GSA_HIP_TRY(allow_lds(kern, lds));
     const int total = (pl.d_k + pl.d_v) / NS * pl.H * pl.n_seqs * (MODE == 0 ? 1 : a.max_seg);
+    // Snapshots through the set (kTile) or straight from the registers, in pieces of 32 or 64 bytes.  With more than one
+    // workgroup on a CU the launch is bound by what leaves the chip and whole lines are faster: 8 x 2048 tokens, 4 heads, 16
+    // slots, 320 workgroups 33 us against 36, 640 workgroups 52 against 59; 32 slots 37 / 40 and 61 / 65.  With at most one
+    // it waits for the chain, which the detour lengthens: 16 slots, 256 workgroups 27.5 against 25.0; 32 slots, 16
+    // workgroups (1024 tokens) 14.4 against 13.3.
+    constexpr bool can = MODE != 1 && ScanLds<T, M, NS, true>::kTile;   // a summary pass takes no snapshots
+    const bool tile = can && total > 256;
+    auto kern = tile ? scan_kernel<T, M, NS, REVERSE, MODE, can> : scan_kernel<T, M, NS, REVERSE, MODE, false>;
+    const size_t lds = tile ? ScanLds<T, M, NS, can>::bytes : ScanLds<T, M, NS, false>::bytes;
+    GSA_HIP_TRY(allow_lds(kern, lds));
     KernelTimer kt(slot, st);
     hipLaunchKernelGGL(kern, dim3(total), dim3(Geo<T>::NT), lds, st, cm, pl.H, pl.d_k, pl.d_v, pl.n_seqs, a);
     return hipGetLastError();
