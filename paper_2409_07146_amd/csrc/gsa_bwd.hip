@@ -684,9 +684,11 @@ static hipError_t launch_bwd_tm(const Plan &pl, const Work &w, const void *q, co
     }
     // 4. everything chunk-local, and in bf16 without the feature map the wide contractions as well.  One workgroup
     // then walks all 64-column units of its (chunk, head), which takes longer than a kernel of its own where few
-    // pairs are left to fill the chip: without / with them inside (backward call, m = 64): 64 pairs of d = 512 (24
-    // units) 92 / 98 us, 96 pairs 110 / 111, 128 pairs 119 / 117, 512 pairs 214 / 193, 1024 pairs 411 / 373; d = 1024 (48
-    // units) 128 pairs 153 / 159, 192 pairs 188 / 185; d = 128 (6 units) 32 pairs 56 / 54.
+    // pairs are left to fill the chip.  Time of the backward call with them inside over that without, 64 slots: d = 512 (24
+    // units) 1.18 at 8 pairs, 1.08 at 64, 1.02 at 96, 0.94 at 256, 0.92 from 1024 on; d = 1024 (48 units) 1.30, 1.13, 1.08,
+    // 0.98, 0.96; d = 128 (6 units) 0.97, 0.95, 0.96, 0.92, 0.90.  With 128 slots 1 to 4 per cent lower throughout (one
+    // workgroup per CU holds the 127 KB, the kernel it replaces reads everything again); with 16 and 32 slots the same up to
+    // d = 512 and 0.96 to 1.04 above.
     const int64_t pairs = (int64_t)pl.chunk_slots * pl.H;
     const bool wide = sizeof(T) == 2 && !pl.phi && pairs >= 4 * (2 * pl.d_k + pl.d_v) / 64;
     {

@@ -14,9 +14,9 @@
 //                     registers, and the two small matrices of pass 2: p*exp(G) [C x m] and
 //                     the pair weights A2 [C x C].  z and p never round-trip HBM except for
 //                     the z the backward needs.
-//                     In bf16 o = (p e^G) Vt_start + A2 V, the wide contraction, follows in the
-//                     same kernel (gsa_wide.h).
-//   apply_kernel      (gsa_apply.hip) the wide contraction where it does not (fp32, feature map,
+//                     o = (p e^G) Vt_start + A2 V, the wide contraction, follows in the same kernel
+//                     (gsa_wide.h) in bf16 where that is the faster form (the rule stands at the launch).
+//   apply_kernel      (gsa_apply.hip) the wide contraction where it does not (also: fp32, feature map,
 //                     output epilogue).
 #include "gsa_chunk.h"
 #include "gsa_launch.h"
@@ -240,11 +240,16 @@ static hipError_t launch_fwd_tm(const Plan &pl, const Work &w, const void *q, co
         const ScanIo io = {k, v, K0, V0, KT, VT, pl.keep ? w.SF : nullptr, false, pl.phi != 0, pl.phi != 0};
         GSA_HIP_TRY(launch_scan(pl, w, io, st));
     }
-    // bf16 without the feature map and the output epilogue: the wide contraction follows in the chunk kernel.  Forward
-    // call with a kernel of its own / inside, m = 64: d = 512, 64 (chunk, head) pairs 43.0 / 43.3 us, 512 pairs 90 / 79, 1024
-    // pairs 156 / 146; d = 128, 1024 pairs 80 / 73; but d = 1024 with 1536 pairs 410 / 428 (512 pairs: 148 / 143).
+    // bf16 without the feature map and the output epilogue: the wide contraction follows in the chunk kernel.  Its
+    // workgroup then walks the d_v/64 units one after the other, which takes longer than a kernel of its own where the walk
+    // is long and few (chunk, head) pairs leave the chip idle.  Time of the forward call with the contraction inside over
+    // that with a kernel of its own, 16 to 128 slots, d_k = d_v or 64:
+    //   up to 9 units: 0.77 to 1.02 at 8 to 2048 pairs (d = 128, 64 slots, 1024 pairs: 73 us instead of 80)
+    //   10 to 16 units: 1.2 to 1.03 at 8 to 64 pairs; equal at 144 pairs, with 128 slots at 96; 0.87 to 0.99 beyond
+    //   more than 12 units and 512 pairs: 0.95 to 1.14 up to 64 slots (d_v = 1024)
+    const int64_t pairs = (int64_t)pl.chunk_slots * pl.H;
     const bool wide = sizeof(T) == 2 && !pl.phi && !pl.act_out && !pl.act_ssq &&
-                      (pl.d_v <= 768 || (int64_t)pl.chunk_slots * pl.H <= 512);
+                      (pl.d_v <= 576 || pairs >= (M > 64 ? 96 : 144)) && (pl.d_v <= 768 || pairs <= 512);
     {
         constexpr bool kWide = sizeof(T) == 2;
         auto kern = pl.phi          ? chunk_fwd_kernel<T, M, true, true, false>
