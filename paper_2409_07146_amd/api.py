@@ -43,8 +43,13 @@ def _check(t, name, dtype=None, shape=None, optional=False):
         raise ValueError("%s must have shape %s, got %s" % (name, tuple(shape), tuple(t.shape)))
 
 
+# The handle of a device's current stream without building a Stream object per call; private to torch, hence the public way
+# beside it.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda index: torch.cuda.current_stream(index).cuda_stream)
+
+
 def _stream(t: torch.Tensor):
-    return torch._C._cuda_getCurrentRawStream(t.device.index)   # without building a Stream object per call
+    return _raw_stream(t.device.index)
 
 
 def make_problem(q, v, g, scale=1.0, cu_seqlens=None, keep_states=False):

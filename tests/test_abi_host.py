@@ -123,3 +123,19 @@ def test_python_binding_fails_loudly_without_library(monkeypatch, tmp_path):
     monkeypatch.setattr(_lib, "LIB_PATH", str(tmp_path / "missing.so"))
     with pytest.raises(RuntimeError, match="no CPU fallback"):
         _lib.load()
+
+
+def test_stream_handle_without_the_private_torch_function(monkeypatch):
+    """A torch build that lacks the private function: the handle comes through the public Stream object."""
+    import importlib.util
+    from types import SimpleNamespace
+
+    import torch
+
+    from paper_2409_07146_amd import api
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda index: SimpleNamespace(cuda_stream=1000 + index))
+    spec = importlib.util.spec_from_file_location("paper_2409_07146_amd.api_without", api.__file__)
+    mod = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(mod)
+    assert mod._stream(SimpleNamespace(device=SimpleNamespace(index=3))) == 1003
