@@ -2,8 +2,9 @@
 //
 //     out[C x cols] = A_tok[C x C] X[C x cols]  +  A_slot[C x m] St[m x cols]
 //
-// per (chunk, head), for the calls whose chunk kernels do not evaluate it themselves (gsa_wide.h: bf16 without feature map
-// and output epilogue): the intra-chunk term contracts a small token-by-token matrix with a token
+// per (chunk, head), for the calls whose chunk kernels do not evaluate it themselves (gsa_wide.h): fp32, the feature map, the
+// output epilogue, and in bf16 where the walk over the columns is long and the (chunk, head) pairs are few, or in the
+// forward many and very wide (the rules stand at the launches of the chunk kernels).  The intra-chunk term contracts a small token-by-token matrix with a token
 // tensor of the chunk, the inter-chunk term contracts a small token-by-slot matrix with a slot
 // memory (paper, Appendix A, Eq. (gla-chunk): intra and inter parts).  The small matrices are
 // produced by the chunk kernels and are tiny next to the [tokens x d] tensors, so this kernel

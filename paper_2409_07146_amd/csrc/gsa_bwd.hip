@@ -304,8 +304,8 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
         // key half: A = Q K^T, X += K E_k^T
         // (two passes over k, each in 64-column steps like the value half: together their operand
         // fragments would not fit the registers; the second read of k is served by the caches)
-        // Non-temporal loads for what is read here for the last time in this call (q, v, the chunk-end
-        // memories); k comes twice and the apply kernel right after reads E again, so those stay cached.
+        // Non-temporal loads for what is read here for the last time (v, the chunk-end memories, and q where the wide
+        // contractions run on their own); k and E are read again, by this kernel or by the apply kernel right after it.
         for (int kk = 64 * w; kk < d_k; kk += 64 * NW) {
             Frag fq[2][CI], fk[2][CI];
 #pragma unroll

@@ -17,7 +17,6 @@ namespace gsa {
 typedef __bf16 bf16_t;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x8 __attribute__((ext_vector_type(8)));
 
@@ -101,26 +100,6 @@ template <typename T> struct Geo {
 };
 inline int chunk_of_dtype(int dtype) { return dtype == 0 ? Geo<float>::C : Geo<bf16_t>::C; }
 
-// acc[MI][NI] += A[16*mi + r][k] * B[16*ni + r][k] summed over k in [0,K), K a multiple of 32.
-// A and B are LDS tiles stored [row][k] with row strides lda, ldb (elements).
-template <typename T, int MI, int NI>
-__device__ __forceinline__ void gemm_nt(f32x4 (&acc)[MI][NI], const T *A, int lda, const T *B, int ldb,
-                                        int K, int lane)
-{
-    const int r = lane & 15, g8 = (lane >> 4) * 8;
-    for (int k0 = 0; k0 < K; k0 += 32) {
-        typename Atom<T>::Frag a[MI], b[NI];
-#pragma unroll
-        for (int mi = 0; mi < MI; ++mi) a[mi] = Atom<T>::load(A + (mi * 16 + r) * lda + k0 + g8);
-#pragma unroll
-        for (int ni = 0; ni < NI; ++ni) b[ni] = Atom<T>::load(B + (ni * 16 + r) * ldb + k0 + g8);
-#pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-            for (int ni = 0; ni < NI; ++ni) Atom<T>::mma(acc[mi][ni], a[mi], b[ni]);
-    }
-}
-
 template <int MI, int NI> __device__ __forceinline__ void zero_acc(f32x4 (&acc)[MI][NI])
 {
 #pragma unroll
@@ -128,29 +107,6 @@ template <int MI, int NI> __device__ __forceinline__ void zero_acc(f32x4 (&acc)[
 #pragma unroll
         for (int ni = 0; ni < NI; ++ni) acc[mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
 }
-
-// ----------------------------------------------------------------------------
-// Global -> LDS staging.  Sources are rows of `cols` elements (cols % 8 == 0),
-// row r at src + r*gld.  Rows >= nvalid are filled with zeros.
-// ----------------------------------------------------------------------------
-template <typename Tin> struct Vec8;
-template <> struct Vec8<bf16_t> {
-    float v[8];
-    __device__ __forceinline__ void load(const bf16_t *p) {
-        const bf16x8 x = *reinterpret_cast<const bf16x8 *>(p);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = (float)x[e];
-    }
-};
-template <> struct Vec8<float> {
-    float v[8];
-    __device__ __forceinline__ void load(const float *p) {
-        const f32x4 lo = *reinterpret_cast<const f32x4 *>(p);
-        const f32x4 hi = *reinterpret_cast<const f32x4 *>(p + 4);
-        v[0] = lo[0]; v[1] = lo[1]; v[2] = lo[2]; v[3] = lo[3];
-        v[4] = hi[0]; v[5] = hi[1]; v[6] = hi[2]; v[7] = hi[3];
-    }
-};
 
 template <typename T> __device__ __forceinline__ void store8(T *dst, const float (&v)[8]);
 template <> __device__ __forceinline__ void store8<bf16_t>(bf16_t *dst, const float (&v)[8]) {
@@ -229,45 +185,6 @@ __device__ __forceinline__ void store4(bf16_t *p, float a, float b, float c, flo
 __device__ __forceinline__ void store4(float *p, float a, float b, float c, float d)
 {
     *reinterpret_cast<f32x4 *>(p) = f32x4{a, b, c, d};
-}
-
-// dst[r][c] = src[r][c]   (dst row stride ld)
-template <typename T, typename Tin>
-__device__ __forceinline__ void stage_rows(T *dst, int ld, const Tin *src, size_t gld, int rows, int cols,
-                                           int nvalid, int tid, int nthreads)
-{
-    const int vpr = cols >> 3;
-    for (int idx = tid; idx < rows * vpr; idx += nthreads) {
-        const int r = idx / vpr, c = (idx - r * vpr) << 3;
-        Vec8<Tin> x;
-        if (r < nvalid) x.load(src + (size_t)r * gld + c);
-        else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) x.v[e] = 0.f;
-        }
-        store8<T>(dst + r * ld + c, x.v);
-    }
-}
-
-// dst[c][r] = src[r][c]   (dst row stride ld >= rows): the transposed view that lets a
-// contraction over tokens read 8 consecutive tokens per lane.
-template <typename T, typename Tin>
-__device__ __forceinline__ void stage_cols(T *dst, int ld, const Tin *src, size_t gld, int rows, int cols,
-                                           int nvalid, int tid, int nthreads)
-{
-    const int vpr = cols >> 3;
-    for (int idx = tid; idx < rows * vpr; idx += nthreads) {
-        // consecutive threads take consecutive 16-byte pieces of a row: global loads coalesce
-        const int r = idx / vpr, c = (idx - r * vpr) << 3;
-        Vec8<Tin> x;
-        if (r < nvalid) x.load(src + (size_t)r * gld + c);
-        else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) x.v[e] = 0.f;
-        }
-#pragma unroll
-        for (int e = 0; e < 8; ++e) dst[(c + e) * ld + r] = from_f32<T>(x.v[e]);
-    }
 }
 
 // ----------------------------------------------------------------------------
@@ -367,8 +284,7 @@ template <int M, int NT, int C, bool GEN = false> struct GatePrep {
     float sv[GEN ? TP : 1];
     bool given = false;
     float tau = 0.f;
-    // Issues the loads (rows clamped into the chunk).  May be called well before finish() so that
-    // other work hides the latency.
+    // Issues the loads (rows clamped into the chunk).
     __device__ __forceinline__ void load(const float *g, size_t gld, int len, int tid, const float *sin = nullptr,
                                          float gate_tau = 0.f)
     {
@@ -433,19 +349,10 @@ template <typename T> __device__ __forceinline__ void swish_frag(typename Atom<T
     for (int e = 0; e < 8; ++e) f[e] = from_f32<T>(swish_value((float)f[e]));
 }
 
-// Fragment straight from global memory: 8 consecutive elements of one row.  Loads in this
-// library are never placed under a data-dependent branch (the compiler would have to wait for
+// Loads in this library are never placed under a data-dependent branch (the compiler would have to wait for
 // each one before leaving the branch, which serialises them): callers clamp the row index into
 // the valid range so the load is always legal, and rows past the end are zeroed by a register
-// select here -- or left as finite duplicates of the last row where they only ever meet zero
-// weights.
-template <typename T>
-__device__ __forceinline__ typename Atom<T>::Frag gfrag(const T *p, bool live)
-{
-    const typename Atom<T>::Frag f = Atom<T>::load(p);
-    const typename Atom<T>::Frag z = Atom<T>::zero();
-    return live ? f : z;
-}
+// select -- or left as finite duplicates of the last row where they only ever meet zero weights.
 
 // ----------------------------------------------------------------------------
 // Transposed token tile in LDS: XT[c][t] for c < ncols, t < C, row stride C + kPad,

@@ -21,7 +21,7 @@ struct Plan {
     bool fine;                  // segments shorter than kSegChunks
     // workspace offsets in bytes (256-byte aligned); 0-sized parts share an offset
     size_t off_table, off_seqtab, off_segbase, off_Wf, off_dec, off_S, off_tA, off_tP, off_sum_fwd, total_fwd;
-    size_t off_SF, off_Wr, off_E, off_dz, off_dgf, off_tB, off_tBT, off_tA2T, off_tAvT, off_tSbe, off_sum_bwd, size_sumY, total_bwd;
+    size_t off_SF, off_Wr, off_E, off_dz, off_dgf, off_tBT, off_tA2T, off_tAvT, off_tSbe, off_sum_bwd, size_sumY, total_bwd;
     // layout of every memory snapshot record (elements); see gsa_layout.h
     StateLayout lay;
     // variants (gsa_fwd_ex / gsa_bwd_ex): write intensity as an input of its own, element-wise read-outs
@@ -52,7 +52,10 @@ struct Work {
     void *SF;         // per (sequence, head): memory after the last token (Plan::lay)
     void *Wr;         // [2][m][C]   reverse scan weights
     void *E;          // gradient of the memory at the end of the chunk (Plan::lay)
-    void *tBT;        // [C][C]      scale*Bm^T
+    // Used twice in bf16: chunk_dz leaves in it what the rounding of tAvT left behind, chunk_intra reads that and (where the
+    // wide contractions run on their own) puts scale*Bm^T in its place.  Both belong to one (chunk, head), i.e. to one
+    // workgroup, whose waves have all read their share before any of them writes (the wait and the barrier there).
+    void *tBT;        // [C][C]      rest of tAvT, then scale*Bm^T
     void *tA2T;       // [C][C]      A2^T
     void *tAvT;       // [C][C]      (dO_t . v_r)^T, causally masked
     void *tSbe;       // [C][KM]     s*exp(G_C-G)

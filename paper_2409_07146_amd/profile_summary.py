@@ -138,9 +138,14 @@ def main():
     if args.kernel_trace:
         dur = kernel_trace(args.kernel_trace)
         total = sum(sum(v) for v in dur.values())
+        # the wide contractions run inside the chunk kernels or in the apply kernel; the trace says which
+        apply = [k for k in dur if k.startswith("apply_kernel")]
+        two = any("forward (o)" in k for k in apply)
+        wide = ("both followed by apply" if two else "one of them followed by apply" if apply else
+                "with the wide contractions inside")
         note = args.trace_note or (
-            "Per step the forward launches gate, scan(forward), chunk_fwd; the backward launches gate,\n"
-            "scan(forward), chunk_dz, scan(reverse), chunk_intra (the wide contractions inside).  scan(forward)\n"
+            "Per step the forward launches gate, scan(forward), chunk_fwd; the backward launches gate, scan(forward),\n"
+            "chunk_dz, scan(reverse), chunk_intra; chunk_fwd and chunk_intra " + wide + ".  scan(forward)\n"
             "therefore appears twice per step; its average mixes the forward's and the backward's launch.  The run\n"
             "also times the steps without recomputation, the decode steps and the 256 MiB copy probe.")
         with open(os.path.join(args.out, args.trace_name or "%s_fwd_bwd_kernel_trace.txt" % wl), "w") as f:

@@ -20,7 +20,7 @@ def test_wide_and_ordinary_row_blocks(oracle, m, T, H, d_k, d_v, dtype):
 
     def override(g):
         out = g.clone()
-        out[:, 18:44, :, 1::5] = -25.0   # e^-400 across the block that starts at 16, ordinary slots beside it
+        out[:, 18:44, :, 1::5] = -25.0   # e^-350 across the block that starts at 16, ordinary slots beside it
         out[:, 4:7, :, ::4] = -25.0      # e^-75 and a little: the widest block that is still factored
         out[1, 40:46, :, 2] = -300.0     # below the documented floor of -30
         return out

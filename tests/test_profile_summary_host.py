@@ -58,6 +58,7 @@ def test_summaries_from_small_csv_files(tmp_path):
     subprocess.run(cmd, cwd=ROOT, check=True)
     trace = open(out / "toy_fwd_bwd_kernel_trace.txt").read()
     assert "chunk_intra_kernel<bf16,64>" in trace and "scan_kernel<bf16,64,reverse>" in trace
+    assert "both followed by apply" in trace
     assert "apply_kernel<bf16,64> forward (o)" in trace and "apply_kernel<bf16,64> backward (dq,dk,dv)" in trace
     line = [l for l in trace.splitlines() if l.startswith("chunk_intra_kernel")][0].split()
     assert int(line[1]) == 2 and abs(float(line[3]) - 129.0) < 1e-6      # two calls, 130 and 128 us
