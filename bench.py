@@ -36,21 +36,24 @@ def per_token_head_flops(cfg, C=64):
              full: forward 2C(d_k+d_v) + 4Cm + 4m(d_k+d_v); backward (recompute, dp/dz, reverse scan,
              gradients) 5C(d_k+d_v) + 10Cm + 10m(d_k+d_v).
     executed: what the kernels issue.  The chunk kernels skip the 16 x 16 blocks above the diagonal of every
-             causally masked C x C product (10 of 16 blocks at C = 64); the wide contractions (apply kernel)
-             multiply the masked matrices in full.  This is the number the MFMA fraction is quoted on.
+             causally masked C x C product (10 of 16 blocks at C = 64); the wide contractions
+             multiply the masked matrices in full.  In bf16 the gated intra parts of z, dp and ds take their products
+             of token rows twice (the rounded product and what the rounding left behind).  This is the number the
+             MFMA fraction is quoted on; the hardware's operation counter reads the same.
     algorithmic: the chunk-free recurrent form, 4m(d_k+d_v) forward and 8m(d_k+d_v) backward."""
     dk, dv, m = cfg.d_k, cfg.d_v, cfg.m
     D = dk + dv
     nb = C // 16
     tri = (nb * (nb + 1) // 2) / float(nb * nb)
+    rest = 2 * C * m * tri if cfg.dtype == "bf16" else 0.0
     nominal = (2 * C * D + 4 * C * m + 4 * m * D, 5 * C * D + 10 * C * m + 10 * m * D)
     fwd = (2 * m * D                                             # scan
            + 2 * C * dk * tri + 2 * m * dk + 4 * C * m * tri     # QK^T, Q Kt^T, gated intra scores, pair weights A2
-           + 2 * C * dv + 2 * m * dv)                            # o
+           + rest + 2 * C * dv + 2 * m * dv)                     # o
     bwd = (2 * m * D                                             # recomputed scan
-           + 2 * C * dv * tri + 2 * m * dv + 2 * C * m * tri     # dO V^T, dO Vt^T, gated intra part of dp
+           + 2 * C * dv * tri + 2 * m * dv + 2 * C * m * tri + rest   # dO V^T, dO Vt^T, gated intra part of dp
            + 2 * m * D                                           # reverse scan
-           + 2 * C * dk * tri + 2 * m * D + 8 * C * m * tri      # QK^T, [K|V] E^T, intra part of ds (2x), Bm, A2
+           + 2 * C * dk * tri + 2 * m * D + 10 * C * m * tri + rest   # QK^T, [K|V] E^T, intra part of ds (2x), Bm, Bm^T, A2^T
            + 2 * C * (2 * dk + dv) + 2 * m * (2 * dk + dv))      # dq, dk, dv
     return dict(executed=(fwd, bwd), nominal=nominal, algorithmic=(4 * m * D, 8 * m * D))
 
