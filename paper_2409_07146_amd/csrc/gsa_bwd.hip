@@ -513,8 +513,14 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
         exa = pair_tile_exact<M, GEN>(p, bg, lane);
     }
     if (bg.kind == kHalf) {
-        exb = pair_tile_half<T, M, GEN>(wd, bg, lane);
-        exa = pair_tile_half<T, M, GEN>(p, bg, lane);
+        for (int u = 0; u < 2; ++u) {   // one body for both: two of them cost registers (three spilled at m = 64)
+            f32x4 wt[MI];
+#pragma unroll
+            for (int ni = 0; ni < MI; ++ni) wt[ni] = u ? p[ni] : wd[ni];
+            const f32x4 x = pair_tile_half<T, M, GEN>(wt, bg, lane);
+            if (u) exa = x;
+            else exb = x;
+        }
     }
     // ---- phase 2b: the gate gradient inside the block, and the block's total for the earlier ones
     f32x4 dg[MI];
