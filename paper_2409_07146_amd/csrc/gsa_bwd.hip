@@ -163,13 +163,21 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_dz_kernel(
             if (sizeof(T) == 2) X[(2 * M + C + b * 16 + g4 + j) * L::ldx + r] = alo[b][j];
         }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    T *dW = Wr + ch * 2 * M * C + rowb, *dAv = tAvT + ch * C * C + rowb, *dLo = tAvLo + ch * C * C + rowb;
+    // The scan weights in fragment order: 16 slots, a piece of the tokens next to each other in a run of 256 bytes.
+    T *dW = Wr + ch * 2 * M * C, *dAv = tAvT + ch * C * C + rowb, *dLo = tAvLo + ch * C * C + rowb;
+    constexpr int PV = 16 / sizeof(T), PT = 16 / PV;   // pieces of a row's 16 tokens
 #pragma unroll
-    for (int u = 0; u < 2 * L::kRows / kWave; ++u) {
+    for (int u = 0; u < 2 * M * PT / kWave; ++u) {
+        const int idx = lane + u * kWave, rr = idx / (16 * PT) * 16 + (idx & 15), c = idx / 16 % PT * PV;
+        const f32x4 x = *reinterpret_cast<const f32x4 *>(X + rr * L::ldx + c);
+        *reinterpret_cast<f32x4 *>(dW + (rr / M) * M * C + frag_order<T, C / 32>(rr % M, rowb + c)) = x;
+    }
+#pragma unroll
+    for (int u = 0; u < 2 * (L::kRows - 2 * M) / kWave; ++u) {
         const int idx = lane + u * kWave, rr = idx >> 1, c8 = (idx & 1) * 8;
         Raw8<T> x;
-        x.load(X + rr * L::ldx + c8);
-        x.store((rr < 2 * M ? dW + (size_t)rr * C : rr < 2 * M + C ? dAv + (size_t)(rr - 2 * M) * C : dLo + (size_t)(rr - 2 * M - C) * C) + c8);
+        x.load(X + (2 * M + rr) * L::ldx + c8);
+        x.store((rr < C ? dAv + (size_t)rr * C : dLo + (size_t)(rr - C) * C) + c8);
     }
 }
 

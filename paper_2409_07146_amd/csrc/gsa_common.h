@@ -91,6 +91,22 @@ template <> struct Atom<float> {
     }
 };
 
+// Fragment order: a matrix [rows][32*steps] kept for one reader, as that reader's depth-32 operands (tile after tile of 16
+// rows, step after step), so that a fragment load of a wave is one contiguous kilobyte.  From an array of rows the
+// same load takes 16 bytes of each of 16 rows per quarter of the wave, and the address unit works line by line: four times as long.
+template <typename T, int STEPS> __device__ __forceinline__ uint32_t frag_order(int row, int k)   // k % (16 / sizeof(T)) = 0: start of a 16-byte piece
+{
+    constexpr int PV = 16 / sizeof(T);
+    const int lane = (row & 15) + 16 * ((k & 31) >> 3);
+    return (uint32_t)(((row >> 4) * STEPS + (k >> 5)) * 512 + ((k & 7) / PV) * (kWave * PV) + lane * PV);
+}
+__device__ __forceinline__ bf16x8 load_frag_order(const bf16_t *tile, uint32_t lane) { return *reinterpret_cast<const bf16x8 *>(tile + lane * 8); }
+__device__ __forceinline__ f32x8 load_frag_order(const float *tile, uint32_t lane)
+{
+    const f32x4 lo = *reinterpret_cast<const f32x4 *>(tile + lane * 4), hi = *reinterpret_cast<const f32x4 *>(tile + 256 + lane * 4);
+    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
 // Chunk geometry per element type: one wave per 16-token row block.  fp32 tiles are
 // twice as large in LDS, so the fp32 path uses half the chunk.
 template <typename T> struct Geo {
@@ -365,6 +381,39 @@ template <int C> __device__ __forceinline__ int xt_off(int c, int t, int ld)
     constexpr int NB = C / 8;
     return c * ld + ((((t >> 3) ^ (c >> 3)) & (NB - 1)) << 3) + (t & 7);
 }
+
+// ----------------------------------------------------------------------------
+// bf16 tile [rows][64 columns] in LDS as it lies in memory, read by the transposing LDS load, which hands a lane four
+// consecutive rows of one column.  Rows are 128 bytes.  Their 8-byte pieces are XOR-swizzled so that the 32 lanes of half a
+// transposing load (eight rows, four pieces each, STEP pieces apart) touch every bank once.
+// ----------------------------------------------------------------------------
+template <int STEP> struct TrTile {
+    static constexpr int kCols = 64;
+    static constexpr int B0 = STEP == 1 ? 2 : 0, B1 = STEP == 4 ? 1 : 3;   // the two address bits of a piece that STEP leaves free
+    __device__ static __forceinline__ int swz(int row) { return (((row >> 1) & 1) << B0) | (((row >> 3) & 1) << B1); }
+    __device__ static __forceinline__ void put(bf16_t *tile, int row, int cg, bf16x8 x)
+    {
+        const int f = swz(row);
+        const bf16x8 y = __builtin_shufflevector(x, x, 4, 5, 6, 7, 0, 1, 2, 3);
+        *reinterpret_cast<bf16x8 *>(tile + row * kCols + ((cg ^ (f >> 1)) << 3)) = (B0 == 0 && (f & 1)) ? y : x;
+    }
+    // Eight rows of one column: lane l of 16 gets element l%4 of the piece (of four columns) that lane l/4 of the 16
+    // names, so each lane names the piece for lanes 4*(l%4) .. +3.  lane_off: where a lane of the wave reads, relative to the
+    // first of 32 rows; frag: rows 8*(l/16) .. +7 from there.  (The swizzle of a row is that of the row 4, 16 or 32 further.)
+    __device__ static __forceinline__ uint32_t lane_off(int piece, int lane)
+    {
+        const int row = 8 * (lane >> 4) + ((lane & 15) >> 2);
+        return (uint32_t)(row * kCols + ((piece ^ swz(row)) << 2));
+    }
+    __device__ static __forceinline__ bf16x8 frag(const bf16_t *p)
+    {
+        typedef short s16x4 __attribute__((ext_vector_type(4)));
+        typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)p);
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + 4 * kCols));
+        return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    }
+};
 
 // Token tile held in registers between the global load and the transposing LDS write.
 // The tile is C tokens x NCOLS columns; thread (tid) owns row pairs and 8-column groups.

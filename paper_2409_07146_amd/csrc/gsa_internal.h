@@ -44,13 +44,13 @@ struct Work {
     int32_t *seqtab;  // [4*n_seqs]     packed form only
     int32_t *segbase; // [n_seqs+1]     packed form only: scan segments before each sequence
     // per (chunk, head) records, element type = I/O dtype unless noted; KM = max(m, 32)
-    void *Wf;         // [m][C]      forward scan weights s*exp(G_C-G)
+    void *Wf;         // [m][C] in fragment order   forward scan weights s*exp(G_C-G)
     float *dec;       // [m]         chunk decay exp(G_C)                                  (fp32)
     void *S;          // memory at the start of the chunk (Plan::lay)
     void *tA;         // [C][C]      forward: pair weights A2;  backward: scale*Bm
     void *tP;         // [C][KM]     forward: p*exp(G);         backward: scale*dz*exp(G)
     void *SF;         // per (sequence, head): memory after the last token (Plan::lay)
-    void *Wr;         // [2][m][C]   reverse scan weights
+    void *Wr;         // [2], [m][C] in fragment order   reverse scan weights
     void *E;          // gradient of the memory at the end of the chunk (Plan::lay)
     // Used twice in bf16: chunk_dz leaves in it what the rounding of tAvT left behind, chunk_intra reads that and (where the
     // wide contractions run on their own) puts scale*Bm^T in its place.  Both belong to one (chunk, head), i.e. to one

@@ -13,10 +13,12 @@
 //
 //   * one workgroup per (sequence, head, column slice); the slice of acc lives in MFMA
 //     accumulators for the whole sequence;
-//   * the tiles of chunk n+1 are prefetched into registers while chunk n is multiplied;
-//   * snapshots leave by 16-byte pieces: the accumulator tiles are D[column][slot], with the columns dealt to
-//     the matrix rows so that a lane holds runs of consecutive columns of one slot, and a workgroup's tile of
-//     the record is one contiguous block (the records are tiled by column slice for this);
+//   * the operands of the next chunks are prefetched into registers while one is multiplied.  Every access to memory is
+//     by whole lines: the weights come in fragment order (see frag_order), the token rows go through LDS as they lie
+//     and are read back by the transposing LDS load, snapshots are put together in LDS;
+//   * snapshots are one contiguous block per workgroup and chunk (the records are tiled by column slice for this).
+//     With the chip full the launch is bound by these bytes: 8 x 2048 tokens, 4 heads, d = 512, 64 slots, 285 MB in 53 us; loads
+//     and stores of this pattern alone, without arithmetic, take 43;
 //   * workgroups that share (sequence, head) — and therefore W and dec — are mapped to
 //     the same XCD so those re-reads hit its L2.
 #include "gsa_chunk.h"
@@ -63,16 +65,21 @@ __global__ __launch_bounds__(Geo<T>::NT) void gate_kernel(ChunkMap cm, int H, co
         w[tt] *= __expf(after);
         after += x[tt];
     }
-    T *W = Wf + ch * M * C + (size_t)i * C + part * TP;
-    if constexpr (TP % 8 == 0) {
+    T *W = Wf + ch * M * C;   // in fragment order: a slot's neighbours write next to it
+    constexpr int PV = 16 / sizeof(T);
+    static_assert(TP % 4 == 0, "tokens per thread");
 #pragma unroll
-        for (int t8 = 0; t8 < TP; t8 += 8) {
-            const float y[8] = {w[t8], w[t8 + 1], w[t8 + 2], w[t8 + 3], w[t8 + 4], w[t8 + 5], w[t8 + 6], w[t8 + 7]};
-            store8<T>(W + t8, y);
+    for (int t4 = 0; t4 < TP; t4 += 4) {
+        const int t = part * TP + t4;
+        T *dst = W + frag_order<T, C / 32>(i, t / PV * PV) + t % PV;
+        if (sizeof(T) == 2 && TP % 8 == 0) {
+            if (t4 % 8 == 0) {
+                const float y[8] = {w[t4], w[t4 + 1], w[t4 + 2], w[t4 + 3], w[(t4 + 4) % TP], w[(t4 + 5) % TP], w[(t4 + 6) % TP], w[(t4 + 7) % TP]};
+                store8<T>(dst, y);
+            }
+        } else {
+            store4(dst, w[t4], w[t4 + 1], w[t4 + 2], w[t4 + 3]);
         }
-    } else {
-        static_assert(TP == 4, "tokens per thread");
-        store4(W, w[0], w[1], w[2], w[3]);
     }
     if (part == 0) dec[ch * M + i] = __expf(after);
 }
@@ -81,7 +88,7 @@ __global__ __launch_bounds__(Geo<T>::NT) void gate_kernel(ChunkMap cm, int H, co
 // The scan.
 // ---------------------------------------------------------------------------------------
 template <typename T> struct ScanArgs {
-    const T *W;            // [chunk][H][parts][M][C]
+    const T *W;            // [chunk][H][parts], [M][C] in fragment order
     int w_parts;           // 1 (forward) or 2 (reverse: key part, value part)
     const float *dec;      // [chunk][H][M]
     const T *xk, *xv;      // token tensors feeding the key / value columns
@@ -98,32 +105,79 @@ template <typename T> struct ScanArgs {
     float *sumD;           // [n_seqs][max_seg][H][slices][M]    its total decay
 };
 
-template <typename T, int M, int NS, bool TILE> struct ScanLds {
-    static constexpr int C = Geo<T>::C;
-    static constexpr int PAD = Atom<T>::kPad;
-    static constexpr int ldw = C + PAD;      // XT [NS][ldw]
-    // a workgroup's waves share out the slots first, then the columns
-    static constexpr int NW = Geo<T>::NW;
-    static constexpr int WS = M / 16 < NW ? M / 16 : NW, WC = NW / WS;
-    static constexpr int MI = M / (16 * WS), NI = NS / (16 * WC);   // slot and column tiles of a wave
-    // We [M][C] has no padding: its 8-element groups are XOR-swizzled by the row instead (we_off), which
-    // keeps the fragment reads of 16 rows off each other's banks just as well.
-    static constexpr int GW = C / 8;         // groups per row
-    __device__ static __forceinline__ int we_off(int i, int t8) { return i * C + (((t8 >> 3) ^ (i & (GW - 1))) << 3); }
-    // one set per parity of the chunk's position in the walk: a set is written while the other is read
-    static constexpr size_t szW = sizeof(T) * M * C, szX = sizeof(T) * NS * ldw;
-    static constexpr size_t oW = 0;
-    static constexpr size_t oX = oW + szW;
-    static constexpr size_t oDec = oX + szX;              // chunk decays, fp32 [M]
-    // Where a wave owns whole rows of the snapshot tile (kRows) its 16 slots meet in LDS of its own, so that they leave in
-    // full lines.  Where it owns less than a line of each (kTile: bf16 with 16 and 32 slots) the whole tile can meet in the
-    // set and leave one step later, behind the step's barrier; the rule stands at the launch.
-    static constexpr bool kRows = NI * 16 == NS, kTile = TILE && NI * 16 * sizeof(T) < 128;
-    static constexpr int ldx = NS + PAD;
-    static constexpr size_t oSn = oDec + sizeof(float) * M, szSn = kTile ? sizeof(T) * M * ldx : 0;
-    static constexpr size_t set = oSn + szSn;
-    static constexpr size_t oEx = 2 * set, szEx = kRows ? sizeof(T) * 16 * ldx : 0;   // per wave
-    static constexpr size_t bytes = oEx + NW * szEx;
+// Shape of a scan workgroup: four waves that share out the slots (WS), then the columns (WC); a wave holds MI x NI tiles.
+// (Eight waves, of two column tiles each with 64 slots, load the weights twice: 8 x 2048 tokens, 4 heads, d = 512 64 us
+// against 56; 32 slots 47 against 44.)
+template <typename T, int M> struct ScanGeo {
+    static constexpr int C = Geo<T>::C, NS = kSnapTile, NW = 4, NT = NW * kWave;
+    static constexpr int WS = M < 64 ? M / 16 : 4, WC = NW / WS, MI = M / (16 * WS), NI = NS / (16 * WC);
+};
+
+template <typename T, int M> struct ScanLds {
+    using G = ScanGeo<T, M>;
+    // Per parity of the chunk's position in the walk, one written while the other is read: the token tile [C][NS] as it lies
+    // in memory (TokRows), and the snapshot tile, which leaves in whole lines one step later, behind the step's barrier.
+    // (Straight from the registers a store takes 16 bytes or 32 of each of many lines: d = 512, 64 slots, 512 workgroups 62 us
+    // against 57; 32 slots 57 against 47; 128 workgroups 31 against 30.)
+    static constexpr size_t szX = sizeof(T) * G::C * G::NS;
+    static constexpr int ldx = G::NS + Atom<T>::kPad;
+    static constexpr size_t oSn = szX, szSn = sizeof(T) * M * ldx;
+    static constexpr size_t set = oSn + szSn, bytes = 2 * set;
+};
+
+// Matrix-core operands from a token tile that lies in LDS as it lies in memory ([token][column]), and the columns they
+// leave a lane with.  frags: the A operands X^T of one depth-32 step for a wave's NI column tiles; after the product, a
+// lane's accumulators hold 4*NI consecutive columns from 4*NI*(l/16) on, group g of four by get / set.
+//   bf16: the transposing LDS load hands a lane four tokens of one column; which columns is the lane's choice.
+//   fp32: there is no such load for 32 bits, and none is needed: a lane's NI tiles are dealt NI consecutive columns of a row.
+template <typename T, int NS, int NI> struct TokRows;
+template <int NS, int NI> struct TokRows<bf16_t, NS, NI> {
+    static_assert(NS == TrTile<NI>::kCols && (NI == 1 || NI == 2 || NI == 4), "columns per lane");
+    typedef bf16x8 Piece;   // 16 bytes of one row
+    __device__ static __forceinline__ void put(bf16_t *X, int row, int p, const Piece &x) { TrTile<NI>::put(X, row, p, x); }
+    uint32_t off[NI];   // where this lane reads, per column tile
+    __device__ __forceinline__ TokRows(int wcol, int lane)
+    {
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni) off[ni] = TrTile<NI>::lane_off((wcol >> 2) + NI * (lane & 3) + ni, lane);
+    }
+    __device__ __forceinline__ void frags(bf16x8 (&f)[NI], const bf16_t *X, int k0) const
+    {
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni) f[ni] = TrTile<NI>::frag(X + k0 * NS + off[ni]);
+    }
+    __device__ static __forceinline__ f32x4 get(const f32x4 (&acc)[NI], int g) { return acc[g]; }
+    __device__ static __forceinline__ void set(f32x4 (&acc)[NI], int g, const f32x4 &x) { acc[g] = x; }
+};
+template <int NS, int NI> struct TokRows<float, NS, NI> {
+    static_assert(NI == 1 || NI == 2 || NI == 4, "columns per lane");
+    typedef f32x4 Piece;
+    __device__ static __forceinline__ void put(float *X, int row, int p, const Piece &x) { *reinterpret_cast<f32x4 *>(X + row * NS + p * 4) = x; }
+    uint32_t off;
+    __device__ __forceinline__ TokRows(int wcol, int lane) : off(8 * (lane >> 4) * NS + wcol + NI * (lane & 15)) {}
+    __device__ __forceinline__ void frags(f32x8 (&f)[NI], const float *X, int k0) const
+    {
+        typedef float vec __attribute__((ext_vector_type(NI)));
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const vec x = *reinterpret_cast<const vec *>(X + (k0 + e) * NS + off);
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni) f[ni][e] = x[ni];
+        }
+    }
+    // matrix row rho = 4*(l/16) + j of tile ni is column NI*rho + ni
+    __device__ static __forceinline__ f32x4 get(const f32x4 (&acc)[NI], int g)
+    {
+        f32x4 x;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = acc[(4 * g + e) % NI][(4 * g + e) / NI];
+        return x;
+    }
+    __device__ static __forceinline__ void set(f32x4 (&acc)[NI], int g, const f32x4 &x)
+    {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[(4 * g + e) % NI][(4 * g + e) / NI] = x[e];
+    }
 };
 
 // MODE 0: one workgroup walks a whole sequence.  A sequence of many chunks leaves the chip waiting on
@@ -132,21 +186,24 @@ template <typename T, int M, int NS, bool TILE> struct ScanLds {
 // and leaves what the segment adds (sumY) and its total decay (sumD); MODE 2 walks every segment for
 // real, starting from the memory its predecessors leave behind, which it gets by running the
 // recurrence over their summaries (at most max_seg - 1 steps of an element-wise update).
-template <typename T, int M, int NS, bool REVERSE, int MODE, bool TILE>
-__global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void scan_kernel(ChunkMap cm, int H, int d_k, int d_v, int n_seqs,
-                                                          ScanArgs<T> a)
+//
+// AHEAD: chunks whose loads are in flight while one multiplies (the rule stands at the launch).
+template <typename T, int M, bool REVERSE, int MODE, int AHEAD>
+__global__ __launch_bounds__((ScanGeo<T, M>::NT), 2) void scan_kernel(ChunkMap cm, int H, int d_k, int d_v,
+                                                                                    int n_seqs, ScanArgs<T> a)
 {
-    using L = ScanLds<T, M, NS, TILE>;
-    constexpr int C = Geo<T>::C, NT = Geo<T>::NT;
-    constexpr int MI = L::MI, NI = L::NI;
-    constexpr int WVEC = M * C / 8, WV = (WVEC + NT - 1) / NT;
+    using L = ScanLds<T, M>;
+    using G = ScanGeo<T, M>;
+    constexpr int C = G::C, NS = G::NS, NT = G::NT, MI = G::MI, NI = G::NI;
+    using R = TokRows<T, NS, NI>;
+    typedef typename R::Piece Piece;
+    constexpr int PV = 16 / sizeof(T), PR = NS / PV, XV = C * PR / NT;   // elements per piece, pieces per row, pieces per thread
+    static_assert(XV * NT == C * PR && NT % PR == 0, "whole pieces per thread, all in one column group");
     extern __shared__ __align__(16) unsigned char smem[];
-    auto We = [&](int b) { return reinterpret_cast<T *>(smem + b * L::set + L::oW); };
-    auto XT = [&](int b) { return reinterpret_cast<T *>(smem + b * L::set + L::oX); };
-    auto Dec = [&](int b) { return reinterpret_cast<float *>(smem + b * L::set + L::oDec); };
+    auto XT = [&](int b) { return reinterpret_cast<T *>(smem + b * L::set); };
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int r = lane & 15, g8 = (lane >> 4) * 8;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 15;
     const int D = d_k + d_v;
     const int nsl = D / NS;
     // XCD-aware placement: consecutive workgroup ids go round-robin over the 8 XCDs.  The slices of one
@@ -193,13 +250,9 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void scan_kernel(Chun
 
     int chunk0, nch_seq, tok0, ntok;
     seq_lookup(cm, s, chunk0, nch_seq, tok0, ntok);
-    // acc[mi][ni][j]: slot slot0 + 16*mi, column lcol + tcol(ni) + j of the slice.  Matrix row rho of column tile ni is
-    // column wcol + (rho/4)*4*NP + tcol(ni) + rho%4: a lane's registers are runs of 4*NP consecutive columns, and
-    // the four lanes that share a slot cover 16*NP of them in a row with each store.
-    constexpr int NP = NI < 2 ? 1 : 2;
-    const int slot0 = (wave % L::WS) * MI * 16 + r, wcol = (wave / L::WS) * 16 * NI;
-    const int lcol = wcol + (lane >> 4) * 4 * NP, xrow = wcol + (r >> 2) * 4 * NP + (r & 3);
-    auto tcol = [](int ni) { return (ni / NP) * 16 * NP + (ni % NP) * 4; };
+    // acc[mi]: slot slot0 + 16*mi, columns lcol + 4*g .. +3 of the slice in group g
+    const int slot0 = (wave % G::WS) * MI * 16 + r, wcol = (wave / G::WS) * 16 * NI, lcol = wcol + (lane >> 4) * 4 * NI;
+    const R rows_of(wcol, lane);
     // the chunks this workgroup walks: [first, first + nch) of the sequence
     int first = 0, nch = nch_seq, nseg = 1;
     if (MODE != 0) {
@@ -219,11 +272,11 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void scan_kernel(Chun
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-            for (int ni = 0; ni < NI; ++ni) {
+            for (int g = 0; g < NI; ++g) {
                 const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-                acc[mi][ni] = (MODE != 1 && S0) ? *reinterpret_cast<const f32x4 *>(
-                                                      S0 + (((size_t)s * H + h) * M + slot0 + 16 * mi) * dsrc + c0 + lcol + tcol(ni))
-                                                : zero;
+                R::set(acc[mi], g, (MODE != 1 && S0) ? *reinterpret_cast<const f32x4 *>(
+                                                           S0 + (((size_t)s * H + h) * M + slot0 + 16 * mi) * dsrc + c0 + lcol + 4 * g)
+                                                     : zero);
             }
         if (MODE == 2 && !starts_walk) {
             // the memory at the start of this segment: the recurrence over the summaries of the segments
@@ -239,8 +292,9 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void scan_kernel(Chun
                 for (int mi = 0; mi < MI; ++mi) {
                     const float dd = Dd[slot0 + 16 * mi];
 #pragma unroll
-                    for (int ni = 0; ni < NI; ++ni)
-                        acc[mi][ni] = dd * acc[mi][ni] + *reinterpret_cast<const f32x4 *>(Y + (size_t)(slot0 + 16 * mi) * D + lcol + tcol(ni));
+                    for (int g = 0; g < NI; ++g)
+                        R::set(acc[mi], g, dd * R::get(acc[mi], g) +
+                                               *reinterpret_cast<const f32x4 *>(Y + (size_t)(slot0 + 16 * mi) * D + lcol + 4 * g));
                 }
             }
         }
@@ -253,184 +307,168 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void scan_kernel(Chun
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi) dprod[mi] = 1.f;
 
-    // Operands of one chunk, staged in registers: the loads of the next two chunks are in flight
-    // while the current one multiplies (one chunk ahead does not cover the memory latency of a
-    // loaded chip, and the chain over the chunks is the only sequential part of the method).
-    struct Stage {
-        Raw8<T> wreg[WV];
-        TokTile<T, C, NS, NT> xt;   // transposed (and swizzled) when it enters LDS
-        float dec;                  // decay of slot tid (threads < M)
+    // Operands of one chunk, in registers: the weights are matrix-core operands as they lie in memory, the token rows wait
+    // there for their turn in LDS.  The loads of AHEAD chunks are in flight while one multiplies: a step takes a
+    // fraction of the memory latency, and the chain over the chunks is the only sequential part of the method.
+    struct Weights {
+        typename Atom<T>::Frag w[C / 32][MI];
+        float dec[MI];
     };
-    auto fetch = [&](Stage &st, int n) {
-        const size_t ch = (size_t)(chunk0 + n) * H + h;
-        st.dec = a.dec[ch * M + (tid & (M - 1))];
-        const T *Wg = a.W + ch * a.w_parts * M * C + wpart;
-#pragma unroll
-        for (int u = 0; u < WV; ++u) {
-            const int idx = tid + NT * u;
-            st.wreg[u].load(Wg + (size_t)(idx < WVEC ? idx : 0) * 8);
-        }
-        const int len = min(C, ntok - n * C);
-        const T *Xg = src + ((size_t)(tok0 + n * C) * H + h) * dsrc + c0;
-        st.xt.template load<true>(Xg, (size_t)H * dsrc, len, NS, tid);
+    struct Tokens {
+        Piece x[XV];
+        int len;
     };
-    // accumulator -> this workgroup's tile of a record (rec: its start); read back by the next kernel: cached
-    auto snapshot = [&](T *rec) {
-        static_assert(NS == kSnapTile, "one workgroup owns one tile of the record");
-        T *dst = rec + (isK ? a.lay.oK : a.lay.oV) + (size_t)(c0 / kSnapTile) * (M * kSnapTile) + slot0 * kSnapTile + lcol;
+        // Bases are uniform and advance from chunk to chunk, lanes add 32-bit byte offsets.  Positions past the end of the walk
+    // repeat the last chunk, so that refills can be issued unconditionally (a refill under a branch makes the number of
+    // loads in flight unknown to the compiler, which then waits for all of them wherever it needs one).
+    const int n0 = first + (REVERSE ? nch - 1 : 0);   // first chunk of the walk
+    constexpr int dir = REVERSE ? -1 : 1;
+    const int64_t dW = (int64_t)dir * H * a.w_parts * (M * C * (int)sizeof(T)), dD = (int64_t)dir * H * (M * (int)sizeof(float));
+    const int64_t dX = (int64_t)dir * C * H * dsrc * (int)sizeof(T), dS = dir * (int64_t)H * a.lay.stride;
+    const size_t ch0 = (size_t)(chunk0 + n0) * H + h;
+    const char *wp = reinterpret_cast<const char *>(a.W + ch0 * a.w_parts * M * C + wpart), *dp = reinterpret_cast<const char *>(a.dec + ch0 * M);
+    const char *xp = reinterpret_cast<const char *>(src + ((size_t)(tok0 + n0 * C) * H + h) * dsrc + c0);
+    static_assert(NS == kSnapTile, "one workgroup owns one tile of the record");
+    auto tile_of = [&](T *rec) { return rec + (isK ? a.lay.oK : a.lay.oV) + (size_t)(c0 / kSnapTile) * (M * kSnapTile); };   // contiguous [M][NS]
+    T *sp = tile_of(a.snap + ch0 * a.lay.stride);   // where the next snapshot goes
+    int wleft = nch - 1, xleft = nch - 1;   // chunks the weights and the tokens can still move on
+    const uint32_t wtile = (wave % G::WS) * MI * (C / 32), doff = (uint32_t)slot0 * sizeof(float);
+    const uint32_t xstep = (uint32_t)H * dsrc * sizeof(T), xcol = (tid % PR) * 16;
+    auto fetch_w = [&](Weights &st) {
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi) {
-            T *d = dst + mi * 16 * kSnapTile;
-            if constexpr (L::kRows) {
-                T *X = reinterpret_cast<T *>(smem + L::oEx + wave * L::szEx);
+            st.dec[mi] = *reinterpret_cast<const float *>(dp + (doff + 64 * mi));
 #pragma unroll
-                for (int ni = 0; ni < NI; ni += 2) {
-                    const f32x4 x = acc[mi][ni], y = acc[mi][ni + 1];
-                    const float v[8] = {x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]};
-                    store8<T>(X + r * L::ldx + lcol + tcol(ni), v);
-                }
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                T *rows = dst - r * kSnapTile - lcol + mi * 16 * kSnapTile;
+            for (int ks = 0; ks < C / 32; ++ks)
+                st.w[ks][mi] = load_frag_order(reinterpret_cast<const T *>(wp) + (wtile + mi * (C / 32) + ks) * 512, lane);
+        }
+        const bool more = wleft > 0;
+        wp += more ? dW : 0;
+        dp += more ? dD : 0;
+        --wleft;
+    };
+    int xn = n0;
+    auto fetch_x = [&](Tokens &st) {
+        st.len = min(C, ntok - xn * C);
 #pragma unroll
-                for (int u = 0; u < 16 * NS / 8 / kWave; ++u) {
-                    const int idx = lane + kWave * u;
-                    Raw8<T> x;
-                    x.load(X + (idx / (NS / 8)) * L::ldx + (idx % (NS / 8)) * 8);
-                    x.store(rows + (size_t)idx * 8);
-                }
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            } else if constexpr (NI == 1) {
-                store4(d, acc[mi][0][0], acc[mi][0][1], acc[mi][0][2], acc[mi][0][3]);
-            } else {
+        for (int v = 0; v < XV; ++v) {
+            const uint32_t row = min(tid / PR + v * (NT / PR), st.len - 1);
+            st.x[v] = __builtin_nontemporal_load(reinterpret_cast<const Piece *>(xp + (row * xstep + xcol)));
+        }
+        const bool more = xleft > 0;
+        xp += more ? dX : 0;
+        xn += more ? dir : 0;
+        --xleft;
+    };
+    auto tokens_to_lds = [&](const Tokens &st, int b) {
 #pragma unroll
-                for (int ni = 0; ni < NI; ni += 2) {
-                    const f32x4 x = acc[mi][ni], y = acc[mi][ni + 1];
-                    const float v[8] = {x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]};
-                    store8<T>(d + tcol(ni), v);
-                }
+        for (int v = 0; v < XV; ++v) {
+            const int row = tid / PR + v * (NT / PR);
+            const f32x4 none = {0.f, 0.f, 0.f, 0.f};   // missing rows are zero
+            Piece x = __builtin_bit_cast(Piece, row < st.len ? __builtin_bit_cast(f32x4, st.x[v]) : none);
+            if (phi) {   // uniform over the workgroup
+#pragma unroll
+                for (int e = 0; e < PV; ++e) x[e] = from_f32<T>(swish_value(to_f32(x[e])));
             }
+            R::put(XT(b), row, tid % PR, x);
         }
     };
-    // position in the walk -> chunk; positions past the end repeat the last chunk, so that refills can be
-    // issued unconditionally (a refill under a branch makes the number of loads in flight unknown to the
-    // compiler, which then waits for all of them wherever it needs one)
-    auto chunk_of = [&](int it) { it = min(it, nch - 1); return first + (REVERSE ? nch - 1 - it : it); };
-    // kTile: accumulator -> tile of set b, and (behind a barrier) that tile -> this workgroup's tile of a record
+    // The accumulator on its way to a record, in two halves: what a lane holds goes to the tile of a set, and from there
+    // (behind a barrier) to this workgroup's tile of the record.
     auto gather = [&](int b) {
         T *X = reinterpret_cast<T *>(smem + b * L::set + L::oSn) + slot0 * L::ldx + lcol;
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi)
             if constexpr (NI == 1) {
-                store4(X + mi * 16 * L::ldx, acc[mi][0][0], acc[mi][0][1], acc[mi][0][2], acc[mi][0][3]);
+                const f32x4 x = R::get(acc[mi], 0);
+                store4(X + mi * 16 * L::ldx, x[0], x[1], x[2], x[3]);
             } else {
 #pragma unroll
-                for (int ni = 0; ni < NI; ni += 2) {
-                    const f32x4 x = acc[mi][ni], y = acc[mi][ni + 1];
+                for (int g = 0; g < NI; g += 2) {
+                    const f32x4 x = R::get(acc[mi], g), y = R::get(acc[mi], g + 1);
                     const float v[8] = {x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]};
-                    store8<T>(X + mi * 16 * L::ldx + tcol(ni), v);
+                    store8<T>(X + mi * 16 * L::ldx + 4 * g, v);
                 }
             }
     };
-    auto send = [&](T *rec, int b) {
+    auto send = [&](T *tile, int b) {
         const T *X = reinterpret_cast<const T *>(smem + b * L::set + L::oSn);
-        T *dst = rec + (isK ? a.lay.oK : a.lay.oV) + (size_t)(c0 / kSnapTile) * (M * kSnapTile);   // contiguous [M][NS]
-        static_assert(!L::kTile || M * NS / 8 <= NT, "one 16-byte piece per thread at most");
-        const int idx = min(tid, M * NS / 8 - 1);
-        Raw8<T> x;
-        x.load(X + (idx / (NS / 8)) * L::ldx + (idx % (NS / 8)) * 8);   // clamped: the read is not under the branch
-        if (tid < M * NS / 8) x.store(dst + (size_t)tid * 8);
-    };
-    auto snap_of = [&](int it) { return a.snap + ((size_t)(chunk0 + chunk_of(it)) * H + h) * a.lay.stride; };
-    // staged registers -> LDS set b (W as is, X transposed)
-    auto stage_to_lds = [&](const Stage &st, int b) {
-        T *w = We(b);
+        constexpr int N = M * PR;
 #pragma unroll
-        for (int u = 0; u < WV; ++u) {
-            const int idx = tid + NT * u;
-            if (idx < WVEC) {
-                const int i = idx / (C / 8), tg = idx - i * (C / 8);
-                st.wreg[u].store(w + L::we_off(i, tg * 8));
-            }
+        for (int u = 0; u < (N + NT - 1) / NT; ++u) {
+            const int idx = min(tid + u * NT, N - 1);
+            const f32x4 x = *reinterpret_cast<const f32x4 *>(X + (idx / PR) * L::ldx + (idx % PR) * PV);   // clamped: the read is not under the branch
+            if (N % NT == 0 || tid + u * NT < N) *reinterpret_cast<f32x4 *>(tile + (uint32_t)idx * PV) = x;   // read back by the next kernel: cached
         }
-        if (phi) st.xt.template store_transposed<true>(XT(b), L::ldw, NS, tid);
-        else st.xt.store_transposed(XT(b), L::ldw, NS, tid);
-        Dec(b)[tid & (M - 1)] = st.dec;   // every thread stores (slots have NT/M writers of the same value): no branch around a loaded value
     };
     // The walk, software-pipelined with ONE barrier per chunk.  At the top of step `it` LDS set it%2
-    // holds the operands of chunk `it` (written during the previous step).  The step
-    //   - sends the accumulator (the memory chunk `it` starts from) to the snapshots (kTile: to its set, and the previous one's
-    //     from the other set to the snapshots),
-    //   - applies S <- Diag(dec) S + W X with fragments read from its own set,
-    //   - writes the operands of chunk it+1 (register stage `nx`) into the other set and refills
-    //     that stage with chunk it+3,
-    // so only the accumulator update lies on the chain from one chunk to the next; everything
-    // else rides beside it.  A step used to write its snapshot with sixteen 2-byte LDS stores per thread and tile, which
-    // is what a workgroup alone on its CU waits for: m = 128, 256 workgroups 37 -> 31 us; fwd d = 128, 128 workgroups 36 ->
-    // 30 us; eight sequences of 2048 tokens, d = 512, m = 64 (bound by bandwidth) 59 -> 56 us.  Straight from the
-    // registers, by 16-byte pieces 32 bytes apart, the last one took 63 us.
-    auto step = [&](Stage &nx, int it) {
-        const int b = it & 1;
-        if constexpr (MODE != 1 && L::kTile) {
-            if (it > 0) send(snap_of(it - 1), b ^ 1);
+    // holds the token rows of chunk `it` (written during the previous step).  The step
+    //   - sends the memory the previous step gathered, and gathers the accumulator, which chunk `it` starts from,
+    //   - applies S <- Diag(dec) S + W X,
+    //   - writes the token rows of chunk it+1 into the other set,
+    // and the caller refills the registers that became free, so only the accumulator update lies on the chain from one
+    // chunk to the next.
+    // The walk is rounded up to whole trips of AHEAD steps: steps past its end (real = false) update and store nothing.
+    // (Their store is switched off lane by lane and not by a branch, for the same reason as the refills.)
+    int lane_nch = nch;
+    asm("" : "+v"(lane_nch));
+    auto step = [&](const Weights &op, const Tokens &nx, int it, int b) {   // b = it % 2, a constant where it is called
+        typename Atom<T>::Frag bf[C / 32][NI];
+#pragma unroll
+        for (int ks = 0; ks < C / 32; ++ks) rows_of.frags(bf[ks], XT(b), ks * 32);
+        if constexpr (MODE != 1) {
+            if (it > 0 && it <= lane_nch) send(sp - dS, b ^ 1);
             gather(b);
-        } else if constexpr (MODE != 1) {
-            snapshot(snap_of(it));
+            sp += dS;
         }
-        typename Atom<T>::Frag af[C / 32][MI], bf[C / 32][NI];
-        const T *w = We(b), *x = XT(b);
+        if (it < nch) {
 #pragma unroll
-        for (int ks = 0; ks < C / 32; ++ks) {
+            for (int mi = 0; mi < MI; ++mi) {
+                if (MODE == 1) dprod[mi] *= op.dec[mi];
 #pragma unroll
-            for (int mi = 0; mi < MI; ++mi) af[ks][mi] = Atom<T>::load(w + L::we_off(slot0 + 16 * mi, ks * 32 + g8));
+                for (int ni = 0; ni < NI; ++ni) acc[mi][ni] *= op.dec[mi];
+            }
 #pragma unroll
-            for (int ni = 0; ni < NI; ++ni)
-                bf[ks][ni] = Atom<T>::load(x + xt_off<C>(xrow + tcol(ni), ks * 32 + g8, L::ldw));
+            for (int ks = 0; ks < C / 32; ++ks)
+#pragma unroll
+                for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+                    for (int ni = 0; ni < NI; ++ni) Atom<T>::mma(acc[mi][ni], bf[ks][ni], op.w[ks][mi]);
         }
-#pragma unroll
-        for (int mi = 0; mi < MI; ++mi) {
-            const float dcur = Dec(b)[slot0 + 16 * mi];
-            if (MODE == 1) dprod[mi] *= dcur;
-#pragma unroll
-            for (int ni = 0; ni < NI; ++ni) acc[mi][ni] *= dcur;
-        }
-#pragma unroll
-        for (int ks = 0; ks < C / 32; ++ks)
-#pragma unroll
-            for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-                for (int ni = 0; ni < NI; ++ni) Atom<T>::mma(acc[mi][ni], bf[ks][ni], af[ks][mi]);
-        stage_to_lds(nx, b ^ 1);
+        tokens_to_lds(nx, b ^ 1);
     };
-    // (the scheduling fences keep the compiler from hoisting a stage's refill above the LDS stores
-    // that read its registers: it would then load into other registers and copy them back at the
-    // end of the trip, which means waiting for loads that were only just issued)
-    Stage sa, sb;
+    // (the scheduling fences keep the compiler from hoisting a refill above the reads of its registers: it would
+    // then load into other registers and copy them back at the end of the trip, which means waiting for loads that
+    // were only just issued)
     if (nch > 0) {
-        fetch(sa, chunk_of(0));
-        fetch(sb, chunk_of(1));
-        stage_to_lds(sa, 0);
+        Weights op[AHEAD];
+        Tokens tk[AHEAD];
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) {
+            fetch_x(tk[u]);
+            __builtin_amdgcn_sched_barrier(0);   // in the order of their use, as in the loop
+            fetch_w(op[u]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        tokens_to_lds(tk[0], 0);
         __builtin_amdgcn_sched_barrier(0);
-        fetch(sa, chunk_of(2));
+        fetch_x(tk[0]);
         __syncthreads();
-    }
-    int it = 0;
-    for (; it + 1 < nch; it += 2) {   // two steps per trip: each stage keeps its own registers
-        step(sb, it);                 // operands in set 0; sb holds chunk it+1
-        __builtin_amdgcn_sched_barrier(0);
-        fetch(sb, chunk_of(it + 3));
-        __syncthreads();
-        step(sa, it + 1);             // operands in set 1; sa holds chunk it+2
-        __builtin_amdgcn_sched_barrier(0);
-        fetch(sa, chunk_of(it + 4));
-        __syncthreads();
-    }
-    if (it < nch) {
-        step(sb, it);
-        __syncthreads();
-        ++it;
-    }
-    if constexpr (MODE != 1 && L::kTile) {
-        if (nch > 0) send(snap_of(nch - 1), (nch - 1) & 1);
+        int it = 0;
+        do {
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u) {   // every position keeps its own registers
+                step(op[u], tk[(u + 1) % AHEAD], it + u, u & 1);
+                __builtin_amdgcn_sched_barrier(0);
+                fetch_w(op[u]);
+                fetch_x(tk[(u + 1) % AHEAD]);
+                __syncthreads();
+            }
+            it += AHEAD;
+        } while (it < nch);
+        if constexpr (MODE != 1) {
+            if (it == nch) send(sp - dS, (AHEAD - 1) & 1);
+        }
     }
     if (MODE == 1) {   // what this segment adds and how much it decays, for its successors
         const size_t rec = ((size_t)s * a.max_seg + seg) * H + h;
@@ -438,7 +476,8 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void scan_kernel(Chun
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-            for (int ni = 0; ni < NI; ++ni) *reinterpret_cast<f32x4 *>(Y + (size_t)(slot0 + 16 * mi) * D + lcol + tcol(ni)) = acc[mi][ni];
+            for (int g = 0; g < NI; ++g)
+                *reinterpret_cast<f32x4 *>(Y + (size_t)(slot0 + 16 * mi) * D + lcol + 4 * g) = R::get(acc[mi], g);
         if (lcol == 0) {   // one lane per slot
             float *Dd = a.sumD + (rec * nsl + slice) * M;
 #pragma unroll
@@ -453,19 +492,14 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void scan_kernel(Chun
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-            for (int ni = 0; ni < NI; ++ni)
-                *reinterpret_cast<f32x4 *>(ST + (((size_t)s * H + h) * M + slot0 + 16 * mi) * dsrc + c0 + lcol + tcol(ni)) = acc[mi][ni];
+            for (int g = 0; g < NI; ++g)
+                *reinterpret_cast<f32x4 *>(ST + (((size_t)s * H + h) * M + slot0 + 16 * mi) * dsrc + c0 + lcol + 4 * g) = R::get(acc[mi], g);
     }
     if (a.outJ) {
-        T *rec = a.outJ + ((size_t)s * H + h) * a.lay.stride;
-        if constexpr (L::kTile) {
-            __syncthreads();   // the last snapshot may still be on its way out of the set
-            gather(0);
-            __syncthreads();
-            send(rec, 0);
-        } else {
-            snapshot(rec);
-        }
+        __syncthreads();   // the last snapshot may still be on its way out of the set
+        gather(0);
+        __syncthreads();
+        send(tile_of(a.outJ + ((size_t)s * H + h) * a.lay.stride), 0);
     }
 }
 
@@ -501,32 +535,31 @@ hipError_t launch_gates(const Plan &pl, const Work &w, const float *g, const flo
 #undef GSA_GATES
 }
 
-template <typename T, int M, int NS, bool REVERSE, int MODE>
+template <typename T, int M, bool REVERSE, int MODE>
 static hipError_t run_scan_mode(const Plan &pl, const ChunkMap &cm, const ScanArgs<T> &a, int slot, hipStream_t st)
 {
-    const int total = (pl.d_k + pl.d_v) / NS * pl.H * pl.n_seqs * (MODE == 0 ? 1 : a.max_seg);
-    // Snapshots through the set (kTile) or straight from the registers, in pieces of 32 or 64 bytes.  With more than one
-    // workgroup on a CU the launch is bound by what leaves the chip and whole lines are faster: 8 x 2048 tokens, 4 heads, 16
-    // slots, 320 workgroups 33 us against 36, 640 workgroups 52 against 59; 32 slots 37 / 40 and 61 / 65.  With at most one
-    // it waits for the chain, which the detour lengthens: 16 slots, 256 workgroups 27.5 against 25.0; 32 slots, 16
-    // workgroups (1024 tokens) 14.4 against 13.3.
-    constexpr bool can = MODE != 1 && ScanLds<T, M, NS, true>::kTile;   // a summary pass takes no snapshots
-    const bool tile = can && total > 256;
-    auto kern = tile ? scan_kernel<T, M, NS, REVERSE, MODE, can> : scan_kernel<T, M, NS, REVERSE, MODE, false>;
-    const size_t lds = tile ? ScanLds<T, M, NS, can>::bytes : ScanLds<T, M, NS, false>::bytes;
+    using G = ScanGeo<T, M>;
+    const int total = (pl.d_k + pl.d_v) / G::NS * pl.H * pl.n_seqs * (MODE == 0 ? 1 : a.max_seg);
+    // Prefetch depth: with at most one workgroup per CU the launch waits for the chain and its loads (8 x 2048 tokens, 4
+    // heads, d = 128, 64 slots, 128 workgroups: 27.5 us four chunks ahead, 30.0 two; d = 512, 4 sequences, 256 workgroups:
+    // 31.2 and 32.6); with more, more loads in flight only get into the way of the stores (512 workgroups: 57 and 56).  With 128
+    // slots (256 workgroups 26.5 and 25.4) and for fp32 from 64 on (registers): two.
+    constexpr int kDeep = M > 64 || (sizeof(T) == 4 && M > 32) ? 2 : 4;
+    auto kern = total <= 256 ? scan_kernel<T, M, REVERSE, MODE, kDeep> : scan_kernel<T, M, REVERSE, MODE, 2>;
+    constexpr size_t lds = ScanLds<T, M>::bytes;
     GSA_HIP_TRY(allow_lds(kern, lds));
     KernelTimer kt(slot, st);
-    hipLaunchKernelGGL(kern, dim3(total), dim3(Geo<T>::NT), lds, st, cm, pl.H, pl.d_k, pl.d_v, pl.n_seqs, a);
+    hipLaunchKernelGGL(kern, dim3(total), dim3(G::NT), lds, st, cm, pl.H, pl.d_k, pl.d_v, pl.n_seqs, a);
     return hipGetLastError();
 }
 
-template <typename T, int M, int NS, bool REVERSE>
+template <typename T, int M, bool REVERSE>
 static hipError_t run_scan(const Plan &pl, const ChunkMap &cm, const ScanArgs<T> &a, hipStream_t st)
 {
     const int slot = REVERSE ? kSlotScanBwd : kSlotScanFwd;
-    if (a.max_seg <= 1) return run_scan_mode<T, M, NS, REVERSE, 0>(pl, cm, a, slot, st);
-    GSA_HIP_TRY((run_scan_mode<T, M, NS, REVERSE, 1>(pl, cm, a, kSlotScanSummary, st)));
-    return run_scan_mode<T, M, NS, REVERSE, 2>(pl, cm, a, slot, st);
+    if (a.max_seg <= 1) return run_scan_mode<T, M, REVERSE, 0>(pl, cm, a, slot, st);
+    GSA_HIP_TRY((run_scan_mode<T, M, REVERSE, 1>(pl, cm, a, kSlotScanSummary, st)));
+    return run_scan_mode<T, M, REVERSE, 2>(pl, cm, a, slot, st);
 }
 
 template <typename T, int M>
@@ -553,8 +586,8 @@ static hipError_t launch_scan_tm(const Plan &pl, const Work &w, const ScanIo &io
     a.sumY = w.sumY;
     a.sumD = w.sumD;
     // 64-column slices: several workgroups per CU, so that their dependent chains overlap
-    if (io.reverse) return run_scan<T, M, 64, true>(pl, cm, a, st);
-    return run_scan<T, M, 64, false>(pl, cm, a, st);
+    if (io.reverse) return run_scan<T, M, true>(pl, cm, a, st);
+    return run_scan<T, M, false>(pl, cm, a, st);
 }
 
 hipError_t launch_scan(const Plan &pl, const Work &w, const ScanIo &io, hipStream_t st)

@@ -17,34 +17,18 @@ template <int M> struct Wide {
     static constexpr int C = Geo<bf16_t>::C, NT = Geo<bf16_t>::NT, PAD = Atom<bf16_t>::kPad;
     static constexpr int KM = (M < 32) ? 32 : M;              // slot rows, padded with zeros to the contraction depth
     static constexpr int lda = C + PAD, lds = KM + PAD;       // A_tok [C][lda], A_slot [C][lds]
-    static constexpr int kCols = 64;
+    static constexpr int kCols = TrTile<2>::kCols;
     static constexpr size_t szBuf = sizeof(bf16_t) * (KM + C) * kCols;   // slot tile, token tile
     static constexpr size_t szTok = sizeof(bf16_t) * C * lda, szSlot = sizeof(bf16_t) * C * lds;
     static constexpr int SV = KM * kCols / 8 / NT, XV = C * kCols / 8 / NT;
     static_assert(SV * NT * 8 == KM * kCols && XV * NT * 8 == C * kCols, "whole 16-byte pieces per thread");
 
-    // Rows of a tile are 128 bytes.  Their 8-byte pieces are XOR-swizzled so that the 32 lanes of half a transposing
-    // load (eight rows, four pieces each) touch every bank once.
-    __device__ static __forceinline__ int swz(int row) { return ((row >> 1) & 1) | (((row >> 3) & 1) << 3); }
-    __device__ static __forceinline__ void put(bf16_t *tile, int row, int cg, bf16x8 x)
-    {
-        const int f = swz(row);
-        const bf16x8 y = __builtin_shufflevector(x, x, 4, 5, 6, 7, 0, 1, 2, 3);
-        *reinterpret_cast<bf16x8 *>(tile + row * kCols + ((cg ^ (f >> 1)) << 3)) = (f & 1) ? y : x;
-    }
     // Fragment of column tile ni: lane l gets column 32*(ni/2) + 8*((l%16)/4) + 4*(ni%2) + l%4 and the rows k0 +
     // 8*(l/16) .. +7, so that a lane of the product D[column][token] holds columns 32*(ni/2) + 8*(l/16) + 4*(ni%2) + j:
     // two runs of eight, and the four lanes that share a token store 64 bytes in a row.
     __device__ static __forceinline__ bf16x8 frag(const bf16_t *tile, int k0, int ni, int lane)
     {
-        typedef short s16x4 __attribute__((ext_vector_type(4)));
-        typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-        const int row = k0 + 8 * (lane >> 4) + ((lane & 15) >> 2), q = 8 * (ni >> 1) + 2 * (lane & 3) + (ni & 1);
-        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(tile + row * kCols + ((q ^ swz(row)) << 2)));
-        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(tile + (row + 4) * kCols + ((q ^ swz(row + 4)) << 2)));
-        typedef short s16x8 __attribute__((ext_vector_type(8)));
-        const s16x8 x = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-        return __builtin_bit_cast(bf16x8, x);
+        return TrTile<2>::frag(tile + k0 * kCols + TrTile<2>::lane_off(8 * (ni >> 1) + 2 * (lane & 3) + (ni & 1), lane));
     }
     struct Stage { bf16x8 s[SV], x[XV]; };
     // One unit: tile `slot` is [M][64] contiguous, rows of `tok` and `out` are `ld` elements apart.
@@ -69,12 +53,12 @@ template <int M> struct Wide {
 #pragma unroll
         for (int v = 0; v < SV; ++v) {
             const int idx = tid + NT * v;
-            put(buf, idx >> 3, idx & 7, (M < KM && idx >= M * 8) ? zero : st.s[v]);
+            TrTile<2>::put(buf, idx >> 3, idx & 7, (M < KM && idx >= M * 8) ? zero : st.s[v]);
         }
 #pragma unroll
         for (int v = 0; v < XV; ++v) {
             const int idx = tid + NT * v;
-            put(buf + KM * kCols, idx >> 3, idx & 7, (idx >> 3) < len ? st.x[v] : zero);   // missing rows are zero
+            TrTile<2>::put(buf + KM * kCols, idx >> 3, idx & 7, (idx >> 3) < len ? st.x[v] : zero);   // missing rows are zero
         }
     }
     // This wave's 16 tokens of one unit.  FULL: every token of the chunk exists (the store is then unconditional,
