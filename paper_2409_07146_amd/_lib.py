@@ -5,6 +5,12 @@ import os
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libgsa.so")
 
+# the native part of the binding (csrc/gsa_binding.cpp); without it api.py marshals every call itself
+if os.path.exists(os.path.join(_HERE, "_binding.so")):
+    from . import _binding as native
+else:
+    native = None
+
 # every symbol include/gsa.h declares
 EXPORTS = ("gsa_status_string", "gsa_abi_version", "gsa_workspace_bytes", "gsa_fwd", "gsa_bwd", "gsa_fwd_ex", "gsa_bwd_ex",
            "gsa_decode_step", "gsa_decode_workspace_bytes", "gsa_decode_step_ws", "gsa_decode_step_ex",
@@ -69,5 +75,6 @@ def load():
                                      ctypes.POINTER(ctypes.c_int64)]
     lib.gsa_profile_copy.restype = ctypes.c_int
     lib.gsa_profile_copy.argtypes = [vp, vp, ctypes.c_size_t, vp]
+    lib.decode_entry = ctypes.cast(lib.gsa_decode_step_ex, vp).value   # for the native part
     _lib = lib
     return lib

@@ -30,7 +30,7 @@ def _check(t, name, dtype=None, shape=None, optional=False):
         if optional:
             return
         raise ValueError("%s is required" % name)
-    # the usual case first: a decode step makes seven of these checks in the time its kernels run
+    # the usual case first
     if t.shape == shape and t.dtype == dtype and t.is_cuda and t.is_contiguous():
         return
     if not t.is_cuda:
@@ -41,6 +41,9 @@ def _check(t, name, dtype=None, shape=None, optional=False):
         raise ValueError("%s must be %s, got %s" % (name, dtype, t.dtype))
     if shape is not None and tuple(t.shape) != tuple(shape):
         raise ValueError("%s must have shape %s, got %s" % (name, tuple(shape), tuple(t.shape)))
+
+
+_native_decode = _lib.native.decode_step if _lib.native else None
 
 
 # The handle of a device's current stream without building a Stream object per call; private to torch, hence the public way
@@ -222,6 +225,14 @@ def gsa_decode_step(q, k, v, g, K_state, V_state, scale=1.0, out=None, workspace
     With a workspace (alloc_decode_workspace) the call goes through gsa_decode_step_ws, which spreads
     each memory over several workgroups.  With s ([B,H,m] fp32 write intensities), a readout other than
     "softmax", gate_tau > 0 or feature_map "swish" it goes through gsa_decode_step_ex.  Returns o [B,H,d_v]."""
+    if _native_decode is not None and readout in READOUTS and feature_map in FEATURE_MAPS:
+        res = _native_decode(_lib.load().decode_entry, _raw_stream, q, k, v, g, K_state, V_state, scale, out, workspace, s,
+                             READOUTS[readout], gate_tau, FEATURE_MAPS[feature_map])
+        if type(res) is int:
+            raise GsaError(res, "gsa_decode_step")
+        if res is not None:
+            return res
+    # anything but the plain case: looked at here, argument by argument
     B, H, d_k = q.shape
     d_v, m = v.shape[-1], g.shape[-1]
     if q.dtype not in _DTYPES:

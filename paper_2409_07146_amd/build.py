@@ -8,6 +8,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libgsa.so")
+BINDING = os.path.join(HERE, "_binding.so")
 SOURCES = ["gsa_api.hip", "gsa_fwd.hip", "gsa_bwd.hip", "gsa_scan.hip", "gsa_apply.hip", "gsa_decode.hip",
            "gsa_profile.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
@@ -35,10 +36,31 @@ def _compile(src):
     return obj
 
 
+def _compile_binding():
+    """The native part of the Python binding: host code only, against torch's headers and libraries."""
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    inc = [os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
+           sysconfig.get_paths()["include"]]
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI]
+    for i in inc:
+        cmd += ["-isystem", i]
+    cmd += [os.path.join(CSRC, "gsa_binding.cpp"), "-o", BINDING, "-L" + os.path.join(root, "lib"), "-ltorch_python",
+            "-ltorch_cpu", "-lc10"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("g++ failed for gsa_binding.cpp:\n%s" % res.stderr)
+
+
 def build(jobs: int = 4) -> str:
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=jobs) as ex:
+        binding = ex.submit(_compile_binding)
         objs = list(ex.map(_compile, SOURCES))
+        binding.result()
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs
     subprocess.run(cmd, check=True)
     return LIB
