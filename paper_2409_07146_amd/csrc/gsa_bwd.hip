@@ -47,11 +47,8 @@ template <typename T, int M> struct DzLds {
     static constexpr int kRows = 2 * M + (sizeof(T) == 2 ? 2 : 1) * C;   // the products' roundings leave a rest in bf16
     static constexpr size_t szX = sizeof(T) * kRows * ldx;
     static_assert(kRows * ldx >= kPrivate<T, M>, "gated_rows' scratch");
-    static constexpr size_t end = oX + szX * (C / 16);
-    static constexpr int kRpr = 2;                 // row blocks per round of the reduction
-    static constexpr size_t szRed = sizeof(f32x4) * kWave * (C / 16) *
-                                    reduce_fragments<C / 16, C / 16 + M / 16, C / 16, kRpr>();   // from offset 0: dead before the tiles are written
-    static constexpr size_t bytes = end > szRed ? end : szRed;
+    static constexpr size_t end = oX + szX * (C / 16), endC = oX + HeadContraction<T, M, C, 0, 0>::kBytes;   // the contraction's buffers go first
+    static constexpr size_t bytes = end > endC ? end : endC;
 };
 
 // GEN: the general form (write intensities from `sin` when it is not NULL; opts: read-out in the low
@@ -90,18 +87,18 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_dz_kernel(
     f32x4 dp[MI], zv[MI];
     typename Atom<T>::Frag16 a[CI], alo[CI];
     BlockGates<M, GEN> bg;
-    // dO is hinted; v and the chunk-start value memory are read again by chunk_intra and stay cached
-    contract_heads<T, M, C, GEN, L::kRpr, kHintX>(
-        dp, a, alo, reinterpret_cast<f32x4 *>(smem), dO + tokh * d_v, v + tokh * d_v, (size_t)H * d_v, d_v, Vn, ci.len, lane, w,
-        PHI ? kHintY : 0, [&] {
-            bg.load(g + tokh * M, (size_t)H * M, ci.len, rowb, lane, (GEN && sin) ? sin + tokh * M : nullptr, gate_tau);
+    bg.load(g + tokh * M, (size_t)H * M, ci.len, rowb, lane, (GEN && sin) ? sin + tokh * M : nullptr, gate_tau);
 #pragma unroll
-            for (int ni = 0; ni < MI; ++ni) zv[ni] = *reinterpret_cast<const f32x4 *>(z + row + ni * 16);
-        });
-    bg.template finish<T>(ci.len, rowb, lane);
-    bg.template write_tiles<T>(nullptr, 0, Vt, L::ldt, Rb, rowb, lane);
+    for (int ni = 0; ni < MI; ++ni) zv[ni] = *reinterpret_cast<const f32x4 *>(z + row + ni * 16);
+    __builtin_amdgcn_sched_barrier(0);
+    {
+        // dO is hinted; v and the chunk-start value memory are read again by chunk_intra and stay cached
+        HeadContraction<T, M, C, kHintX, PHI ? kHintY : 0> hc(dO + tokh * d_v, v + tokh * d_v, (size_t)H * d_v, d_v, Vn, ci.len, tid);
+        bg.template finish<T>(ci.len, rowb, lane);
+        bg.template write_tiles<T>(nullptr, 0, Vt, L::ldt, Rb, rowb, lane);
+        hc.finish(dp, a, alo, smem + L::oX, lane, w);
+    }
     T *X = reinterpret_cast<T *>(smem + L::oX + (size_t)w * L::szX);   // this wave's scratch
-    __syncthreads();
     gated_rows<T, M, C, GEN>(dp, a, alo, bg, Vt, L::ldt, Rb, X, lane, w);
     // slope*(dp - pdp) is dz: p and <p,dp> for the softmax, f'(z) and 0 for an element-wise read-out
     f32x4 p[MI], slope[MI];
@@ -184,15 +181,6 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_dz_kernel(
 // ---------------------------------------------------------------------------------------
 // Intra-chunk gradient kernel.
 // ---------------------------------------------------------------------------------------
-template <typename T> __device__ __forceinline__ float frag_dot(const typename Atom<T>::Frag &a,
-                                                                const typename Atom<T>::Frag &b)
-{
-    float d = 0.f;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) d += to_f32(a[e]) * to_f32(b[e]);
-    return d;
-}
-
 // By value: a conditional expression over variables selects their addresses, which keeps them in memory.
 template <typename P> __device__ __forceinline__ P pick(bool c, P x, P y) { return c ? x : y; }
 
@@ -206,17 +194,16 @@ template <typename T, int M, bool WIDE> struct IntraLds {
     static constexpr size_t oUd = oVn + sizeof(T) * C * ldn;          // Ud [M][ldt]
     static constexpr size_t oUp = oUd + sizeof(T) * M * ldt;          // Up [M][ldt]
     static constexpr size_t tiles = oUp + sizeof(T) * M * ldt;
-    // Rb, Rd, Rr, dGam totals: [C/16][M] fp32 each, behind the first buffer of the wide contractions (they are read
-    // until that buffer has been written)
+    // Rb, Rd, Rr, dGam totals: [C/16][M] fp32 each, and the carry [M], behind the first buffer of the wide contractions
+    // (they are read until that buffer has been written)
     static constexpr size_t oRb = (WIDE && tiles < Wide<M>::szBuf) ? Wide<M>::szBuf : tiles;
-    static constexpr size_t endR = oRb + 4 * sizeof(float) * (C / 16) * M;
-    static constexpr size_t oMat = (WIDE && endR < 2 * Wide<M>::szBuf) ? 2 * Wide<M>::szBuf : endR;   // Bm, Bm^T, A2^T, scale*dz*exp(G), s*exp(G_C-G)
-    static constexpr size_t end = oMat + (WIDE ? 3 * Wide<M>::szTok + 2 * Wide<M>::szSlot : 0);
-    static constexpr int kRpr = 2;        // row blocks per round of the reduction
-    static constexpr size_t szRed = sizeof(f32x4) * kWave * (C / 16) *
-                                    reduce_fragments<C / 16, C / 16 + M / 16, C / 16, kRpr, true>();   // from offset 0: dead before the tiles are written
-    static constexpr size_t oCarry = end > szRed ? end : szRed;
-    static constexpr size_t bytes = oCarry + sizeof(float) * (C / 16) * M;   // per-wave partial carries
+    static constexpr size_t oCarry = oRb + 4 * sizeof(float) * (C / 16) * M;
+    static constexpr size_t endR = oCarry + sizeof(float) * M;
+    // the buffers of the contractions; later Bm, Bm^T, A2^T, scale*dz*exp(G), s*exp(G_C-G)
+    static constexpr size_t oMat = (WIDE && endR < 2 * Wide<M>::szBuf) ? 2 * Wide<M>::szBuf : endR;
+    static constexpr size_t oK = sizeof(T) * C * StepTile<T>::KS, oE = 2 * oK, szBuf = oE + sizeof(T) * M * StepTile<T>::KS;   // q, k or v, E
+    static constexpr size_t szMat = WIDE ? 3 * Wide<M>::szTok + 2 * Wide<M>::szSlot : 0;
+    static constexpr size_t bytes = oMat + (szMat > 2 * szBuf ? szMat : 2 * szBuf);
 };
 
 template <typename T> struct IntraArgs {
@@ -240,20 +227,20 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
                                                                  IntraArgs<T> a)
 {
     using L = IntraLds<T, M, WIDE>;
-    constexpr int C = Geo<T>::C, NW = Geo<T>::NW;
+    constexpr int C = Geo<T>::C;
     constexpr int MI = M / 16, CI = C / 16, KM = L::KM;
     constexpr int NB = CI + MI;
     extern __shared__ __align__(16) unsigned char smem[];
     T *Vn = reinterpret_cast<T *>(smem + L::oVn), *Ud = reinterpret_cast<T *>(smem + L::oUd), *Up = reinterpret_cast<T *>(smem + L::oUp);
     float *Rb = reinterpret_cast<float *>(smem + L::oRb), *Rd = Rb + CI * M, *Rr = Rd + CI * M, *Tot = Rr + CI * M;
-    float *carry = reinterpret_cast<float *>(smem + L::oCarry);   // [NW][M]
+    float *carry = reinterpret_cast<float *>(smem + L::oCarry);   // [M]
 
     ChunkInfo ci;
     int cid, h;
     chunk_order(cm, H, false, cid, h);   // the reverse scan has just written the first chunks
     if (!chunk_lookup(cm, cid, ci)) return;
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int r = lane & 15, g4 = (lane >> 4) * 4, g8 = (lane >> 4) * 8;
+    const int r = lane & 15, g4 = (lane >> 4) * 4;
     const size_t tokh = (size_t)ci.tok0 * H + h;
     const size_t ch = (size_t)cid * H + h;
     const T *EK = a.E + ch * a.lay.stride + a.lay.oK;        // memory gradient at chunk end
@@ -273,11 +260,6 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
     const T *AvT = a.tAvT + ch * C * C;
     const int rowb = 16 * w;
 
-    // ---- phase 1: contractions over the head dimension, operands straight from global memory
-    //   A[t][r] = q_t . k_r (r <= t),  X[r][i] = <E[i], [k_r | v_r]>,  carry[i] = <E[i], S_end[i]>
-    // Split over the waves in steps of 64 columns (see contract_heads): every wave covers all row
-    // blocks over its share of the columns, the partial sums meet in LDS.  Wave w keeps the tiles of its
-    // own tokens as r: A as D[t][r] for the row blocks of t from w on, X as D[slot][r].
     const int t = rowb + r;                                  // this lane's token
     const bool live = t < ci.len;
     const size_t row = (tokh + (size_t)min(t, ci.len - 1) * H) * M + g4;   // clamped; nothing is stored past len
@@ -285,168 +267,171 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
     typename Atom<T>::Frag16 fa[CI], fav[CI], favlo[CI];                // (q_t . k_r) and (dO_t . v_r), masked: operands of contractions over t
     BlockGates<M, GEN> bg;
     const bool given = GEN && a.sin != nullptr;   // write intensities are an input of their own
-    {
-        typedef typename Atom<T>::Frag Frag;
-        f32x4 acc[NW][NB];   // [row block of r][row blocks of t (causal) | slot blocks]
-#pragma unroll
-        for (int rb = 0; rb < NW; ++rb)
-#pragma unroll
-            for (int cb = 0; cb < NB; ++cb) acc[rb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
-        float cpart[MI];     // this lane's share of the carry of slot 16*ni + lane%16
-#pragma unroll
-        for (int ni = 0; ni < MI; ++ni) cpart[ni] = 0.f;
-        // Token rows past the end of a ragged chunk are read as copies of its last row (finite; they
-        // only feed rows that are never stored or that meet zero weights).
-        uint32_t tk[CI], tv[CI], ek[MI], ev[MI];
-#pragma unroll
-        for (int ni = 0; ni < CI; ++ni) {
-            const uint32_t row = (uint32_t)min(ni * 16 + r, ci.len - 1) * (uint32_t)H;
-            tk[ni] = row * (uint32_t)d_k + g8;
-            tv[ni] = row * (uint32_t)d_v + g8;
-        }
-#pragma unroll
-        for (int ni = 0; ni < MI; ++ni) {
-            ek[ni] = ev[ni] = (uint32_t)(ni * 16 + r) * kSnapTile + g8;   // snapshot parts are tiled
-        }
-        const T *qb = a.q + tokh * d_k, *kb = a.k + tokh * d_k, *vb = a.v + tokh * d_v;
-        // key half: A = Q K^T, X += K E_k^T
-        // (two passes over k, each in 64-column steps like the value half: together their operand
-        // fragments would not fit the registers; the second read of k is served by the caches)
-        // Non-temporal loads for what is read here for the last time (v, the chunk-end memories, and q where the wide
-        // contractions run on their own); k and E are read again, by this kernel or by the apply kernel right after it.
-        for (int kk = 64 * w; kk < d_k; kk += 64 * NW) {
-            Frag fq[2][CI], fk[2][CI];
-#pragma unroll
-            for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-                for (int ni = 0; ni < CI; ++ni) fq[hh][ni] = WIDE ? Atom<T>::load(qb + tk[ni] + kk + 32 * hh) : Atom<T>::load_nt(qb + tk[ni] + kk + 32 * hh);
-#pragma unroll
-            for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-                for (int ni = 0; ni < CI; ++ni) fk[hh][ni] = Atom<T>::load(kb + tk[ni] + kk + 32 * hh);
-            __builtin_amdgcn_sched_barrier(0);   // all loads of the step before its multiplies (see contract_heads)
-            if (PHI) {
-#pragma unroll
-                for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-                    for (int ni = 0; ni < CI; ++ni) { swish_frag<T>(fq[hh][ni]); swish_frag<T>(fk[hh][ni]); }
-            }
-#pragma unroll
-            for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-                for (int rb = 0; rb < NW; ++rb)
-#pragma unroll
-                    for (int cb = rb; cb < CI; ++cb) Atom<T>::mma(acc[rb][cb], fq[hh][cb], fk[hh][rb]);
-        }
-        for (int kk = 64 * w; kk < d_k; kk += 64 * NW) {
-            Frag fk[2][CI], fe[2][MI], fs[2][MI];
-#pragma unroll
-            for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-                for (int ni = 0; ni < CI; ++ni) fk[hh][ni] = Atom<T>::load(kb + tk[ni] + kk + 32 * hh);
-#pragma unroll
-            for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-                for (int ni = 0; ni < MI; ++ni) fe[hh][ni] = Atom<T>::load(EK + ek[ni] + snap_col<M>(kk + 32 * hh));
-#pragma unroll
-            for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-                for (int ni = 0; ni < MI; ++ni) fs[hh][ni] = Atom<T>::load_nt(SendK + ek[ni] + snap_col<M>(kk + 32 * hh));
-            __builtin_amdgcn_sched_barrier(0);
-            if (PHI) {
-#pragma unroll
-                for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-                    for (int ni = 0; ni < CI; ++ni) swish_frag<T>(fk[hh][ni]);
-            }
-#pragma unroll
-            for (int hh = 0; hh < 2; ++hh) {
-#pragma unroll
-                for (int rb = 0; rb < NW; ++rb)
-#pragma unroll
-                    for (int ni = 0; ni < MI; ++ni) Atom<T>::mma(acc[rb][CI + ni], fe[hh][ni], fk[hh][rb]);
-#pragma unroll
-                for (int ni = 0; ni < MI; ++ni) cpart[ni] += frag_dot<T>(fe[hh][ni], fs[hh][ni]);
-            }
-        }
-        // value half: X += V E_v^T
-        // (64 columns per wave and step here, as in contract_heads: the registers allow it in this half)
-        for (int kk = 64 * w; kk < d_v; kk += 64 * NW) {
-            Frag fv[2][CI], fe[2][MI], fs[2][MI];
-#pragma unroll
-            for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-                for (int ni = 0; ni < CI; ++ni) fv[hh][ni] = Atom<T>::load_nt(vb + tv[ni] + kk + 32 * hh);
-#pragma unroll
-            for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-                for (int ni = 0; ni < MI; ++ni) fe[hh][ni] = Atom<T>::load(EV + ev[ni] + snap_col<M>(kk + 32 * hh));
-#pragma unroll
-            for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-                for (int ni = 0; ni < MI; ++ni) fs[hh][ni] = Atom<T>::load_nt(SendV + ev[ni] + snap_col<M>(kk + 32 * hh));
-            __builtin_amdgcn_sched_barrier(0);
-            if (PHI) {
-#pragma unroll
-                for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-                    for (int ni = 0; ni < CI; ++ni) swish_frag<T>(fv[hh][ni]);
-            }
-#pragma unroll
-            for (int hh = 0; hh < 2; ++hh) {
-#pragma unroll
-                for (int rb = 0; rb < NW; ++rb)
-#pragma unroll
-                    for (int ni = 0; ni < MI; ++ni) Atom<T>::mma(acc[rb][CI + ni], fe[hh][ni], fv[hh][rb]);
-#pragma unroll
-                for (int ni = 0; ni < MI; ++ni) cpart[ni] += frag_dot<T>(fe[hh][ni], fs[hh][ni]);
-            }
-        }
-#pragma unroll
-        for (int ni = 0; ni < MI; ++ni) {
-            float x = cpart[ni];
-            x += __shfl_xor(x, 16, 64);
-            x += __shfl_xor(x, 32, 64);
-            if (lane < 16) carry[w * M + ni * 16 + lane] = x;   // read after the barriers of the reduction
-        }
-        // the loads of everything phase 2 needs from global memory land during the reduction
-        bg.load(a.g + tokh * M, (size_t)H * M, ci.len, rowb, lane, given ? a.sin + tokh * M : nullptr, GEN ? a.gate_tau : 0.f);
+    bg.load(a.g + tokh * M, (size_t)H * M, ci.len, rowb, lane, given ? a.sin + tokh * M : nullptr, GEN ? a.gate_tau : 0.f);
+    __builtin_amdgcn_sched_barrier(0);
+    // ---- phase 1: contractions over the head dimension (see StepTile)
+    //   A[t][r] = q_t . k_r (r <= t),  X[r][i] = <E[i], [k_r | v_r]>,  carry[i] = <E[i], S_end[i]>
+    // Wave w keeps the tiles of its own tokens as r: A as D[t][r] for the row blocks of t from w on, X as D[slot][r].  The
+    // carry is the product of two tiles of the same layout, piece by piece in the registers they arrive in: the chunk-end
+    // memory does not go through LDS.
+    // Non-temporal loads for what is read here for the last time (v, the chunk-end memories, and q where the wide
+    // contractions run on their own); k and E are read again, by this kernel or by the apply kernel right after it.
+    f32x4 dgl[MI];   // z*dz + p*dp of this lane's token
+    constexpr bool kTwo = sizeof(T) == 2 || M < 64;   // registers for two steps at a time (see walk_steps), gates and scores
+    auto gates = [&] {   // the write-intensity tile Vn is for the pair weights of other waves
+        bg.template finish<T>(ci.len, rowb, lane);
+        bg.template write_tiles<T>(Vn, L::ldn, nullptr, 0, Rb, rowb, lane);
+    };
+    auto load_scores = [&] {
 #pragma unroll
         for (int ni = 0; ni < MI; ++ni) {
             p[ni] = *reinterpret_cast<const f32x4 *>(a.z + row + ni * 16);
             wd[ni] = *reinterpret_cast<const f32x4 *>(a.dz + row + ni * 16);
         }
+    };
+    {
+        using Tile = StepTile<T>;
+        constexpr int NT = Geo<T>::NT;
+        typedef StepRows<T, C, NT, false, !WIDE> RQ;
+        typedef StepRows<T, C, NT, false, false> RK;
+        typedef StepRows<T, C, NT, false, true> RV;
+        typedef StepRows<T, M, NT, true, false> RE;
+        typedef StepRows<T, M, NT, true, true> RS;
+        const RQ rq(a.q + tokh * d_k, (size_t)H * d_k, ci.len, tid);
+        const RK rk(a.k + tokh * d_k, (size_t)H * d_k, ci.len, tid);
+        const RV rv(a.v + tokh * d_v, (size_t)H * d_v, ci.len, tid);
+        const RE rek(EK, 0, 0, tid), rev(EV, 0, 0, tid);
+        const RS rsk(SendK, 0, 0, tid), rsv(SendV, 0, 0, tid);
+        typename RQ::Stage sq[2];
+        typename RK::Stage sk[2];
+        typename RE::Stage se[2];
+        typename RS::Stage ss[2];
+        StepSums<T, NB> sums;   // [row blocks of t (causal) | slot blocks]
+        float cpart[RE::V];   // this thread's share of the carry of its pieces' slots
 #pragma unroll
-        for (int b = 0; b < CI; ++b) {
-            const size_t off = (size_t)t * C + max(b, w) * 16 + g4;
-            fav[b] = Atom<T>::load16(AvT + off);
-            if (sizeof(T) == 2) favlo[b] = Atom<T>::load16(a.tAvLo + ch * C * C + off);
+        for (int v = 0; v < RE::V; ++v) cpart[v] = 0.f;
+        auto add_carry = [&](const typename RE::Stage &e, const typename RS::Stage &s) {
+#pragma unroll
+            for (int v = 0; v < RE::V; ++v)
+#pragma unroll
+                for (int j = 0; j < Tile::PV; ++j) cpart[v] += to_f32(e.x[v][j]) * to_f32(s.x[v][j]);
+        };
+        const int nk = d_k / Tile::KS, nv = d_v / Tile::KS;
+        unsigned char *buf = smem + L::oMat;
+        auto fetch_k = [&](auto u, int step) {
+            constexpr int U = decltype(u)::value;
+            rq.fetch(sq[U], step);
+            rk.fetch(sk[U], step);
+            rek.fetch(se[U], step);
+            rsk.fetch(ss[U], step);
+        };
+        fetch_k(std::integral_constant<int, 0>{}, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (kTwo) fetch_k(std::integral_constant<int, 1>{}, min(1, nk - 1));
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (kTwo) {
+            gates();   // while the first operands are on their way
+            __builtin_amdgcn_sched_barrier(0);
         }
-        f32x4 own[NB];
-        reduce_row_blocks<NW, NB, CI, L::kRpr, true>(own, acc, reinterpret_cast<f32x4 *>(smem), lane, w);
+        // key half: A = Q K^T, X += K E_k^T
+        walk_steps<kTwo>(
+            nk, fetch_k,
+            [&](auto u, int step) {
+                constexpr int U = decltype(u)::value;
+                unsigned char *at = buf + U * L::szBuf;
+                if (step < nk) add_carry(se[U], ss[U]);
+                rq.template put<PHI>(reinterpret_cast<T *>(at), sq[U], tid);
+                rk.template put<PHI>(reinterpret_cast<T *>(at + L::oK), sk[U], tid);
+                rek.put(reinterpret_cast<T *>(at + L::oE), se[U], tid);
+            },
+            [&](auto parity, int b) {
+                f32x4(&acc)[NB] = sums.x[decltype(parity)::value % StepSums<T, NB>::P];
+                const T *Q = reinterpret_cast<const T *>(buf + b * L::szBuf), *K = reinterpret_cast<const T *>(buf + b * L::szBuf + L::oK);
+                const T *E = reinterpret_cast<const T *>(buf + b * L::szBuf + L::oE);
+#pragma unroll
+                for (int f = 0; f < Tile::F; ++f) {
+                    const typename Atom<T>::Frag x = Tile::frag(K, rowb, f, lane);
+#pragma unroll
+                    for (int ni = 0; ni < MI; ++ni) Atom<T>::mma(acc[CI + ni], Tile::frag(E, 16 * ni, f, lane), x);
+#pragma unroll
+                    for (int cb = 0; cb < CI; ++cb)
+                        if (cb >= w) Atom<T>::mma(acc[cb], Tile::frag(Q, 16 * cb, f, lane), x);   // wave-uniform
+                }
+            });
+        if constexpr (kTwo) {
+            load_scores();   // land during the value half
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        // value half: X += V E_v^T
+        typename RV::Stage sv[2];
+        auto fetch_v = [&](auto u, int step) {
+            constexpr int U = decltype(u)::value;
+            rv.fetch(sv[U], step);
+            rev.fetch(se[U], step);
+            rsv.fetch(ss[U], step);
+        };
+        fetch_v(std::integral_constant<int, 0>{}, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (kTwo) fetch_v(std::integral_constant<int, 1>{}, min(1, nv - 1));
+        __builtin_amdgcn_sched_barrier(0);
+        walk_steps<kTwo>(
+            nv, fetch_v,
+            [&](auto u, int step) {
+                constexpr int U = decltype(u)::value;
+                unsigned char *at = buf + U * L::szBuf;
+                if (step < nv) add_carry(se[U], ss[U]);
+                rv.template put<PHI>(reinterpret_cast<T *>(at + L::oK), sv[U], tid);
+                rev.put(reinterpret_cast<T *>(at + L::oE), se[U], tid);
+            },
+            [&](auto parity, int b) {
+                f32x4(&acc)[NB] = sums.x[decltype(parity)::value % StepSums<T, NB>::P];
+                const T *V = reinterpret_cast<const T *>(buf + b * L::szBuf + L::oK), *E = reinterpret_cast<const T *>(buf + b * L::szBuf + L::oE);
+#pragma unroll
+                for (int f = 0; f < Tile::F; ++f) {
+                    const typename Atom<T>::Frag x = Tile::frag(V, rowb, f, lane);
+#pragma unroll
+                    for (int ni = 0; ni < MI; ++ni) Atom<T>::mma(acc[CI + ni], Tile::frag(E, 16 * ni, f, lane), x);
+                }
+            });
+#pragma unroll
+        for (int v = 0; v < RE::V; ++v) {   // eight neighbouring threads hold the pieces of one slot
+            float x = cpart[v];
+            x += __shfl_xor(x, 1, 64);
+            x += __shfl_xor(x, 2, 64);
+            x += __shfl_xor(x, 4, 64);
+            const int idx = tid + v * NT;
+            if (idx % Tile::PR == 0 && idx < RE::N) carry[idx / Tile::PR] = x;   // read behind the barrier of phase 2e
+        }
 #pragma unroll
         for (int b = 0; b < CI; ++b) {
-            f32x4 x = own[b];
+            f32x4 x = sums.total(b);
 #pragma unroll
             for (int j = 0; j < 4; ++j) x[j] = (b > w || (b == w && g4 + j >= r)) ? x[j] : 0.f;
             fa[b] = to_frag16<T>(x);
         }
 #pragma unroll
-        for (int ni = 0; ni < MI; ++ni) ds[ni] = own[CI + ni];
+        for (int ni = 0; ni < MI; ++ni) ds[ni] = sums.total(CI + ni);
     }
-    f32x4 dgl[MI];   // z*dz + p*dp of this lane's token
+    // what the rest of phase 2 needs from global memory
+    if constexpr (!kTwo) {
+        load_scores();
+        gates();
+    }
+#pragma unroll
+    for (int b = 0; b < CI; ++b) {
+        const size_t off = (size_t)t * C + max(b, w) * 16 + g4;
+        fav[b] = Atom<T>::load16(AvT + off);
+        if (sizeof(T) == 2) favlo[b] = Atom<T>::load16(a.tAvLo + ch * C * C + off);
+    }
 #pragma unroll
     for (int ni = 0; ni < MI; ++ni) dgl[ni] = *reinterpret_cast<const f32x4 *>(a.dgf + row + ni * 16);
-    // ---- phase 2 (register tiles and one barrier in place of fp32 LDS tiles and seven: with m = 128, H = 4, d = 512, 4 x 1000
-    // tokens 84 -> 72 us; with m = 64 the launch is bound by its loads): gates, p and scale*dz in D[slot][token] tiles of this wave's block.  What the other waves
-    // need goes to LDS (it overwrites the reduction buffer, which every wave has left by now): the
-    // write-intensity tile Vn for the pair weights, and the tiles U = (scale*dz | p) * exp(L_t - ref) for ds.
+    __builtin_amdgcn_sched_barrier(0);
+    // ---- phase 2: p and scale*dz in D[slot][token] tiles of this wave's block.  The other waves need of them the tiles
+    // U = (scale*dz | p) * exp(L_t - ref) for ds.
     // ref lies halfway down the block's decay, so that neither U nor exp(ref - L_r) leaves fp32's range by
     // more than e^40; a kPairs block is referenced to its start, which serves the earlier blocks, and its own pairs are
     // evaluated one by one.
-    bg.template finish<T>(ci.len, rowb, lane);
     const bool unsafe = bg.kind == kPairs;
-    bg.template write_tiles<T>(Vn, L::ldn, nullptr, 0, Rb, rowb, lane);
     if (!GEN || a.readout == kReadSoftmax) {
         softmax_slots<M>(p);
     } else {
@@ -639,8 +624,6 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
 #pragma unroll
     for (int ni = 0; ni < MI; ++ni) {
         f32x4 off = *reinterpret_cast<const f32x4 *>(carry + ni * 16 + g4);
-#pragma unroll
-        for (int u = 1; u < NW; ++u) off += *reinterpret_cast<const f32x4 *>(carry + u * M + ni * 16 + g4);
 #pragma unroll
         for (int b = 1; b < CI; ++b)
             if (b > w) off += *reinterpret_cast<const f32x4 *>(Tot + b * M + ni * 16 + g4);

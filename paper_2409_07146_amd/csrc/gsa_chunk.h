@@ -18,74 +18,144 @@
 // token is a sum over a lane's own registers and two shuffles.  And a cumulative sum over the
 // tokens of a block runs over 16 neighbouring lanes (DPP row shifts), with no barrier.
 #pragma once
+#include <type_traits>
+
 #include "gsa_common.h"
 
 namespace gsa {
 
-// Split-contraction bookkeeping.  The chunk kernels contract over the head dimension with
-// every wave taking a slice of that dimension for ALL row blocks of the chunk (so each
-// operand byte is loaded by exactly one wave, in whole 128-byte lines), and then sum the
-// per-wave partial accumulators so that wave w ends up with the totals of row block w.
-// acc[rb][cb] are D fragments; the first CAUSAL column blocks are only needed for cb <= rb.
-// Red: LDS, NW*NB*64 f32x4 (fragments are exchanged lane for lane, so any wave's layout
-// is every wave's layout).  w must be wave-uniform.  Contains barriers: all threads of the
-// workgroup must call it.
-// RPR row blocks are exchanged per round (RPR divides NW): fewer, fuller rounds need fewer barriers
-// and keep more waves busy adding, at the price of a larger buffer, reduce_fragments<..>() * NW * 64 f32x4.
-// UPPER: the causal column blocks are needed for cb >= rb instead.
-template <int NW, int NB, int CAUSAL, bool UPPER> constexpr bool reduce_skips(int rb, int cb)
-{
-    return cb < CAUSAL && (UPPER ? cb < rb : cb > rb);
-}
-template <int NW, int NB, int CAUSAL, int RPR, bool UPPER = false> constexpr int reduce_fragments()
-{
-    int worst = 0;
-    for (int rb0 = 0; rb0 < NW; rb0 += RPR) {
-        int n = 0;
-        for (int rb = rb0; rb < rb0 + RPR; ++rb)
-            for (int cb = 0; cb < NB; ++cb)
-                if (!reduce_skips<NW, NB, CAUSAL, UPPER>(rb, cb)) ++n;
-        worst = n > worst ? n : worst;
+// ----------------------------------------------------------------------------
+// Contractions over the head dimension.  A workgroup walks the columns in steps of 128 bytes per row; the tiles of a step
+// ([rows][128 bytes]) come from memory in whole lines, every thread taking 16-byte pieces, wait in registers for their turn
+// and lie in one of two LDS buffers while the waves read them as depth-32 operands, wave w for the tokens of row block w.
+// One barrier per step.  What this replaces: every wave took a share of the columns for all row blocks, with its operands
+// straight from memory (16 bytes of each of 16 rows per quarter of a load, four times the address unit's time) and the
+// partial sums exchanged through LDS.  Forward chunk kernel, 64 slots, 8 x 2048 tokens, 4 heads: d = 128 41.4 -> 36.0 us, d = 512 86 -> 82; one
+// sequence of 2048, d = 512 26.7 -> 22.6; 128 slots, 4 x 1000 tokens 41 -> 36; intra-chunk gradients, d = 128 77 -> 68, d = 512 201 -> 198.
+// ----------------------------------------------------------------------------
+template <typename T> struct StepTile {
+    static constexpr int KS = 128 / sizeof(T), PV = 16 / sizeof(T), PR = 8;   // columns per step, elements per piece, pieces per row
+    static constexpr int F = KS / 32;                                         // depth-32 operands per step
+    typedef T Piece __attribute__((ext_vector_type(16 / sizeof(T))));
+    // Pieces are XOR-swizzled so that the same piece of 16 rows lies in all banks.
+    __device__ static __forceinline__ void put(T *tile, int row, int p, const Piece &x)
+    {
+        *reinterpret_cast<Piece *>(tile + row * KS + ((p ^ ((row >> 1) & 7)) * PV)) = x;
     }
-    return worst;
+    // operand f of rows row0 .. row0+15 (row0 a multiple of 16)
+    __device__ static __forceinline__ typename Atom<T>::Frag frag(const T *tile, int row0, int f, int lane)
+    {
+        const int r = lane & 15, g = lane >> 4, s = r >> 1;
+        const T *row = tile + (row0 + r) * KS;
+        if constexpr (sizeof(T) == 2) {
+            return Atom<T>::load(row + (((f * 4 + g) ^ s) * PV));
+        } else {
+            const f32x4 lo = *reinterpret_cast<const f32x4 *>(row + (((2 * g) ^ s) * PV)), hi = *reinterpret_cast<const f32x4 *>(row + (((2 * g + 1) ^ s) * PV));
+            return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+        }
+    }
+};
+
+// One operand of such a walk: ROWS rows of a token tensor (rows `ld` elements apart, those past the end of a ragged
+// chunk read as copies of its last row: they stay finite and only ever produce rows of the result that are not stored or
+// that meet zero weights), or of one part of a memory snapshot (SNAP, tiled as StateLayout describes).
+// HINT: loads carry the non-temporal hint (for what the caller knows nobody reads again soon).
+template <typename T, int ROWS, int NT, bool SNAP, bool HINT> struct StepRows {
+    using Tile = StepTile<T>;
+    typedef typename Tile::Piece Piece;
+    static constexpr int N = ROWS * Tile::PR, V = (N + NT - 1) / NT;   // pieces, pieces per thread
+    struct Stage { Piece x[V]; };
+    const char *base;
+    uint32_t off[V];
+    __device__ __forceinline__ StepRows(const T *p, size_t ld, int len, int tid) : base(reinterpret_cast<const char *>(p))
+    {
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            const int idx = min(tid + v * NT, N - 1), row = idx / Tile::PR;
+            off[v] = SNAP ? (uint32_t)(row * kSnapTile * (int)sizeof(T) + (idx % Tile::PR) * 16)
+                          : (uint32_t)min(row, len - 1) * (uint32_t)(ld * sizeof(T)) + (idx % Tile::PR) * 16;
+        }
+    }
+    __device__ __forceinline__ void fetch(Stage &st, int step) const
+    {
+        const char *p = base + (SNAP ? (size_t)(step / (kSnapTile / Tile::KS)) * (ROWS * kSnapTile * sizeof(T)) + (size_t)(step % (kSnapTile / Tile::KS)) * 128
+                                     : (size_t)step * 128);
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            const Piece *q = reinterpret_cast<const Piece *>(p + off[v]);
+            if (HINT) st.x[v] = __builtin_nontemporal_load(q);
+            else st.x[v] = *q;
+        }
+    }
+    // PHI: with the feature map applied on the way
+    template <bool PHI = false> __device__ __forceinline__ void put(T *tile, const Stage &st, int tid) const
+    {
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            const int idx = tid + v * NT;
+            Piece x = st.x[v];
+            if (PHI) {
+#pragma unroll
+                for (int e = 0; e < Tile::PV; ++e) x[e] = from_f32<T>(swish_value(to_f32(x[e])));
+            }
+            if (N % NT == 0 || idx < N) Tile::put(tile, idx / Tile::PR, idx % Tile::PR, x);
+        }
+    }
+};
+
+// The walk over n steps, two at a time, so that 256 bytes of a row are asked for together (one step at a time, two ahead: forward,
+// 8 x 2048 tokens, 4 heads, d = 512, 64 slots 92 us instead of 82).  fetch(u, step): loads of a step into register stage u; put(u,
+// step): stage u, which holds that step, to LDS buffer u; multiply(parity, b): the products of buffer b, which holds a step of that
+// parity.  The caller has issued the loads of the first two steps (past the end: of the last one again) and has the buffers
+// free; the walk ends with a barrier.
+// PAIRS = false: one step at a time, stage and buffer 0 only, where two do not fit the registers.
+template <bool PAIRS = true, typename Fetch, typename Put, typename Multiply>
+__device__ __forceinline__ void walk_steps(int n, Fetch &&fetch, Put &&put, Multiply &&multiply)
+{
+    constexpr std::integral_constant<int, 0> even{};
+    constexpr std::integral_constant<int, 1> odd{};
+    for (int it = 0;; it += 2) {
+        put(even, it);
+        if constexpr (PAIRS) put(odd, it + 1);
+        __builtin_amdgcn_sched_barrier(0);   // a refill stays behind the reads of its registers
+        if (it + (PAIRS ? 2 : 1) < n) {   // uniform over the grid
+            fetch(even, it + (PAIRS ? 2 : 1));
+            if constexpr (PAIRS) fetch(odd, min(it + 3, n - 1));
+        }
+        __syncthreads();
+        multiply(even, 0);
+        __builtin_amdgcn_sched_barrier(0);   // operands of both at a time would not fit the registers
+        if constexpr (PAIRS) {
+            if (it + 1 < n) multiply(odd, 1);
+        }
+        __syncthreads();
+        if constexpr (!PAIRS) {
+            if (it + 1 >= n) return;
+            put(even, it + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            if (it + 2 < n) fetch(even, it + 2);
+            __syncthreads();
+            multiply(odd, 0);
+            __syncthreads();
+        }
+        if (it + 2 >= n) return;
+    }
 }
 
-template <int NW, int NB, int CAUSAL, int RPR = 1, bool UPPER = false>
-__device__ __forceinline__ void reduce_row_blocks(f32x4 (&own)[NB], const f32x4 (&acc)[NW][NB], f32x4 *Red, int lane,
-                                                  int w)
-{
-    static_assert(NW % RPR == 0, "row blocks per round");
+// Accumulators of such a walk.  fp32 sums the steps of either parity on their own: the longer one chain of roundings, the larger
+// its error (m = 32, 700 tokens, d_k = 192: dq 2.92e-7 from the fp64 recurrence with one chain, 2.56e-7 with two).
+template <typename T, int N> struct StepSums {
+    static constexpr int P = sizeof(T) == 4 ? 2 : 1;
+    f32x4 x[P][N];
+    __device__ __forceinline__ StepSums()
+    {
 #pragma unroll
-    for (int cb = 0; cb < NB; ++cb) own[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // Per round: every wave posts its partials of the round's row blocks, each block's owner adds
-    // them in wave order.  (Register arrays are indexed by constants only; the wave index enters
-    // through LDS addresses.)  Slot numbers count the posted fragments of a round in (rb, cb) order.
+        for (int p = 0; p < P; ++p)
 #pragma unroll
-    for (int rb0 = 0; rb0 < NW; rb0 += RPR) {
-        int slot = 0;
-#pragma unroll
-        for (int rb = rb0; rb < rb0 + RPR; ++rb)
-#pragma unroll
-            for (int cb = 0; cb < NB; ++cb)
-                if (!reduce_skips<NW, NB, CAUSAL, UPPER>(rb, cb)) { Red[(slot * NW + w) * kWave + lane] = acc[rb][cb]; ++slot; }
-        __syncthreads();
-        slot = 0;
-#pragma unroll
-        for (int rb = rb0; rb < rb0 + RPR; ++rb)
-#pragma unroll
-            for (int cb = 0; cb < NB; ++cb) {
-                if (reduce_skips<NW, NB, CAUSAL, UPPER>(rb, cb)) continue;
-                if (w == rb) {
-                    f32x4 x = Red[(slot * NW) * kWave + lane];
-#pragma unroll
-                    for (int u = 1; u < NW; ++u) x += Red[(slot * NW + u) * kWave + lane];
-                    own[cb] = x;
-                }
-                ++slot;
-            }
-        __syncthreads();
+            for (int i = 0; i < N; ++i) x[p][i] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-}
+    __device__ __forceinline__ f32x4 total(int i) const { return P == 1 ? x[0][i] : x[0][i] + x[P - 1][i]; }
+};
 
 // ----------------------------------------------------------------------------
 // Row shifts inside the 16 lanes that share l/16 (DPP; lanes without a source read zero).
@@ -265,98 +335,84 @@ template <int M, bool GEN> struct BlockGates {
 //               rounded to T and causally masked: an operand of contractions over r; alo[cb]: the rest
 //   run[ni]   = D[slot][t] tile of <X_t, St[slot]>
 // X, Y: [len][d] rows in global memory (row stride ldx elements); St: one part of a memory snapshot
-// (M slots, d columns, tiled as StateLayout describes).
-// The contraction over d reads its operand fragments straight from global memory (each lane 16
-// bytes of one row; no staging).  It is split over the waves in steps of 64 columns, wave w taking steps
-// w, w+NW, ...: a wave asks for the two halves of a 128-byte line in consecutive instructions, so each line
-// crosses the memory system once.  The partial sums meet through Red (see reduce_row_blocks).  d must be a
-// multiple of 64.  The gate loads are issued after the contraction and land during the reduction.
-// All threads of the workgroup must call it; it ends with a barrier.
-// RPR: row blocks per round of the reduction (Red must hold reduce_fragments<..., RPR>() * NW * 64 f32x4).
-// HINT: which operands are loaded with the non-temporal hint (kHintX | kHintY | kHintSt) -- those the
-// caller knows nobody reads again soon.  Both halves of every 128-byte line are asked for by the
-// same wave in the same step, so a hinted line is never dropped between its two readers.
+// (M slots, d columns, tiled as StateLayout describes).  d must be a multiple of 64.
+// HINT: which operands are loaded with the non-temporal hint (kHintX | kHintY | kHintSt).
+// PHI: which of X, Y get the feature map on their way into LDS (kHintX | kHintY bits).
+// buf: LDS, kBytes, free from the start.  begin() issues the first loads, before which the caller issues its own and behind
+// which it does what needs no operand of the contraction (gates); finish() is for all threads of the workgroup and ends
+// with a barrier.
 constexpr int kHintX = 1, kHintY = 2, kHintSt = 4;
-// phi (general form only): which of X, Y get the feature map after the load (kHintX | kHintY bits).
-template <typename T, int M, int C, bool GEN, int RPR, int HINT, typename Early>
-__device__ __forceinline__ void contract_heads(f32x4 (&run)[M / 16], typename Atom<T>::Frag16 (&a)[C / 16],
-                                               typename Atom<T>::Frag16 (&alo)[C / 16], f32x4 *Red,
-                                               const T *X, const T *Y, size_t ldx, int d, const T *St, int len,
-                                               int lane, int w, int phi, Early &&early_loads)
-{
-    constexpr int MI = M / 16, CI = C / 16, NW = CI, NB = CI + MI;
-    const int r = lane & 15, g4 = (lane >> 4) * 4, g8 = (lane >> 4) * 8;
-    f32x4 acc[NW][NB];   // [row block][Y blocks | St blocks]
+template <typename T, int M, int C, int HINT, int PHI> struct HeadContraction {
+    using Tile = StepTile<T>;
+    static constexpr int NT = Geo<T>::NT, MI = M / 16, CI = C / 16, NB = CI + MI;
+    static constexpr size_t oY = sizeof(T) * C * Tile::KS, oS = 2 * oY, szBuf = oS + sizeof(T) * M * Tile::KS, kBytes = 2 * szBuf;
+    typedef StepRows<T, C, NT, false, (HINT & kHintX) != 0> RX;
+    typedef StepRows<T, C, NT, false, (HINT & kHintY) != 0> RY;
+    typedef StepRows<T, M, NT, true, (HINT & kHintSt) != 0> RS;
+    RX rx;
+    RY ry;
+    RS rs;
+    typename RX::Stage sx[2];
+    typename RY::Stage sy[2];
+    typename RS::Stage ss[2];
+    int n, tid;
+    __device__ __forceinline__ void fetch(int u, int step)
+    {
+        rx.fetch(sx[u], step);
+        ry.fetch(sy[u], step);
+        rs.fetch(ss[u], step);
+    }
+    __device__ __forceinline__ HeadContraction(const T *X, const T *Y, size_t ldx, int d, const T *St, int len, int tid_)
+        : rx(X, ldx, len, tid_), ry(Y, ldx, len, tid_), rs(St, 0, 0, tid_), n(d / Tile::KS), tid(tid_)
+    {
 #pragma unroll
-    for (int rb = 0; rb < NW; ++rb)
-#pragma unroll
-        for (int cb = 0; cb < NB; ++cb) acc[rb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // Rows past the end of a ragged chunk are read as copies of its last row: they stay finite
-    // and only ever produce rows of the result that are not stored or that meet zero weights.
-    uint32_t xo[CI], so[MI];
-#pragma unroll
-    for (int ni = 0; ni < CI; ++ni) xo[ni] = (uint32_t)min(ni * 16 + r, len - 1) * (uint32_t)ldx + g8;
-#pragma unroll
-    for (int ni = 0; ni < MI; ++ni) so[ni] = (uint32_t)(ni * 16 + r) * kSnapTile + g8;
-    typedef typename Atom<T>::Frag Frag;
-    // a wave takes 64 columns at a time: the two halves of every 128-byte line are asked for by the
-    // same wave in consecutive instructions
-    for (int kk = 64 * w; kk < d; kk += 64 * NW) {
-        Frag fx[2][CI], fy[2][CI], fs[2][MI];
-#pragma unroll
-        for (int hh = 0; hh < 2; ++hh) {
-            const int k0 = kk + 32 * hh;
-#pragma unroll
-            for (int ni = 0; ni < CI; ++ni) fx[hh][ni] = (HINT & kHintX) ? Atom<T>::load_nt(X + xo[ni] + k0) : Atom<T>::load(X + xo[ni] + k0);
+        for (int u = 0; u < 2; ++u) {
+            fetch(u, min(u, n - 1));
+            __builtin_amdgcn_sched_barrier(0);
         }
+    }
+    __device__ __forceinline__ void finish(f32x4 (&run)[MI], typename Atom<T>::Frag16 (&a)[CI], typename Atom<T>::Frag16 (&alo)[CI],
+                                           unsigned char *buf, int lane, int w)
+    {
+        const int r = lane & 15, g4 = (lane >> 4) * 4;
+        StepSums<T, NB> sums;
+        walk_steps(
+            n, [&](auto u, int step) { fetch(decltype(u)::value, step); },
+            [&](auto u, int) {
+                constexpr int U = decltype(u)::value;
+                unsigned char *p = buf + U * szBuf;
+                rx.template put<(PHI & kHintX) != 0>(reinterpret_cast<T *>(p), sx[U], tid);
+                ry.template put<(PHI & kHintY) != 0>(reinterpret_cast<T *>(p + oY), sy[U], tid);
+                rs.put(reinterpret_cast<T *>(p + oS), ss[U], tid);
+            },
+            [&](auto parity, int b) {
+                f32x4(&acc)[NB] = sums.x[decltype(parity)::value % StepSums<T, NB>::P];
+                const T *X = reinterpret_cast<const T *>(buf + b * szBuf), *Y = reinterpret_cast<const T *>(buf + b * szBuf + oY);
+                const T *S = reinterpret_cast<const T *>(buf + b * szBuf + oS);
 #pragma unroll
-        for (int hh = 0; hh < 2; ++hh) {
-            const int k0 = kk + 32 * hh;
+                for (int f = 0; f < Tile::F; ++f) {
+                    const typename Atom<T>::Frag x = Tile::frag(X, 16 * w, f, lane);
 #pragma unroll
-            for (int ni = 0; ni < CI; ++ni) fy[hh][ni] = (HINT & kHintY) ? Atom<T>::load_nt(Y + xo[ni] + k0) : Atom<T>::load(Y + xo[ni] + k0);
-        }
+                    for (int ni = 0; ni < MI; ++ni) Atom<T>::mma(acc[CI + ni], Tile::frag(S, 16 * ni, f, lane), x);
 #pragma unroll
-        for (int hh = 0; hh < 2; ++hh) {
-            const int k0 = kk + 32 * hh;
-#pragma unroll
-            for (int ni = 0; ni < MI; ++ni) fs[hh][ni] = (HINT & kHintSt) ? Atom<T>::load_nt(St + so[ni] + snap_col<M>(k0)) : Atom<T>::load(St + so[ni] + snap_col<M>(k0));
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        if (GEN && phi) {
-#pragma unroll
-            for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-                for (int ni = 0; ni < CI; ++ni) {
-                    if (phi & kHintX) swish_frag<T>(fx[hh][ni]);
-                    if (phi & kHintY) swish_frag<T>(fy[hh][ni]);
+                    for (int cb = 0; cb < CI; ++cb)
+                        if (cb <= w) Atom<T>::mma(acc[cb], Tile::frag(Y, 16 * cb, f, lane), x);   // wave-uniform
                 }
+            });
+#pragma unroll
+        for (int cb = 0; cb < CI; ++cb) {
+            f32x4 x = sums.total(cb);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) x[j] = (cb < w || (cb == w && g4 + j <= r)) ? x[j] : 0.f;
+            a[cb] = to_frag16<T>(x);
+            alo[cb] = rest_frag16<T>(x, a[cb]);
         }
 #pragma unroll
-        for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-            for (int rb = 0; rb < NW; ++rb) {
-#pragma unroll
-                for (int cb = 0; cb <= rb; ++cb) Atom<T>::mma(acc[rb][cb], fy[hh][cb], fx[hh][rb]);
-#pragma unroll
-                for (int ni = 0; ni < MI; ++ni) Atom<T>::mma(acc[rb][CI + ni], fs[hh][ni], fx[hh][rb]);
-            }
+        for (int ni = 0; ni < MI; ++ni) run[ni] = sums.total(CI + ni);
     }
-    early_loads();
-    f32x4 own[NB];
-    reduce_row_blocks<NW, NB, CI, RPR>(own, acc, Red, lane, w);
-#pragma unroll
-    for (int cb = 0; cb < CI; ++cb) {
-        f32x4 x = own[cb];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) x[j] = (cb < w || (cb == w && g4 + j <= r)) ? x[j] : 0.f;
-        a[cb] = to_frag16<T>(x);
-        alo[cb] = rest_frag16<T>(x, a[cb]);
-    }
-#pragma unroll
-    for (int ni = 0; ni < MI; ++ni) run[ni] = own[CI + ni];
-}
+};
 
-// Second part: the gated sum itself, from the tiles of contract_heads and of BlockGates::write_tiles (which
+// Second part: the gated sum itself, from the tiles of HeadContraction and of BlockGates::write_tiles (which
 // must be visible to all waves).  Vp: LDS, kPrivate<T, M> elements of this wave's own.
 //   run[ni][j] <- exp(G_t[i]) * <X_t, St[i]>  +  sum_{r<=t} <X_t, Y_r> s_r[i] exp(G_t[i]-G_r[i])
 // `run` walks its reference from the chunk start (where it is the inter-chunk term) to the end of this

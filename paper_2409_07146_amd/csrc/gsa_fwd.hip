@@ -98,14 +98,14 @@ template <typename T, int M, bool WIDE> struct ChunkFwdLds {
     static constexpr size_t oVn = 0;                                  // Vn [C][ldn]
     static constexpr size_t oVt = oVn + sizeof(T) * C * ldn;          // Vt [M][ldt]
     static constexpr size_t oRb = oVt + sizeof(T) * M * ldt;          // Rb [C/16][M] fp32
-    static constexpr size_t endR = oRb + sizeof(float) * (C / 16) * M;
-    static constexpr size_t oMat = (WIDE && endR < 2 * Wide<M>::szBuf) ? 2 * Wide<M>::szBuf : endR;   // A2, p*exp(G)
-    static constexpr size_t oVp = oMat + (WIDE ? Wide<M>::szTok + Wide<M>::szSlot : 0);   // per wave: see gated_rows
-    static constexpr size_t end = oVp + sizeof(T) * kPrivate<T, M> * (C / 16);
-    static constexpr int kRpr = 2;                 // row blocks per round of the reduction
-    static constexpr size_t szRed = sizeof(f32x4) * kWave * (C / 16) *
-                                    reduce_fragments<C / 16, C / 16 + M / 16, C / 16, kRpr>();   // from offset 0: dead before the tiles are written
-    static constexpr size_t bytes = end > szRed ? end : szRed;
+    // behind the gate tiles: the buffers of the contraction; in their place gated_rows' scratch of every wave, then the
+    // buffers of the wide contraction; A2 and p*exp(G) behind what scratch a slower wave may still use
+    static constexpr size_t oBuf = oRb + sizeof(float) * (C / 16) * M;
+    static constexpr size_t szVp = sizeof(T) * kPrivate<T, M> * (C / 16), szWide = WIDE ? 2 * Wide<M>::szBuf : 0;
+    static constexpr size_t oMat = oBuf + (szVp > szWide ? szVp : szWide);
+    static constexpr size_t end = oMat + (WIDE ? Wide<M>::szTok + Wide<M>::szSlot : 0);
+    static constexpr size_t endC = oBuf + HeadContraction<T, M, C, 0, 0>::kBytes;
+    static constexpr size_t bytes = end > endC ? end : endC;
 };
 
 // GEN: the general form (write intensities from `sin` when it is not NULL; opts: read-out in the low
@@ -139,19 +139,21 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_fwd_kernel
     const T *Kn = S + ch * lay.stride + lay.oK;      // key memory at chunk start (tiled)
     const int rowb = 16 * w, t = rowb + r;            // this wave's row block, this lane's token
 
-    // ---- pass 1: z = scale * (inter + gated intra), Eq. (gla-chunk) with the gate on the slot side
+    // ---- pass 1: z = scale * (inter + gated intra), Eq. (gla-chunk) with the gate on the slot side.  The gates are
+    // evaluated while the first operands of the contraction are on their way.
     f32x4 p[MI];
     typename Atom<T>::Frag16 a[CI], alo[CI];
     BlockGates<M, GEN> bg;
-    // q, k and the key memory are not read again by this forward call: all three hinted
-    contract_heads<T, M, C, GEN, L::kRpr, kHintX | kHintY | kHintSt>(
-        p, a, alo, reinterpret_cast<f32x4 *>(smem), q + tokh * d_k, k + tokh * d_k, (size_t)H * d_k, d_k, Kn, ci.len, lane, w,
-        PHI ? (kHintX | kHintY) : 0,
-        [&] { bg.load(g + tokh * M, (size_t)H * M, ci.len, rowb, lane, (GEN && sin) ? sin + tokh * M : nullptr, gate_tau); });
-    bg.template finish<T>(ci.len, rowb, lane);
-    bg.template write_tiles<T>(Vn, L::ldn, Vt, L::ldt, Rb, rowb, lane);
-    __syncthreads();
-    gated_rows<T, M, C, GEN>(p, a, alo, bg, Vt, L::ldt, Rb, reinterpret_cast<T *>(smem + L::oVp) + w * kPrivate<T, M>, lane, w);
+    bg.load(g + tokh * M, (size_t)H * M, ci.len, rowb, lane, (GEN && sin) ? sin + tokh * M : nullptr, gate_tau);
+    __builtin_amdgcn_sched_barrier(0);
+    {
+        // q, k and the key memory are not read again by this forward call: all three hinted
+        HeadContraction<T, M, C, kHintX | kHintY | kHintSt, PHI ? (kHintX | kHintY) : 0> hc(q + tokh * d_k, k + tokh * d_k, (size_t)H * d_k, d_k, Kn, ci.len, tid);
+        bg.template finish<T>(ci.len, rowb, lane);
+        bg.template write_tiles<T>(Vn, L::ldn, Vt, L::ldt, Rb, rowb, lane);
+        hc.finish(p, a, alo, smem + L::oBuf, lane, w);
+    }
+    gated_rows<T, M, C, GEN>(p, a, alo, bg, Vt, L::ldt, Rb, reinterpret_cast<T *>(smem + L::oBuf) + w * kPrivate<T, M>, lane, w);
     // ---- softmax over the slots, in registers
 #pragma unroll
     for (int ni = 0; ni < MI; ++ni) p[ni] *= scale;
@@ -220,8 +222,8 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_fwd_kernel
     // ---- pass 2: o = A2 V + (p * exp(G)) Vt_start (B=8, T=2048, H=4, d=512, m=64: 57 us and a kernel of its own of 40 us -> 86 us)
     if constexpr (WIDE) {
         __syncthreads();   // the small matrices are whole, and the tiles they were made from are dead
-        if (ci.len == C) W::template walk<true>(unit, units, sa, sb, smem, ci.len, tid);
-        else W::template walk<false>(unit, units, sa, sb, smem, ci.len, tid);
+        if (ci.len == C) W::template walk<true>(unit, units, sa, sb, smem + L::oBuf, ci.len, tid);
+        else W::template walk<false>(unit, units, sa, sb, smem + L::oBuf, ci.len, tid);
     }
 }
 
