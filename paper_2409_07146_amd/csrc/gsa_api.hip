@@ -53,7 +53,7 @@ gsa_status make_plan(const gsa_problem *p, Plan *pl, bool fine_segments = true)
     size_t off = 0;
     pl->off_table = off;  off += align_up(p->cu_seqlens ? (size_t)slots * 4 * sizeof(int32_t) : 0);
     pl->off_seqtab = off; off += align_up(p->cu_seqlens ? (size_t)p->n_seqs * 4 * sizeof(int32_t) : 0);
-    pl->off_segbase = off; off += align_up(p->cu_seqlens ? ((size_t)p->n_seqs + 1) * sizeof(int32_t) : 0);
+    pl->off_segbase = off; off += align_up(p->cu_seqlens ? ((size_t)p->n_seqs + 2) * sizeof(int32_t) : 0);
     pl->off_Wf = off;     off += align_up(ch * M * C * esz);
     pl->off_dec = off;    off += align_up(ch * M * sizeof(float));
     pl->off_tA = off;     off += align_up(ch * C * C * esz);
@@ -66,7 +66,9 @@ gsa_status make_plan(const gsa_problem *p, Plan *pl, bool fine_segments = true)
         const int64_t max_nch = ((int64_t)p->T + pl->chunk - 1) / pl->chunk;
         const int64_t base = (int64_t)pl->n_seqs * p->H * ((dk + dv) / 64);   // workgroups of an unsegmented scan
         auto segs = [&](int64_t c) { return (max_nch + c - 1) / c; };
-        bool on = max_nch > gsa::kSegChunks + gsa::kSegChunks / 2 && base < 512 && base * segs(gsa::kSegChunks) <= 8192;
+        // In packed form the lengths are the device's to know: the prepare kernel decides by the same rule (scan_unsegmented).
+        bool on = base < 512 && base * segs(gsa::kSegChunks) <= 8192 &&
+                  !gsa::scan_unsegmented(max_nch, p->cu_seqlens ? 0 : max_nch * base);
         pl->seg_chunks = gsa::kSegChunks;
         pl->fine = false;
         // Batch form (every sequence really is T long): the shortest segments that still leave the chip one

@@ -210,7 +210,7 @@ __device__ __forceinline__ void store4(float *p, float a, float b, float c, floa
 struct ChunkMap {
     const int32_t *table;   // packed: [4 * n_chunk_slots] = {seq, tok0, len, index in seq}; batch: NULL
     const int32_t *seq_tab; // packed: [4 * n_seqs] = {first chunk id, number of chunks, first token, tokens}
-    const int32_t *seg_base; // packed: [n_seqs + 1] running count of scan segments before each sequence
+    const int32_t *seg_base; // packed, scans in segments: [n_seqs + 1] running count of scan segments before each sequence, chunks per segment
     int32_t T;              // batch: tokens per sequence
     int32_t chunk;          // tokens per chunk (C in Appendix A)
     int32_t chunks_per_seq; // batch: ceil(T / chunk)

@@ -27,13 +27,14 @@ namespace gsa {
 // ---------------------------------------------------------------------------------------
 // Packed form: build the chunk table from the device-side sequence offsets.
 // ---------------------------------------------------------------------------------------
+// width: workgroups per chunk of an unsegmented scan (0: the scans are not segmented, segbase is not needed).
 __global__ void prepare_kernel(const int32_t *__restrict__ cu, int n_seqs, int T, int kChunk, int chunk_slots,
-                               int seg_chunks, int32_t *__restrict__ table, int32_t *__restrict__ seqtab,
+                               int seg_chunks, int width, int32_t *__restrict__ table, int32_t *__restrict__ seqtab,
                                int32_t *__restrict__ segbase)
 {
     __shared__ int total;
     if (threadIdx.x == 0) {
-        int c0 = 0, prev_end = 0, nsegs = 0;
+        int c0 = 0, prev_end = 0, longest = 0;
         for (int s = 0; s < n_seqs; ++s) {
             int b = min(max(cu[s], prev_end), T);
             int e = min(max(cu[s + 1], b), T);
@@ -42,12 +43,20 @@ __global__ void prepare_kernel(const int32_t *__restrict__ cu, int n_seqs, int T
             seqtab[4 * s + 1] = nch;
             seqtab[4 * s + 2] = b;
             seqtab[4 * s + 3] = e - b;
-            segbase[s] = nsegs;                                    // scan segments (gsa_scan.hip); an empty
-            nsegs += max(1, (nch + seg_chunks - 1) / seg_chunks);  // sequence still has one
+            longest = max(longest, nch);
             c0 += nch;
             prev_end = e;
         }
-        segbase[n_seqs] = nsegs;
+        if (width) {   // scan segments (gsa_scan.hip); an empty sequence still has one
+            if (scan_unsegmented(longest, (long long)c0 * width)) seg_chunks = max(longest, 1);   // one per sequence
+            int nsegs = 0;
+            for (int s = 0; s < n_seqs; ++s) {
+                segbase[s] = nsegs;
+                nsegs += max(1, (seqtab[4 * s + 1] + seg_chunks - 1) / seg_chunks);
+            }
+            segbase[n_seqs] = nsegs;
+            segbase[n_seqs + 1] = seg_chunks;
+        }
         total = c0;
     }
     __syncthreads();
@@ -76,7 +85,7 @@ hipError_t launch_prepare(const Plan &pl, const Work &w, hipStream_t st)
     if (!pl.cu_seqlens) return hipSuccess;
     KernelTimer kt(kSlotPrepare, st);
     hipLaunchKernelGGL(prepare_kernel, dim3(1), dim3(256), 0, st, pl.cu_seqlens, pl.n_seqs, pl.T, pl.chunk,
-                       pl.chunk_slots, pl.seg_chunks, w.table, w.seqtab, w.segbase);
+                       pl.chunk_slots, pl.seg_chunks, pl.max_seg > 1 ? pl.H * ((pl.d_k + pl.d_v) / 64) : 0, w.table, w.seqtab, w.segbase);
     return hipGetLastError();
 }
 

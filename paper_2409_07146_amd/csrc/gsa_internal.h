@@ -42,7 +42,7 @@ struct Plan {
 struct Work {
     int32_t *table;   // [4*chunk_slots] packed form only
     int32_t *seqtab;  // [4*n_seqs]     packed form only
-    int32_t *segbase; // [n_seqs+1]     packed form only: scan segments before each sequence
+    int32_t *segbase; // [n_seqs+2]     packed form only: scan segments before each sequence, chunks per segment
     // per (chunk, head) records, element type = I/O dtype unless noted; KM = max(m, 32)
     void *Wf;         // [m][C] in fragment order   forward scan weights s*exp(G_C-G)
     float *dec;       // [m]         chunk decay exp(G_C)                                  (fp32)

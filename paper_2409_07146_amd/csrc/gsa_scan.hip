@@ -99,7 +99,7 @@ template <typename T> struct ScanArgs {
     float *outK, *outV;    // [n_seqs][H][M][d] or NULL: acc after the last chunk
     T *outJ;               // one record per (sequence, head), or NULL: the same, element type T
     // long sequences cut into segments (modes 1 and 2 of the kernel):
-    int seg_chunks;        // chunks per segment
+    int seg_chunks;        // chunks per segment (packed: as the prepare kernel decided, behind seg_base)
     int max_seg;           // segments per sequence the grid provides for
     float *sumY;           // [n_seqs][max_seg][H][M][d_k+d_v]   what a segment adds, from a zero start
     float *sumD;           // [n_seqs][max_seg][H][slices][M]    its total decay
@@ -256,9 +256,10 @@ __global__ __launch_bounds__((ScanGeo<T, M>::NT), 2) void scan_kernel(ChunkMap c
     // the chunks this workgroup walks: [first, first + nch) of the sequence
     int first = 0, nch = nch_seq, nseg = 1;
     if (MODE != 0) {
-        nseg = max(1, (nch_seq + a.seg_chunks - 1) / a.seg_chunks);
-        first = seg * a.seg_chunks;
-        nch = min(a.seg_chunks, nch_seq - first);
+        const int seg_chunks = cm.seg_base ? cm.seg_base[n_seqs + 1] : a.seg_chunks;
+        nseg = max(1, (nch_seq + seg_chunks - 1) / seg_chunks);
+        first = seg * seg_chunks;
+        nch = min(seg_chunks, nch_seq - first);
         const int last_of_walk = REVERSE ? 0 : nseg - 1;
         if (seg >= nseg || (MODE == 1 && seg == last_of_walk)) return;   // uniform over the workgroup
         if (nch_seq == 0) nch = 0;   // a sequence without tokens still hands its initial memory through (MODE 2)
@@ -545,7 +546,9 @@ static hipError_t run_scan_mode(const Plan &pl, const ChunkMap &cm, const ScanAr
     // 31.2 and 32.6); with more, more loads in flight only get into the way of the stores (512 workgroups: 57 and 56).  With 128
     // slots (256 workgroups 26.5 and 25.4) and for fp32 from 64 on (registers): two.
     constexpr int kDeep = M > 64 || (sizeof(T) == 4 && M > 32) ? 2 : 4;
-    auto kern = total <= 256 ? scan_kernel<T, M, REVERSE, MODE, kDeep> : scan_kernel<T, M, REVERSE, MODE, 2>;
+    // (A packed batch may walk its sequences whole, see scan_unsegmented: what counts is how many workgroups that takes.)
+    auto kern = total / (MODE != 0 && pl.cu_seqlens ? a.max_seg : 1) <= 256 ? scan_kernel<T, M, REVERSE, MODE, kDeep>
+                                                                             : scan_kernel<T, M, REVERSE, MODE, 2>;
     constexpr size_t lds = ScanLds<T, M>::bytes;
     GSA_HIP_TRY(allow_lds(kern, lds));
     KernelTimer kt(slot, st);
