@@ -203,7 +203,9 @@ template <typename T, int M, bool WIDE> struct IntraLds {
     static constexpr size_t oMat = (WIDE && endR < 2 * Wide<M>::szBuf) ? 2 * Wide<M>::szBuf : endR;
     static constexpr size_t oK = sizeof(T) * C * StepTile<T>::KS, oE = 2 * oK, szBuf = oE + sizeof(T) * M * StepTile<T>::KS;   // q, k or v, E
     static constexpr size_t szMat = WIDE ? 3 * Wide<M>::szTok + 2 * Wide<M>::szSlot : 0;
-    static constexpr size_t bytes = oMat + (szMat > 2 * szBuf ? szMat : 2 * szBuf);
+    static constexpr size_t oEx = oMat + szMat;   // rows of the outputs on their way out
+    static constexpr size_t szAll = szMat + (WIDE ? Wide<M>::szEx : 0);
+    static constexpr size_t bytes = oMat + (szAll > 2 * szBuf ? szAll : 2 * szBuf);
 };
 
 template <typename T> struct IntraArgs {
@@ -259,7 +261,6 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
     }
     const T *AvT = a.tAvT + ch * C * C;
     const int rowb = 16 * w;
-
     const int t = rowb + r;                                  // this lane's token
     const bool live = t < ci.len;
     const size_t row = (tokh + (size_t)min(t, ci.len - 1) * H) * M + g4;   // clamped; nothing is stored past len
@@ -532,16 +533,17 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
     }
     // ---- phase 2c: the slot-side operand of dk and dv, s*exp(G_C - G)
     // (the five small matrices stay in LDS when the wide contractions follow here)
-    constexpr int lda = WIDE ? Wide<M>::lda : C, lds = WIDE ? Wide<M>::lds : KM;
     T *mB = a.tB + ch * C * C, *mBT = a.tBT + ch * C * C, *mA2T = a.tA2T + ch * C * C, *mD = a.tDZe + ch * C * KM, *mS = a.tSbe + ch * C * KM;
     if constexpr (WIDE) {
         mB = reinterpret_cast<T *>(smem + L::oMat);
-        mBT = mB + C * lda;
-        mA2T = mBT + C * lda;
-        mD = mA2T + C * lda;
-        mS = mD + C * lds;
+        mBT = mB + C * C;
+        mA2T = mBT + C * C;
+        mD = mA2T + C * C;
+        mS = mD + C * KM;
     }
-    T *dS = mS + (size_t)t * lds, *dD = mD + (size_t)t * lds;
+    typedef Wide<M> W;
+    auto tok_at = [](int row, int col) { return WIDE ? W::template at<C>(row, col) : row * C + col; };
+    auto slot_at = [](int row, int col) { return WIDE ? W::template at<KM>(row, col) : row * KM + col; };
 #pragma unroll
     for (int ni = 0; ni < MI; ++ni) {
         f32x4 y;
@@ -550,10 +552,9 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
 #pragma unroll
         for (int b = 1; b < CI; ++b)
             if (b > w) y *= *reinterpret_cast<const f32x4 *>(Rb + b * M + ni * 16 + g4);
-        store_frag16<T>(dS + ni * 16 + g4, y);
+        store_frag16<T>(mS + slot_at(t, ni * 16 + g4), y);
     }
-    if (M < KM) store_frag16<T>(dS + M + g4, f32x4{0.f, 0.f, 0.f, 0.f});   // the padded slot columns
-    typedef Wide<M> W;
+    if (M < KM) store_frag16<T>(mS + slot_at(t, M + g4), f32x4{0.f, 0.f, 0.f, 0.f});   // the padded slot columns
     typename W::Stage sa, sb;
     const int nk = d_k / 64, units = 2 * nk + d_v / 64;
     const T *const SK = a.S + ch * a.lay.stride + a.lay.oK;
@@ -581,7 +582,6 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
             wd[ni][j] *= e;
             p[ni][j] *= e;
         }
-    T *dB = mB + (size_t)t * lda, *dBT = mBT + rowb, *dA2T = mA2T + rowb;
 #pragma unroll
     for (int b = CI - 1; b >= 0; --b) {
         const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
@@ -589,10 +589,10 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
         if (b == w && bg.kind != kNarrow) {   // weights are already at the start of the block
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                dBT[(size_t)(b * 16 + g4 + j) * lda + r] = from_f32<T>(exb[j]);
-                dA2T[(size_t)(b * 16 + g4 + j) * lda + r] = from_f32<T>(exa[j]);
+                mBT[tok_at(b * 16 + g4 + j, t)] = from_f32<T>(exb[j]);
+                mA2T[tok_at(b * 16 + g4 + j, t)] = from_f32<T>(exa[j]);
             }
-            store_frag16<T>(dB + b * 16 + g4, exb);
+            store_frag16<T>(mB + tok_at(t, b * 16 + g4), exb);
             continue;
         }
         if (b <= w) {   // wave-uniform
@@ -612,13 +612,13 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
                 }
             }
         }
-        store_frag16<T>(dB + b * 16 + g4, xb);
-        store_frag16<T>(dBT + (size_t)(b * 16 + r) * lda + g4, xbt);
-        store_frag16<T>(dA2T + (size_t)(b * 16 + r) * lda + g4, xat);
+        store_frag16<T>(mB + tok_at(t, b * 16 + g4), xb);
+        store_frag16<T>(mBT + tok_at(b * 16 + r, rowb + g4), xbt);
+        store_frag16<T>(mA2T + tok_at(b * 16 + r, rowb + g4), xat);
     }
 #pragma unroll
-    for (int ni = 0; ni < MI; ++ni) store_frag16<T>(dD + ni * 16 + g4, wd[ni]);
-    if (M < KM) store_frag16<T>(dD + M + g4, f32x4{0.f, 0.f, 0.f, 0.f});
+    for (int ni = 0; ni < MI; ++ni) store_frag16<T>(mD + slot_at(t, ni * 16 + g4), wd[ni]);
+    if (M < KM) store_frag16<T>(mD + slot_at(t, M + g4), f32x4{0.f, 0.f, 0.f, 0.f});
     // ---- phase 2e: dg = (suffix sum of dGam inside the chunk) + carry - exp(g) ds
     __syncthreads();   // the other blocks' totals
 #pragma unroll
@@ -637,8 +637,8 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
     }
     // ---- phase 3: dq, dk, dv (B=8, T=2048, H=4, d=512, m=64: 131 us and a kernel of its own of 102 us -> 200 us)
     if constexpr (WIDE) {
-        if (ci.len == C) W::template walk<true>(unit, units, sa, sb, smem, ci.len, tid);
-        else W::template walk<false>(unit, units, sa, sb, smem, ci.len, tid);
+        if (ci.len == C) W::template walk<true>(unit, units, sa, sb, smem, smem + L::oEx, ci.len, tid);
+        else W::template walk<false>(unit, units, sa, sb, smem, smem + L::oEx, ci.len, tid);
     }
 }
 

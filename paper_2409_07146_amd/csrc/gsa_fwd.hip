@@ -112,7 +112,8 @@ template <typename T, int M, bool WIDE> struct ChunkFwdLds {
     static constexpr size_t oBuf = oRb + sizeof(float) * (C / 16) * M;
     static constexpr size_t szVp = sizeof(T) * kPrivate<T, M> * (C / 16), szWide = WIDE ? 2 * Wide<M>::szBuf : 0;
     static constexpr size_t oMat = oBuf + (szVp > szWide ? szVp : szWide);
-    static constexpr size_t end = oMat + (WIDE ? Wide<M>::szTok + Wide<M>::szSlot : 0);
+    static constexpr size_t oEx = oMat + (WIDE ? Wide<M>::szTok + Wide<M>::szSlot : 0);   // rows of o on their way out
+    static constexpr size_t end = oEx + (WIDE ? Wide<M>::szEx : 0);
     static constexpr size_t endC = oBuf + HeadContraction<T, M, C, 0, 0>::kBytes;
     static constexpr size_t bytes = end > endC ? end : endC;
 };
@@ -182,7 +183,6 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_fwd_kernel
     // ---- pass-2 pair weights A2[t][r] = sum_i p_t[i] s_r[i] exp(G_t[i] - G_r[i]), r <= t: row t of this wave's
     // block, one column block after the other, nearest first; `p` walks its reference backwards with them and
     // ends as the inter-chunk weights p * exp(G)
-    constexpr int lda = WIDE ? Wide<M>::lda : C, lds = WIDE ? Wide<M>::lds : KM;
     T *mA = tA + ch * C * C, *mP = tP + ch * C * KM;
     typedef Wide<M> W;
     typename W::Stage sa, sb;
@@ -199,7 +199,8 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_fwd_kernel
         W::fetch(sa, unit(0), ci.len, tid);
         W::fetch(sb, unit(min(1, units - 1)), ci.len, tid);
     }
-    T *dA = mA + (size_t)t * lda, *dP = mP + (size_t)t * lds;
+    auto dA = [&](int col) { return mA + (WIDE ? W::template at<C>(t, col) : t * C + col); };
+    auto dP = [&](int col) { return mP + (WIDE ? W::template at<KM>(t, col) : t * KM + col); };
     f32x4 diag = {0.f, 0.f, 0.f, 0.f};
     if (bg.kind == kPairs) diag = pair_tile_exact<M, GEN>(p, bg, lane);
     if (bg.kind == kHalf) diag = pair_tile_half<T, M, GEN>(p, bg, lane);
@@ -223,16 +224,16 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_fwd_kernel
                 for (int j = 0; j < 4; ++j) x[j] = g4 + j <= r ? x[j] : 0.f;
             }
         }
-        store_frag16<T>(dA + b * 16 + g4, x);
+        store_frag16<T>(dA(b * 16 + g4), x);
     }
 #pragma unroll
-    for (int ni = 0; ni < MI; ++ni) store_frag16<T>(dP + ni * 16 + g4, p[ni]);
-    if (M < KM) store_frag16<T>(dP + M + g4, f32x4{0.f, 0.f, 0.f, 0.f});   // the padded slot columns
+    for (int ni = 0; ni < MI; ++ni) store_frag16<T>(dP(ni * 16 + g4), p[ni]);
+    if (M < KM) store_frag16<T>(dP(M + g4), f32x4{0.f, 0.f, 0.f, 0.f});   // the padded slot columns
     // ---- pass 2: o = A2 V + (p * exp(G)) Vt_start (B=8, T=2048, H=4, d=512, m=64: 57 us and a kernel of its own of 40 us -> 86 us)
     if constexpr (WIDE) {
         __syncthreads();   // the small matrices are whole, and the tiles they were made from are dead
-        if (ci.len == C) W::template walk<true>(unit, units, sa, sb, smem + L::oBuf, ci.len, tid);
-        else W::template walk<false>(unit, units, sa, sb, smem + L::oBuf, ci.len, tid);
+        if (ci.len == C) W::template walk<true>(unit, units, sa, sb, smem + L::oBuf, smem + L::oEx, ci.len, tid);
+        else W::template walk<false>(unit, units, sa, sb, smem + L::oBuf, smem + L::oEx, ci.len, tid);
     }
 }
 

@@ -14,12 +14,19 @@
 namespace gsa {
 
 template <int M> struct Wide {
-    static constexpr int C = Geo<bf16_t>::C, NT = Geo<bf16_t>::NT, PAD = Atom<bf16_t>::kPad;
+    static constexpr int C = Geo<bf16_t>::C, NT = Geo<bf16_t>::NT;
     static constexpr int KM = (M < 32) ? 32 : M;              // slot rows, padded with zeros to the contraction depth
-    static constexpr int lda = C + PAD, lds = KM + PAD;       // A_tok [C][lda], A_slot [C][lds]
     static constexpr int kCols = TrTile<2>::kCols;
     static constexpr size_t szBuf = sizeof(bf16_t) * (KM + C) * kCols;   // slot tile, token tile
-    static constexpr size_t szTok = sizeof(bf16_t) * C * lda, szSlot = sizeof(bf16_t) * C * lds;
+    static constexpr size_t szTok = sizeof(bf16_t) * C * C, szSlot = sizeof(bf16_t) * C * KM;   // A_tok [C][C], A_slot [C][KM]
+    static constexpr size_t szEx = sizeof(bf16_t) * C * kCols;   // the rows of a unit on their way out, 16 per wave
+    // Element (row, col) of a matrix with rows of K elements: 16-byte pieces are XOR-swizzled so that the same piece of 16
+    // rows lies in all banks (no padding: with 64 slots chunk_intra's LDS is exactly half of a CU's).
+    template <int K> __device__ static __forceinline__ int at(int row, int col)
+    {
+        constexpr int R = K < 128 ? 128 / K : 1;   // rows per 256 bytes
+        return row * K + ((((col >> 3) ^ (row / R)) & (K / 8 - 1)) << 3) + (col & 7);
+    }
     static constexpr int SV = KM * kCols / 8 / NT, XV = C * kCols / 8 / NT;
     static_assert(SV * NT * 8 == KM * kCols && XV * NT * 8 == C * kCols, "whole 16-byte pieces per thread");
 
@@ -64,7 +71,7 @@ template <int M> struct Wide {
     // This wave's 16 tokens of one unit.  FULL: every token of the chunk exists (the store is then unconditional,
     // which keeps the number of memory operations in flight known).
     template <bool FULL>
-    __device__ static __forceinline__ void multiply(const Unit &u, const bf16_t *buf, int len, int rowb, int lane)
+    __device__ static __forceinline__ void multiply(const Unit &u, const bf16_t *buf, bf16_t *ex, int len, int rowb, int lane)
     {
         const int r = lane & 15, g = lane >> 4;
         f32x4 acc[4];
@@ -72,34 +79,45 @@ template <int M> struct Wide {
         for (int ni = 0; ni < 4; ++ni) acc[ni] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int k0 = 0; k0 < KM; k0 += 32) {
-            const bf16x8 a = Atom<bf16_t>::load(u.As + (rowb + r) * lds + k0 + 8 * g);
+            const bf16x8 a = Atom<bf16_t>::load(u.As + at<KM>(rowb + r, k0 + 8 * g));
 #pragma unroll
             for (int ni = 0; ni < 4; ++ni) Atom<bf16_t>::mma(acc[ni], frag(buf, k0, ni, lane), a);
         }
 #pragma unroll
         for (int k0 = 0; k0 < C; k0 += 32) {
-            const bf16x8 a = Atom<bf16_t>::load(u.At + (rowb + r) * lda + k0 + 8 * g);
+            const bf16x8 a = Atom<bf16_t>::load(u.At + at<C>(rowb + r, k0 + 8 * g));
 #pragma unroll
             for (int ni = 0; ni < 4; ++ni) Atom<bf16_t>::mma(acc[ni], frag(buf + KM * kCols, k0, ni, lane), a);
         }
-        bf16_t *o = u.out + (size_t)(rowb + r) * u.ld + 8 * g;
-        bf16x8 y[2];
+        // The wave's 16 rows meet in LDS of its own and leave in whole lines.  (Straight from the registers a store takes 16 bytes of
+        // each of 16 rows per quarter of the wave: 8 x 2048 tokens, 4 heads, 64 slots, d = 512 forward 82.3 -> 80.1 us, d = 640 98.7 -> 92.8 and
+        // intra-chunk gradients 254 -> 241; 32 slots 73.5 -> 70.8 and 153 -> 148.)
 #pragma unroll
-        for (int ni = 0; ni < 4; ++ni)
+        for (int h = 0; h < 2; ++h) {
+            bf16x8 y;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) y[ni >> 1][(ni & 1) * 4 + j] = (bf16_t)acc[ni][j];
-        if (FULL || rowb + r < len) {
-            __builtin_nontemporal_store(y[0], reinterpret_cast<bf16x8 *>(o));
-            __builtin_nontemporal_store(y[1], reinterpret_cast<bf16x8 *>(o + 32));
+            for (int j = 0; j < 8; ++j) y[j] = (bf16_t)acc[2 * h + (j >> 2)][j & 3];
+            *reinterpret_cast<bf16x8 *>(ex + at<kCols>(r, 32 * h + 8 * g)) = y;
         }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int row = 8 * h + (lane >> 3);
+            const bf16x8 y = *reinterpret_cast<const bf16x8 *>(ex + at<kCols>(row, (lane & 7) * 8));
+            if (FULL || rowb + row < len)
+                __builtin_nontemporal_store(y, reinterpret_cast<bf16x8 *>(u.out + (size_t)(rowb + row) * u.ld + (lane & 7) * 8));
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
-    // All units, unit(i) for i in [0, n).  sa, sb: units 0 and 1 as fetched by the caller.  buf: two buffers of szBuf;
+    // All units, unit(i) for i in [0, n).  sa, sb: units 0 and 1 as fetched by the caller.  smem: two buffers of szBuf;
+    // out: szEx;
     // the first must be free, the second is first written behind a barrier.  The small matrices must be in
     // LDS (a barrier follows the first write of a tile).  All threads of the workgroup must call it.
     template <bool FULL, typename F>
-    __device__ static __forceinline__ void walk(F &&unit, int n, Stage &sa, Stage &sb, unsigned char *smem, int len, int tid)
+    __device__ static __forceinline__ void walk(F &&unit, int n, Stage &sa, Stage &sb, unsigned char *smem, unsigned char *out, int len, int tid)
     {
         const int lane = tid & 63, rowb = 16 * __builtin_amdgcn_readfirstlane(tid >> 6);
+        bf16_t *const ex = reinterpret_cast<bf16_t *>(out) + rowb * kCols;
         bf16_t *b0 = reinterpret_cast<bf16_t *>(smem), *b1 = reinterpret_cast<bf16_t *>(smem + szBuf);
         to_lds(sa, b0, len, tid);
         __builtin_amdgcn_sched_barrier(0);
@@ -107,7 +125,7 @@ template <int M> struct Wide {
         __syncthreads();
         // the refills are unconditional (past the end they repeat the last unit)
         auto step = [&](Stage &nx, int i, bf16_t *cur, bf16_t *next) {
-            multiply<FULL>(unit(i), cur, len, rowb, lane);
+            multiply<FULL>(unit(i), cur, ex, len, rowb, lane);
             to_lds(nx, next, len, tid);
             __builtin_amdgcn_sched_barrier(0);
             fetch(nx, unit(min(i + 3, n - 1)), len, tid);
@@ -118,7 +136,7 @@ template <int M> struct Wide {
             step(sb, i, b0, b1);
             step(sa, i + 1, b1, b0);
         }
-        if (i < n) multiply<FULL>(unit(i), b0, len, rowb, lane);
+        if (i < n) multiply<FULL>(unit(i), b0, ex, len, rowb, lane);
     }
 };
 
