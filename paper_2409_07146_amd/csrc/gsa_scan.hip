@@ -30,17 +30,20 @@ namespace gsa {
 // Gate weights of the forward scan (chunk-parallel).
 //
 // Everything stays in the registers of the thread that owns a slot's tokens; only the partial sums of the
-// partitions meet in LDS.  (A form with gate and intensity tiles in LDS took as long at m = 64, 11 us with the
-// launch around it, and 20 us against 19 at m = 128.)
+// partitions meet in LDS.  A thread takes eight tokens, one 16-byte piece of the weights in bf16: the more waves share the
+// evaluation of the gates, the better it hides its own latency.  With 256 threads whatever the slots: 128 slots, 4 x 1000
+// tokens, 4 heads, 8.8 us instead of 7.0 (with the event), with gate logits 7 us more for the call; 64 slots the same.
 // ---------------------------------------------------------------------------------------
+template <typename T, int M> constexpr int kGateThreads = M * Geo<T>::C / 8;
 template <typename T, int M, bool GEN>
-__global__ __launch_bounds__(Geo<T>::NT) void gate_kernel(ChunkMap cm, int H, const float *__restrict__ g,
-                                                          const float *__restrict__ sin, float gate_tau,
-                                                          T *__restrict__ Wf, float *__restrict__ dec)
+__global__ __launch_bounds__((kGateThreads<T, M>)) void gate_kernel(ChunkMap cm, int H, const float *__restrict__ g,
+                                                                  const float *__restrict__ sin, float gate_tau,
+                                                                  T *__restrict__ Wf, float *__restrict__ dec)
 {
-    constexpr int C = Geo<T>::C, NT = Geo<T>::NT;
+    constexpr int C = Geo<T>::C, NT = kGateThreads<T, M>;
     typedef GatePrep<M, NT, C, GEN> Gates;
     constexpr int P = Gates::P, TP = Gates::TP;   // a thread owns one slot and TP consecutive tokens
+    static_assert(TP == 8, "one operand's worth of tokens");
     __shared__ float tot[NT];
     ChunkInfo ci;
     if (!chunk_lookup(cm, blockIdx.x, ci)) return;
@@ -66,20 +69,11 @@ __global__ __launch_bounds__(Geo<T>::NT) void gate_kernel(ChunkMap cm, int H, co
         after += x[tt];
     }
     T *W = Wf + ch * M * C;   // in fragment order: a slot's neighbours write next to it
-    constexpr int PV = 16 / sizeof(T);
-    static_assert(TP % 4 == 0, "tokens per thread");
-#pragma unroll
-    for (int t4 = 0; t4 < TP; t4 += 4) {
-        const int t = part * TP + t4;
-        T *dst = W + frag_order<T, C / 32>(i, t / PV * PV) + t % PV;
-        if (sizeof(T) == 2 && TP % 8 == 0) {
-            if (t4 % 8 == 0) {
-                const float y[8] = {w[t4], w[t4 + 1], w[t4 + 2], w[t4 + 3], w[(t4 + 4) % TP], w[(t4 + 5) % TP], w[(t4 + 6) % TP], w[(t4 + 7) % TP]};
-                store8<T>(dst, y);
-            }
-        } else {
-            store4(dst, w[t4], w[t4 + 1], w[t4 + 2], w[t4 + 3]);
-        }
+    if constexpr (sizeof(T) == 2) {
+        store8<T>(W + frag_order<T, C / 32>(i, part * TP), w);
+    } else {
+        store4(W + frag_order<T, C / 32>(i, part * TP), w[0], w[1], w[2], w[3]);
+        store4(W + frag_order<T, C / 32>(i, part * TP + 4), w[4], w[5], w[6], w[7]);
     }
     if (part == 0) dec[ch * M + i] = __expf(after);
 }
@@ -514,10 +508,10 @@ static hipError_t launch_gates_tm(const Plan &pl, const Work &w, const float *g,
     const ChunkMap cm = make_chunk_map(pl, w);
     KernelTimer kt(kSlotGates, st);
     if (sin || tau > 0.f)
-        hipLaunchKernelGGL((gate_kernel<T, M, true>), dim3(pl.chunk_slots, pl.H), dim3(Geo<T>::NT), 0, st, cm, pl.H, g,
+        hipLaunchKernelGGL((gate_kernel<T, M, true>), dim3(pl.chunk_slots, pl.H), dim3(kGateThreads<T, M>), 0, st, cm, pl.H, g,
                            sin, tau, (T *)w.Wf, w.dec);
     else
-        hipLaunchKernelGGL((gate_kernel<T, M, false>), dim3(pl.chunk_slots, pl.H), dim3(Geo<T>::NT), 0, st, cm, pl.H, g,
+        hipLaunchKernelGGL((gate_kernel<T, M, false>), dim3(pl.chunk_slots, pl.H), dim3(kGateThreads<T, M>), 0, st, cm, pl.H, g,
                            sin, 0.f, (T *)w.Wf, w.dec);
     return hipGetLastError();
 }
