@@ -347,8 +347,9 @@ __global__ __launch_bounds__((ScanGeo<T, M>::NT), 2) void scan_kernel(ChunkMap c
         st.len = min(C, ntok - xn * C);
 #pragma unroll
         for (int v = 0; v < XV; ++v) {
-            const uint32_t row = min(tid / PR + v * (NT / PR), st.len - 1);
-            st.x[v] = __builtin_nontemporal_load(reinterpret_cast<const Piece *>(xp + (row * xstep + xcol)));
+            const int row0 = min(v * (NT / PR), st.len - 1);   // uniform: 32 bits hold the bytes of the lanes' rows from there
+            const uint32_t row = min(tid / PR + v * (NT / PR), st.len - 1) - row0;
+            st.x[v] = __builtin_nontemporal_load(reinterpret_cast<const Piece *>(xp + (size_t)row0 * xstep + (row * xstep + xcol)));
         }
         const bool more = xleft > 0;
         xp += more ? dX : 0;
