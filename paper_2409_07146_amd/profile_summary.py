@@ -33,7 +33,7 @@ SIMDS = 256 * 4              # compute units x SIMDs
 def short(name):
     """A readable kernel name from the mangled one."""
     n = re.sub(r"^_ZN3gsa\d+", "", name)
-    m = re.match(r"(scan_kernel)I(DF16b|f)Li(\d+)ELi\d+ELb([01])ELi(\d)", n)
+    m = re.match(r"(scan_kernel)I(DF16b|f)Li(\d+)E(?:Li\d+E)?Lb([01])ELi(\d)", n)
     if m:
         mode = {"0": "", "1": " summary pass", "2": " segments"}[m.group(5)]
         return "scan_kernel<%s,%s,%s>%s" % ("bf16" if m.group(2) == "DF16b" else "f32", m.group(3),
