@@ -345,8 +345,8 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
                 rk.template put<PHI>(reinterpret_cast<T *>(at + L::oK), sk[U], tid);
                 rek.put(reinterpret_cast<T *>(at + L::oE), se[U], tid);
             },
-            [&](auto parity, int b) {
-                f32x4(&acc)[NB] = sums.x[decltype(parity)::value % StepSums<T, NB>::P];
+            [&](int b) {
+                f32x4(&acc)[NB] = sums.step();
                 const T *Q = reinterpret_cast<const T *>(buf + b * L::szBuf), *K = reinterpret_cast<const T *>(buf + b * L::szBuf + L::oK);
                 const T *E = reinterpret_cast<const T *>(buf + b * L::szBuf + L::oE);
 #pragma unroll
@@ -358,6 +358,7 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
                     for (int cb = 0; cb < CI; ++cb)
                         if (cb >= w) Atom<T>::mma(acc[cb], Tile::frag(Q, 16 * cb, f, lane), x);   // wave-uniform
                 }
+                sums.done();
             });
         if constexpr (kTwo) {
             load_scores();   // land during the value half
@@ -384,8 +385,8 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
                 rv.template put<PHI>(reinterpret_cast<T *>(at + L::oK), sv[U], tid);
                 rev.put(reinterpret_cast<T *>(at + L::oE), se[U], tid);
             },
-            [&](auto parity, int b) {
-                f32x4(&acc)[NB] = sums.x[decltype(parity)::value % StepSums<T, NB>::P];
+            [&](int b) {
+                f32x4(&acc)[NB] = sums.step();
                 const T *V = reinterpret_cast<const T *>(buf + b * L::szBuf + L::oK), *E = reinterpret_cast<const T *>(buf + b * L::szBuf + L::oE);
 #pragma unroll
                 for (int f = 0; f < Tile::F; ++f) {
@@ -393,6 +394,7 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
 #pragma unroll
                     for (int ni = 0; ni < MI; ++ni) Atom<T>::mma(acc[CI + ni], Tile::frag(E, 16 * ni, f, lane), x);
                 }
+                sums.done();
             });
 #pragma unroll
         for (int v = 0; v < RE::V; ++v) {   // eight neighbouring threads hold the pieces of one slot
@@ -405,13 +407,13 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
         }
 #pragma unroll
         for (int b = 0; b < CI; ++b) {
-            f32x4 x = sums.total(b);
+            f32x4 x = sums.sum[b];
 #pragma unroll
             for (int j = 0; j < 4; ++j) x[j] = (b > w || (b == w && g4 + j >= r)) ? x[j] : 0.f;
             fa[b] = to_frag16<T>(x);
         }
 #pragma unroll
-        for (int ni = 0; ni < MI; ++ni) ds[ni] = sums.total(CI + ni);
+        for (int ni = 0; ni < MI; ++ni) ds[ni] = sums.sum[CI + ni];
     }
     // what the rest of phase 2 needs from global memory
     if constexpr (!kTwo) {

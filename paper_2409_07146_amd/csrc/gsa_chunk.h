@@ -107,9 +107,8 @@ template <typename T, int ROWS, int NT, bool SNAP, bool HINT> struct StepRows {
 
 // The walk over n steps, two at a time, so that 256 bytes of a row are asked for together (one step at a time, two ahead: forward,
 // 8 x 2048 tokens, 4 heads, d = 512, 64 slots 92 us instead of 82).  fetch(u, step): loads of a step into register stage u; put(u,
-// step): stage u, which holds that step, to LDS buffer u; multiply(parity, b): the products of buffer b, which holds a step of that
-// parity.  The caller has issued the loads of the first two steps (past the end: of the last one again) and has the buffers
-// free; the walk ends with a barrier.
+// step): stage u, which holds that step, to LDS buffer u; multiply(b): the products of buffer b.  The caller has issued the loads of
+// the first two steps (past the end: of the last one again) and has the buffers free; the walk ends with a barrier.
 // PAIRS = false: one step at a time, stage and buffer 0 only, where two do not fit the registers.
 template <bool PAIRS = true, typename Fetch, typename Put, typename Multiply>
 __device__ __forceinline__ void walk_steps(int n, Fetch &&fetch, Put &&put, Multiply &&multiply)
@@ -125,10 +124,10 @@ __device__ __forceinline__ void walk_steps(int n, Fetch &&fetch, Put &&put, Mult
             if constexpr (PAIRS) fetch(odd, min(it + 3, n - 1));
         }
         __syncthreads();
-        multiply(even, 0);
+        multiply(0);
         __builtin_amdgcn_sched_barrier(0);   // operands of both at a time would not fit the registers
         if constexpr (PAIRS) {
-            if (it + 1 < n) multiply(odd, 1);
+            if (it + 1 < n) multiply(1);
         }
         __syncthreads();
         if constexpr (!PAIRS) {
@@ -137,26 +136,40 @@ __device__ __forceinline__ void walk_steps(int n, Fetch &&fetch, Put &&put, Mult
             __builtin_amdgcn_sched_barrier(0);
             if (it + 2 < n) fetch(even, it + 2);
             __syncthreads();
-            multiply(odd, 0);
+            multiply(0);
             __syncthreads();
         }
         if (it + 2 >= n) return;
     }
 }
 
-// Accumulators of such a walk.  fp32 sums the steps of either parity on their own: the longer one chain of roundings, the larger
-// its error (m = 32, 700 tokens, d_k = 192: dq 2.92e-7 from the fp64 recurrence with one chain, 2.56e-7 with two).
+// Accumulators of such a walk: step(), the products of one step, done().  fp32 sums every step on its own: the longer a chain of
+// roundings, the larger its error.  With one chain over all columns dq is 2.92e-7 from the fp64 recurrence (m = 32, 700 tokens, d_k = 192).
 template <typename T, int N> struct StepSums {
-    static constexpr int P = sizeof(T) == 4 ? 2 : 1;
-    f32x4 x[P][N];
+    static constexpr bool kSplit = sizeof(T) == 4;
+    f32x4 sum[N], part[kSplit ? N : 1];
     __device__ __forceinline__ StepSums()
     {
 #pragma unroll
-        for (int p = 0; p < P; ++p)
-#pragma unroll
-            for (int i = 0; i < N; ++i) x[p][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int i = 0; i < N; ++i) sum[i] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    __device__ __forceinline__ f32x4 total(int i) const { return P == 1 ? x[0][i] : x[0][i] + x[P - 1][i]; }
+    __device__ __forceinline__ auto step() -> f32x4 (&)[N]
+    {
+        if constexpr (kSplit) {
+#pragma unroll
+            for (int i = 0; i < N; ++i) part[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+            return part;
+        } else {
+            return sum;
+        }
+    }
+    __device__ __forceinline__ void done()
+    {
+        if constexpr (kSplit) {
+#pragma unroll
+            for (int i = 0; i < N; ++i) sum[i] += part[i];
+        }
+    }
 };
 
 // ----------------------------------------------------------------------------
@@ -387,8 +400,8 @@ template <typename T, int M, int C, int HINT, int PHI> struct HeadContraction {
                 ry.template put<(PHI & kHintY) != 0>(reinterpret_cast<T *>(p + oY), sy[U], tid);
                 rs.put(reinterpret_cast<T *>(p + oS), ss[U], tid);
             },
-            [&](auto parity, int b) {
-                f32x4(&acc)[NB] = sums.x[decltype(parity)::value % StepSums<T, NB>::P];
+            [&](int b) {
+                f32x4(&acc)[NB] = sums.step();
                 const T *X = reinterpret_cast<const T *>(buf + b * szBuf), *Y = reinterpret_cast<const T *>(buf + b * szBuf + oY);
                 const T *S = reinterpret_cast<const T *>(buf + b * szBuf + oS);
 #pragma unroll
@@ -400,17 +413,18 @@ template <typename T, int M, int C, int HINT, int PHI> struct HeadContraction {
                     for (int cb = 0; cb < CI; ++cb)
                         if (cb <= w) Atom<T>::mma(acc[cb], Tile::frag(Y, 16 * cb, f, lane), x);   // wave-uniform
                 }
+                sums.done();
             });
 #pragma unroll
         for (int cb = 0; cb < CI; ++cb) {
-            f32x4 x = sums.total(cb);
+            f32x4 x = sums.sum[cb];
 #pragma unroll
             for (int j = 0; j < 4; ++j) x[j] = (cb < w || (cb == w && g4 + j <= r)) ? x[j] : 0.f;
             a[cb] = to_frag16<T>(x);
             alo[cb] = rest_frag16<T>(x, a[cb]);
         }
 #pragma unroll
-        for (int ni = 0; ni < MI; ++ni) run[ni] = sums.total(CI + ni);
+        for (int ni = 0; ni < MI; ++ni) run[ni] = sums.sum[CI + ni];
     }
 };
 

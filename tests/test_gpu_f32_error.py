@@ -1,5 +1,6 @@
-"""Error of the fp32 gradients against the fp64 oracle, as a mean over seeds.  What decides it are the exponentials: theirs
-grows with the size of their argument, which is why a diagonal block splits its decay between the two factors."""
+"""Error of the fp32 gradients and memories against the fp64 oracle, as a mean over seeds.  What decides it are the exponentials: theirs
+grows with the size of their argument, which is why a diagonal block splits its decay between the two factors; and, with wide heads,
+the sums over the head dimension, whose error grows with the length of a chain."""
 import numpy as np
 import pytest
 
@@ -9,20 +10,25 @@ from tests.util import rel_l2, to_np64
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("m,T,d_k,d_v,bar_dq,bar_dK0", [
-    # Measured over 16 seeds, standard error 0.02e-7: dq 2.56e-7 and 3.16e-7, dK0 2.16e-7 and 2.17e-7; with the reference at
-    # the block's end 2.94e-7 and 3.45e-7, 2.29e-7 and 2.33e-7.  The bars lie between.
-    (32, 700, 192, 128, 2.75e-7, 2.24e-7),
-    (16, 500, 64, 64, 3.32e-7, 2.26e-7),
+@pytest.mark.parametrize("m,T,d_k,d_v,bar_dq,bar_dK0,bar_KT", [
+    # Measured over 16 seeds, standard error 0.02e-7: dq 2.41e-7 and 3.04e-7, dK0 1.95e-7 and 1.95e-7; with the reference of a diagonal at
+    # the block's end 2.94e-7 and 3.45e-7, 2.29e-7 and 2.33e-7.  The bars lie between.  KT with 16 slots 9.67e-8; with the decays
+    # behind a token summed in one chain 9.86e-8.
+    (32, 700, 192, 128, 2.75e-7, 2.24e-7, None),
+    (16, 500, 64, 64, 3.32e-7, 2.26e-7, 9.76e-8),
+    # 900 tokens: dq 2.42e-7, dK0 2.07e-7; with the head dimension summed in two chains 3.54e-7 and 3.32e-7
+    (64, 500, 512, 512, 2.9e-7, 2.6e-7, None),
 ])
-def test_f32_gradient_error(oracle, m, T, d_k, d_v, bar_dq, bar_dK0):
+def test_f32_gradient_error(oracle, m, T, d_k, d_v, bar_dq, bar_dK0, bar_KT):
     from paper_2409_07146_amd.synth import GsaConfig
-    errors = {"dq": [], "dK0": []}
+    errors = {"dq": [], "dK0": [], "KT": []}
     for seed in range(12):
         cfg = GsaConfig("f32", B=2, T=T, H=2, d_k=d_k, d_v=d_v, m=m, dtype="f32", init_state_std=0.1, seed=seed)
         x, got = run_fwd_bwd(cfg)
         a = {n: to_np64(x[n]) for n in ("q", "k", "v", "g", "dO", "K0", "V0")}
         ref = oracle.bwd(a["q"], a["k"], a["v"], a["g"], a["dO"], K0=a["K0"], V0=a["V0"])
+        ref["KT"] = oracle.fwd(a["q"], a["k"], a["v"], a["g"], K0=a["K0"], V0=a["V0"])["KT"]
         for n in errors:
             errors[n].append(rel_l2(to_np64(got[n]), ref[n]))
-    assert np.mean(errors["dq"]) <= bar_dq and np.mean(errors["dK0"]) <= bar_dK0, {n: np.mean(e) for n, e in errors.items()}
+    mean = {n: float(np.mean(e)) for n, e in errors.items()}
+    assert mean["dq"] <= bar_dq and mean["dK0"] <= bar_dK0 and (bar_KT is None or mean["KT"] <= bar_KT), mean
