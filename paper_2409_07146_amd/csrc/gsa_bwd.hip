@@ -199,13 +199,20 @@ template <typename T, int M, bool WIDE> struct IntraLds {
     static constexpr size_t oRb = (WIDE && tiles < Wide<M>::szBuf) ? Wide<M>::szBuf : tiles;
     static constexpr size_t oCarry = oRb + 4 * sizeof(float) * (C / 16) * M;
     static constexpr size_t endR = oCarry + sizeof(float) * M;
+    static constexpr bool kTwo = sizeof(T) == 2 || M < 64;   // registers for two steps at a time (see walk_steps), gates and scores
     // the buffers of the contractions; later Bm, Bm^T, A2^T, scale*dz*exp(G), s*exp(G_C-G)
-    static constexpr size_t oMat = (WIDE && endR < 2 * Wide<M>::szBuf) ? 2 * Wide<M>::szBuf : endR;
+    // fp32 with 128 slots: one buffer, in the place of the tiles (without kTwo they are written when the contractions have ended), so that
+    // two workgroups fit a CU: 8 x 2048 tokens, 4 heads, d = 512 726 -> 574 us, d = 64 225 -> 152.  With 64 slots two fit as
+    // it is, and more make no difference on the whole: d = 128 117 -> 105 us, d = 512 354 -> 362, d = 640 417 -> 440.
+    static constexpr bool kTight = sizeof(T) == 4 && M > 64;
+    static constexpr size_t oMat = kTight ? 0 : (WIDE && endR < 2 * Wide<M>::szBuf) ? 2 * Wide<M>::szBuf : endR;
     static constexpr size_t oK = sizeof(T) * C * StepTile<T>::KS, oE = 2 * oK, szBuf = oE + sizeof(T) * M * StepTile<T>::KS;   // q, k or v, E
     static constexpr size_t szMat = WIDE ? 3 * Wide<M>::szTok + 2 * Wide<M>::szSlot : 0;
     static constexpr size_t oEx = oMat + szMat;   // rows of the outputs on their way out
     static constexpr size_t szAll = szMat + (WIDE ? Wide<M>::szEx : 0);
-    static constexpr size_t bytes = oMat + (szAll > 2 * szBuf ? szAll : 2 * szBuf);
+    static constexpr size_t szC = (kTight ? 1 : 2) * szBuf, endC = oMat + (szAll > szC ? szAll : szC);
+    static constexpr size_t bytes = endC > endR ? endC : endR;
+    static_assert(!(kTight && kTwo) && (sizeof(T) == 2 || 2 * bytes <= 160 * 1024), "two workgroups on a CU");
 };
 
 template <typename T> struct IntraArgs {
@@ -278,7 +285,7 @@ __global__ __launch_bounds__(Geo<T>::NT, (M > 64 ? 1 : 2)) void chunk_intra_kern
     // Non-temporal loads for what is read here for the last time (v, the chunk-end memories, and q where the wide
     // contractions run on their own); k and E are read again, by this kernel or by the apply kernel right after it.
     f32x4 dgl[MI];   // z*dz + p*dp of this lane's token
-    constexpr bool kTwo = sizeof(T) == 2 || M < 64;   // registers for two steps at a time (see walk_steps), gates and scores
+    constexpr bool kTwo = L::kTwo;
     auto gates = [&] {   // the write-intensity tile Vn is for the pair weights of other waves
         bg.template finish<T>(ci.len, rowb, lane);
         bg.template write_tiles<T>(Vn, L::ldn, nullptr, 0, Rb, rowb, lane);

@@ -109,7 +109,7 @@ template <typename T, int ROWS, int NT, bool SNAP, bool HINT> struct StepRows {
 // 8 x 2048 tokens, 4 heads, d = 512, 64 slots 92 us instead of 82).  fetch(u, step): loads of a step into register stage u; put(u,
 // step): stage u, which holds that step, to LDS buffer u; multiply(b): the products of buffer b.  The caller has issued the loads of
 // the first two steps (past the end: of the last one again) and has the buffers free; the walk ends with a barrier.
-// PAIRS = false: one step at a time, stage and buffer 0 only, where two do not fit the registers.
+// PAIRS = false: one step at a time, stage and buffer 0 only, where two do not fit.
 template <bool PAIRS = true, typename Fetch, typename Put, typename Multiply>
 __device__ __forceinline__ void walk_steps(int n, Fetch &&fetch, Put &&put, Multiply &&multiply)
 {
@@ -360,7 +360,11 @@ constexpr int kHintX = 1, kHintY = 2, kHintSt = 4;
 template <typename T, int M, int C, int HINT, int PHI> struct HeadContraction {
     using Tile = StepTile<T>;
     static constexpr int NT = Geo<T>::NT, MI = M / 16, CI = C / 16, NB = CI + MI;
-    static constexpr size_t oY = sizeof(T) * C * Tile::KS, oS = 2 * oY, szBuf = oS + sizeof(T) * M * Tile::KS, kBytes = 2 * szBuf;
+    static constexpr size_t oY = sizeof(T) * C * Tile::KS, oS = 2 * oY, szBuf = oS + sizeof(T) * M * Tile::KS;
+    // Two steps at a time (see walk_steps), one for fp32 with 128 slots: a second buffer leaves one workgroup on a CU
+    // instead of two (8 x 2048 tokens, 4 heads, d = 512 forward 324 us against 205; d = 256, 16384 tokens 206 against 118).
+    static constexpr bool kTwo = sizeof(T) == 2 || M < 128;
+    static constexpr size_t kBytes = (kTwo ? 2 : 1) * szBuf;
     typedef StepRows<T, C, NT, false, (HINT & kHintX) != 0> RX;
     typedef StepRows<T, C, NT, false, (HINT & kHintY) != 0> RY;
     typedef StepRows<T, M, NT, true, (HINT & kHintSt) != 0> RS;
@@ -381,7 +385,7 @@ template <typename T, int M, int C, int HINT, int PHI> struct HeadContraction {
         : rx(X, ldx, len, tid_), ry(Y, ldx, len, tid_), rs(St, 0, 0, tid_), n(d / Tile::KS), tid(tid_)
     {
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
+        for (int u = 0; u < (kTwo ? 2 : 1); ++u) {
             fetch(u, min(u, n - 1));
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -391,7 +395,7 @@ template <typename T, int M, int C, int HINT, int PHI> struct HeadContraction {
     {
         const int r = lane & 15, g4 = (lane >> 4) * 4;
         StepSums<T, NB> sums;
-        walk_steps(
+        walk_steps<kTwo>(
             n, [&](auto u, int step) { fetch(decltype(u)::value, step); },
             [&](auto u, int) {
                 constexpr int U = decltype(u)::value;

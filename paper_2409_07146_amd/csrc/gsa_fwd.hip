@@ -116,6 +116,7 @@ template <typename T, int M, bool WIDE> struct ChunkFwdLds {
     static constexpr size_t end = oEx + (WIDE ? Wide<M>::szEx : 0);
     static constexpr size_t endC = oBuf + HeadContraction<T, M, C, 0, 0>::kBytes;
     static constexpr size_t bytes = end > endC ? end : endC;
+    static_assert(sizeof(T) == 2 || 2 * bytes <= 160 * 1024, "two workgroups on a CU");
 };
 
 // GEN: the general form (write intensities from `sin` when it is not NULL; opts: read-out in the low
