@@ -68,7 +68,7 @@ gsa_status make_plan(const gsa_problem *p, Plan *pl, bool fine_segments = true)
         auto segs = [&](int64_t c) { return (max_nch + c - 1) / c; };
         // In packed form the lengths are the device's to know: the prepare kernel decides by the same rule (scan_unsegmented).
         bool on = base < 512 && base * segs(gsa::kSegChunks) <= 8192 &&
-                  !gsa::scan_unsegmented(max_nch, p->cu_seqlens ? 0 : max_nch * base);
+                  !gsa::scan_unsegmented(p->dtype == GSA_F32, p->m, max_nch, p->cu_seqlens ? 0 : max_nch * base);
         pl->seg_chunks = gsa::kSegChunks;
         pl->fine = false;
         // Batch form (every sequence really is T long): the shortest segments that still leave the chip one

@@ -29,7 +29,7 @@ namespace gsa {
 // ---------------------------------------------------------------------------------------
 // width: workgroups per chunk of an unsegmented scan (0: the scans are not segmented, segbase is not needed).
 __global__ void prepare_kernel(const int32_t *__restrict__ cu, int n_seqs, int T, int kChunk, int chunk_slots,
-                               int seg_chunks, int width, int32_t *__restrict__ table, int32_t *__restrict__ seqtab,
+                               int seg_chunks, int width, bool f32, int m, int32_t *__restrict__ table, int32_t *__restrict__ seqtab,
                                int32_t *__restrict__ segbase)
 {
     __shared__ int total;
@@ -48,7 +48,7 @@ __global__ void prepare_kernel(const int32_t *__restrict__ cu, int n_seqs, int T
             prev_end = e;
         }
         if (width) {   // scan segments (gsa_scan.hip); an empty sequence still has one
-            if (scan_unsegmented(longest, (long long)c0 * width)) seg_chunks = max(longest, 1);   // one per sequence
+            if (scan_unsegmented(f32, m, longest, (long long)c0 * width)) seg_chunks = max(longest, 1);   // one per sequence
             int nsegs = 0;
             for (int s = 0; s < n_seqs; ++s) {
                 segbase[s] = nsegs;
@@ -85,7 +85,8 @@ hipError_t launch_prepare(const Plan &pl, const Work &w, hipStream_t st)
     if (!pl.cu_seqlens) return hipSuccess;
     KernelTimer kt(kSlotPrepare, st);
     hipLaunchKernelGGL(prepare_kernel, dim3(1), dim3(256), 0, st, pl.cu_seqlens, pl.n_seqs, pl.T, pl.chunk,
-                       pl.chunk_slots, pl.seg_chunks, pl.max_seg > 1 ? pl.H * ((pl.d_k + pl.d_v) / 64) : 0, w.table, w.seqtab, w.segbase);
+                       pl.chunk_slots, pl.seg_chunks, pl.max_seg > 1 ? pl.H * ((pl.d_k + pl.d_v) / 64) : 0, pl.dtype == 0, pl.m,
+                       w.table, w.seqtab, w.segbase);
     return hipGetLastError();
 }
 

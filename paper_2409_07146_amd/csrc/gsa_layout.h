@@ -20,15 +20,29 @@ constexpr int kSnapTile = 64;
 constexpr int kSegChunks = 32;
 
 // When a scan walks its sequences whole although they could be cut into segments.  longest: chunks of the longest sequence,
-// steps: chunks times workgroups per chunk (heads and column slices).  In one walk the launch takes 0.62 us a chunk of the
-// longest sequence or 3.2 ns a step, whichever is more; in segments, which read the tokens twice, two chains of kSegChunks
-// chunks with what is around them (53 us), or 5.9 ns a step.  Per scan, 64 slots, 4 heads, d = 512 (in segments / whole): four packed
-// sequences of 8191 to 2046 tokens 97 / 76 us, 4 x 4096 97 / 63, 2 x 8192 97 / 92, one of 4096 45 / 43, one of 5000 49 / 55, one of 16384 97 / 154; d = 128,
-// 12000 + 4000 tokens 59 / 113; d = 256, 6000 tokens and four short ones 50 / 59.
-__host__ __device__ inline bool scan_unsegmented(long long longest, long long steps)
+// steps: chunks times workgroups per chunk (heads and column slices).  In one walk the launch waits for the chain of the
+// longest sequence, or for all steps where they fill the chip; in segments for two chains of kSegChunks chunks and what is
+// around them, or for all steps twice, since the tokens are read twice.  Time of the forward call, whole / in segments, us:
+//   the chain (1 head, d = 64)      56 chunks     66          84
+//     bf16  16 slots                  33 / 38       36 / 38     42 / 38
+//           64                        48 / 54       54 / 55     63 / 55
+//          128                        68 / 71       76 / 73     89 / 74
+//     fp32  16                        44 / 50       49 / 50     57 / 50
+//           64                        82 / 85       92 / 87    110 / 86
+//          128                       132 / 133     153 / 136   188 / 135
+//   all steps (n equal sequences, 4 heads, d = 512, 64 slots; steps per chunk of the longest: 64 n)
+//     bf16  n = 1    72 chunks 87 / 87, 144 151 / 130;  n = 2    72 116 / 146, 256 347 / 366;  n = 4    144 308 / 403
+//     fp32  n = 1    72 chunks 147 / 141, 144 239 / 173;  n = 2    72 177 / 200, 96 218 / 218, 144 333 / 304;  n = 4    144 482 / 569
+// (fp32 with 128 slots as with 64; with 16 and 32 as bf16.)
+__host__ __device__ inline bool scan_unsegmented(bool f32, int m, long long longest, long long steps)
 {
-    const long long wide = steps / 110;
-    return longest <= (wide > 72 ? wide : 72);
+    const int few = f32 ? (m > 16 ? 64 : 68) : m > 64 ? 64 : m > 32 ? 68 : 72;
+    long long wide = steps / 110;
+    if (f32 && m > 32) {
+        wide = wide < 96 ? wide : 96;
+        wide = wide > steps / 160 ? wide : steps / 160;
+    }
+    return longest <= (wide > few ? wide : few);
 }
 
 // The device kernels take the read-out and the feature-map switch in one int: the Readout value in
