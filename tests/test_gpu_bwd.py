@@ -3,7 +3,7 @@ import numpy as np
 import pytest
 import torch
 
-from tests.util import check, suffix_mass, to_np64
+from tests.util import check, kernel_launches, suffix_mass, to_np64
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -211,11 +211,12 @@ def test_fwd_bwd_extreme_scales(oracle, scale, dtype):
 
 @pytest.mark.parametrize("dtype,T", [("bf16", 3400), ("f32", 1700)])
 def test_fwd_bwd_long_sequences_walked_in_segments(oracle, dtype, T):
-    """Sequences of more than 48 chunks are walked by the scans in segments of 32 chunks (two launches);
-    here 54 chunks with a ragged tail, initial memories and final-memory gradients."""
+    """54 chunks with a ragged tail in two sequences of few workgroups, which the scans walk in segments of eight (two launches each);
+    initial memories and final-memory gradients."""
     from paper_2409_07146_amd.synth import GsaConfig
     cfg = GsaConfig("long", B=2, T=T, H=2, d_k=64, d_v=128, m=16, dtype=dtype, init_state_std=0.5, seed=71)
-    x, got = run_fwd_bwd(cfg, scale=1.0, with_state_grads=True)
+    (x, got), launches = kernel_launches(lambda: run_fwd_bwd(cfg, scale=1.0, with_state_grads=True))
+    assert launches["scan_summary_kernel"] == 3   # forward, the backward's recomputation, reverse
     compare_bwd(oracle, cfg, x, got)
     f = oracle.fwd(to_np64(x["q"]), to_np64(x["k"]), to_np64(x["v"]), to_np64(x["g"]), K0=to_np64(x["K0"]),
                    V0=to_np64(x["V0"]))
@@ -224,11 +225,12 @@ def test_fwd_bwd_long_sequences_walked_in_segments(oracle, dtype, T):
 
 
 def test_fwd_bwd_packed_long_and_short_sequences(oracle):
-    """Packed: a sequence of 40 chunks (two segments), a short one, an empty one and one of 24 chunks."""
+    """Packed: a sequence of 74 chunks (three segments), a short one, an empty one and one of 24 chunks."""
     from paper_2409_07146_amd.synth import GsaConfig
-    cfg = GsaConfig("longpacked", B=1, T=4150, H=2, d_k=64, d_v=64, m=32, dtype="bf16", init_state_std=0.5,
-                    cu_seqlens=(0, 2530, 2630, 2630, 4150), seed=72)
-    x, got = run_fwd_bwd(cfg, with_state_grads=True)
+    cfg = GsaConfig("longpacked", B=1, T=6320, H=2, d_k=64, d_v=64, m=32, dtype="bf16", init_state_std=0.5,
+                    cu_seqlens=(0, 4700, 4800, 4800, 6320), seed=72)
+    (x, got), launches = kernel_launches(lambda: run_fwd_bwd(cfg, with_state_grads=True))
+    assert launches["scan_summary_kernel"] == 3
     compare_bwd(oracle, cfg, x, got)
 
 

@@ -3,7 +3,7 @@ what it decided, and every sequence against a call of its own."""
 import pytest
 import torch
 
-from tests.util import rel_l2, to_np64
+from tests.util import kernel_launches, rel_l2, to_np64
 
 pytestmark = pytest.mark.gpu
 
@@ -53,12 +53,8 @@ def test_packed_against_single_sequences(case):
         ends.append(ends[-1] + n)
     cu = torch.tensor(ends, dtype=torch.int32, device=dev)
     ws = gsa.alloc_workspace(gsa.make_problem(q, v, g, 1.0, cu), False, dev).fill_(255)
-    gsa.gsa_profile_enable(True)
-    gsa.gsa_profile_reset()
-    o, z, KT, VT = gsa.gsa_fwd(q, k, v, g, K0=K0, V0=V0, cu_seqlens=cu, final_state=True, workspace=ws)
-    launches = gsa.gsa_profile_read()
-    gsa.gsa_profile_enable(False)
-    assert launches["scan_summary_kernel"][1] == (decided is not None)
+    (o, z, KT, VT), launches = kernel_launches(lambda: gsa.gsa_fwd(q, k, v, g, K0=K0, V0=V0, cu_seqlens=cu, final_state=True, workspace=ws))
+    assert launches["scan_summary_kernel"] == (decided is not None)
     assert _decision(ws, T, len(lens), C) == (decided or (-1, -1))
     grads = gsa.gsa_bwd(q, k, v, g, z, dO, K0=K0, V0=V0, cu_seqlens=cu, initial_state_grad=True)
     for i, n in enumerate(lens):

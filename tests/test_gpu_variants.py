@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 import torch
 
-from tests.util import check, suffix_mass, to_np64
+from tests.util import check, kernel_launches, suffix_mass, to_np64
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -281,7 +281,7 @@ def test_feature_map_applied_inside(oracle, readout, given, dtype):
 @pytest.mark.parametrize("m", [32, 128])
 def test_feature_map_other_slot_counts_packed(oracle, m):
     """ragged packed sequences (one of them long enough for the segmented scans), m = 32 and 128"""
-    lens = [70, 1, 64 * 50 + 5, 129]
+    lens = [70, 1, 64 * 76 + 5, 129]
     cu = np.concatenate([[0], np.cumsum(lens)]).tolist()
     cfg, x = _inputs(1, cu[-1], 2, 64, 128, m, "bf16", seed=83, given=False)
     x["K0"] = x["K0"][:1].repeat(len(lens), 1, 1, 1) * 0.2
@@ -289,7 +289,8 @@ def test_feature_map_other_slot_counts_packed(oracle, m):
     gs = torch.Generator().manual_seed(84)
     x["dKT"] = torch.randn(x["K0"].shape, generator=gs) * 0.1
     x["dVT"] = torch.randn(x["V0"].shape, generator=gs) * 0.1
-    _feature_map_case(oracle, cfg, x, cu=cu)
+    _, launches = kernel_launches(lambda: _feature_map_case(oracle, cfg, x, cu=cu))
+    assert launches["scan_summary_kernel"] == 3
 
 
 def test_feature_map_at_the_layer_shape(oracle):

@@ -3,6 +3,18 @@ import numpy as np
 import torch
 
 
+def kernel_launches(fn):
+    """fn's result and {kernel name: launches} of the calls it makes."""
+    import paper_2409_07146_amd as gsa
+    gsa.gsa_profile_enable(True)
+    gsa.gsa_profile_reset()
+    try:
+        res = fn()
+        return res, {name: n for name, (_, n) in gsa.gsa_profile_read().items()}
+    finally:
+        gsa.gsa_profile_enable(False)
+
+
 def rel_l2(x, ref):
     x = np.asarray(x, dtype=np.float64)
     ref = np.asarray(ref, dtype=np.float64)
