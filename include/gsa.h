@@ -30,6 +30,9 @@
  *   - Supported shapes: m in {16, 32, 64, 128}; d_k and d_v
  *     multiples of 64, at most 1024; H, B >= 1; T >= 0 (T = 0 does nothing).  Anything
  *     else returns GSA_ERR_UNSUPPORTED.
+ *   - Sizes: B*T*H*max(d_k,d_v) below 2^40, and min(T-1, 7) rows of a token tensor
+ *     (H*max(d_k,d_v) elements each) below 4 GiB; beyond, gsa_fwd* and gsa_bwd* return
+ *     GSA_ERR_SHAPE.
  */
 #ifndef GSA_H
 #define GSA_H

@@ -4,6 +4,8 @@
 #include "gsa_common.h"
 #include "gsa_internal.h"
 
+#include <algorithm>
+
 namespace {
 
 using gsa::Plan;
@@ -32,7 +34,9 @@ gsa_status make_plan(const gsa_problem *p, Plan *pl, bool fine_segments = true)
     if (p->d_k % 64 || p->d_v % 64 || p->d_k > 1024 || p->d_v > 1024) return GSA_ERR_UNSUPPORTED;
     if (!valid_m(p->m, true)) return GSA_ERR_UNSUPPORTED;
     const int64_t tokens = (int64_t)p->B * p->T;
-    if (tokens * p->H * (int64_t)(p->d_k > p->d_v ? p->d_k : p->d_v) >= ((int64_t)1 << 40)) return GSA_ERR_SHAPE;
+    const int64_t row = (int64_t)p->H * (p->d_k > p->d_v ? p->d_k : p->d_v);   // elements
+    if (tokens * row >= ((int64_t)1 << 40)) return GSA_ERR_SHAPE;
+    if (std::min(p->T - 1, gsa::kLaneRows - 1) * row * (p->dtype == GSA_BF16 ? 2 : 4) + 128 > (int64_t)UINT32_MAX) return GSA_ERR_SHAPE;
     pl->B = p->B; pl->T = p->T; pl->H = p->H; pl->d_k = p->d_k; pl->d_v = p->d_v; pl->m = p->m;
     pl->dtype = p->dtype; pl->scale = p->scale; pl->cu_seqlens = p->cu_seqlens;
     pl->n_seqs = p->cu_seqlens ? p->n_seqs : p->B;

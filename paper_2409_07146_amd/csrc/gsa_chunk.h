@@ -65,14 +65,15 @@ template <typename T, int ROWS, int NT, bool SNAP, bool HINT> struct StepRows {
     typedef typename Tile::Piece Piece;
     static constexpr int N = ROWS * Tile::PR, V = (N + NT - 1) / NT;   // pieces, pieces per thread
     struct Stage { Piece x[V]; };
-    const char *base[V];   // uniform: the first row of a thread's piece v; its lanes are within 32 rows of it, which 32 bits of bytes
-    uint32_t off[V];       // always hold (65535 heads of 1024 columns)
+    const char *base[V];   // uniform over the wave: the first row of its piece v
+    uint32_t off[V];       // bytes from there; kLaneRows, which the host checks
     __device__ __forceinline__ StepRows(const T *p, size_t ld, int len, int tid)
     {
 #pragma unroll
         for (int v = 0; v < V; ++v) {
             const int idx = min(tid + v * NT, N - 1), row = idx / Tile::PR;
-            const int row0 = SNAP ? 0 : min(v * (NT / Tile::PR), len - 1);
+            const int row0 = SNAP ? 0 : min(v * (NT / Tile::PR) + __builtin_amdgcn_readfirstlane(tid >> 6) * (kWave / Tile::PR), len - 1);
+            static_assert(kWave / Tile::PR <= kLaneRows, "rows of a wave");
             base[v] = reinterpret_cast<const char *>(p) + (size_t)row0 * ld * sizeof(T);
             off[v] = SNAP ? (uint32_t)(row * kSnapTile * (int)sizeof(T) + (idx % Tile::PR) * 16)
                           : (uint32_t)(min(row, len - 1) - row0) * (uint32_t)(ld * sizeof(T)) + (idx % Tile::PR) * 16;

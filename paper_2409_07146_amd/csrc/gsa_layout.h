@@ -16,6 +16,10 @@ namespace gsa {
 // slice it needs on its way into LDS.  Offsets are in elements from the start of the record.
 constexpr int kSnapTile = 64;
 
+// The lanes of a wave load up to this many consecutive rows of a token tensor (a row: all heads of a token) at 32-bit byte offsets
+// from the first.  The host refuses rows so long that they would wrap (H * d from 153 million in fp32, 306 million in bf16).
+constexpr int kLaneRows = 8;
+
 // Chunks per segment when the scans cut long sequences into segments.
 constexpr int kSegChunks = 32;
 

@@ -316,7 +316,7 @@ __global__ __launch_bounds__((ScanGeo<T, M>::NT), 2) void scan_kernel(ChunkMap c
         Piece x[XV];
         int len;
     };
-        // Bases are uniform and advance from chunk to chunk, lanes add 32-bit byte offsets.  Positions past the end of the walk
+    // Bases are uniform and advance from chunk to chunk, lanes add 32-bit byte offsets.  Positions past the end of the walk
     // repeat the last chunk, so that refills can be issued unconditionally (a refill under a branch makes the number of
     // loads in flight unknown to the compiler, which then waits for all of them wherever it needs one).
     const int n0 = first + (REVERSE ? nch - 1 : 0);   // first chunk of the walk
@@ -350,7 +350,8 @@ __global__ __launch_bounds__((ScanGeo<T, M>::NT), 2) void scan_kernel(ChunkMap c
         st.len = min(C, ntok - xn * C);
 #pragma unroll
         for (int v = 0; v < XV; ++v) {
-            const int row0 = min(v * (NT / PR), st.len - 1);   // uniform: 32 bits hold the bytes of the lanes' rows from there
+            const int row0 = min(v * (NT / PR) + wave * (kWave / PR), st.len - 1);   // uniform over the wave
+            static_assert(kWave / PR <= kLaneRows, "rows of a wave");
             const uint32_t row = min(tid / PR + v * (NT / PR), st.len - 1) - row0;
             st.x[v] = __builtin_nontemporal_load(reinterpret_cast<const Piece *>(xp + (size_t)row0 * xstep + (row * xstep + xcol)));
         }

@@ -60,6 +60,8 @@ def test_workspace_plan(lib):
     (dict(B=0), 2), (dict(H=0), 2), (dict(T=-1), 2), (dict(dtype=7), 2), (dict(scale=float("nan")), 2),
     (dict(B=2, cu_seqlens=0x1000, n_seqs=2), 2), (dict(B=1, cu_seqlens=0x1000, n_seqs=0), 2),
     (dict(d_k=48), 3), (dict(d_v=2048), 3), (dict(m=24), 3), (dict(m=256), 3),
+    # seven rows of a token tensor: 32-bit byte offsets
+    (dict(B=1, T=64, H=150000, d_k=1024, dtype=0), 2), (dict(B=1, T=64, H=300000, d_v=1024), 2), (dict(B=1, T=2, H=1 << 20, d_k=1024, dtype=0), 2),
 ])
 def test_bad_problem_is_rejected(lib, kw, code):
     n = ctypes.c_size_t(0)
@@ -67,6 +69,13 @@ def test_bad_problem_is_rejected(lib, kw, code):
     assert lib.gsa_workspace_bytes(ctypes.byref(p), 0, ctypes.byref(n)) == code
     null = ctypes.c_void_p(None)
     assert lib.gsa_fwd(ctypes.byref(p), *([null] * 10), null, 0, null) == code
+
+
+@pytest.mark.parametrize("kw", [dict(B=1, T=64, H=149000, d_k=1024, dtype=0), dict(B=1, T=64, H=299000, d_v=1024),
+                                dict(B=1, T=2, H=(1 << 20) - 1, d_k=1024, dtype=0), dict(B=1, T=1, H=1 << 20, d_k=1024, dtype=0)])
+def test_long_rows_are_taken(lib, kw):
+    n = ctypes.c_size_t(0)
+    assert lib.gsa_workspace_bytes(ctypes.byref(_problem(**kw)), 0, ctypes.byref(n)) == 0
 
 
 def test_null_and_workspace_errors_without_device(lib):
