@@ -1,15 +1,32 @@
 """ctypes loader for libgsa.so.  There is no fallback: a missing library is an error."""
 import ctypes
 import os
+import re
+import sys
+import warnings
+
+import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libgsa.so")
 
-# the native part of the binding (csrc/gsa_binding.cpp); without it api.py marshals every call itself
-if os.path.exists(os.path.join(_HERE, "_binding.so")):
-    from . import _binding as native
-else:
-    native = None
+
+def _load_native():
+    """The native part of the binding (csrc/gsa_binding.cpp), or None: then api.py marshals every call itself."""
+    if not os.path.exists(os.path.join(_HERE, "_binding.so")):
+        return None
+    try:
+        from . import _binding
+        have = (re.match(r"[\d.]*\d", torch.__version__).group(), "%d.%d" % sys.version_info[:2])
+        if _binding.built_for != have:
+            raise ImportError("built for torch and Python %s, not %s" % (_binding.built_for, have))
+        return _binding
+    except (ImportError, AttributeError, SystemError) as e:
+        warnings.warn("paper_2409_07146_amd: the native part of the binding is left out (%s); build again" % e)
+        return None
+
+
+native = _load_native()
 
 # every symbol include/gsa.h declares
 EXPORTS = ("gsa_status_string", "gsa_abi_version", "gsa_workspace_bytes", "gsa_fwd", "gsa_bwd", "gsa_fwd_ex", "gsa_bwd_ex",

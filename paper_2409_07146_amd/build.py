@@ -60,9 +60,14 @@ def build(jobs: int = 4) -> str:
     with ThreadPoolExecutor(max_workers=jobs) as ex:
         binding = ex.submit(_compile_binding)
         objs = list(ex.map(_compile, SOURCES))
-        binding.result()
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs
     subprocess.run(cmd, check=True)
+    try:
+        binding.result()
+    except Exception as e:   # no g++, no headers: api.py does without
+        if os.path.exists(BINDING):
+            os.remove(BINDING)   # an older one might not fit the library
+        sys.stderr.write("the native part of the binding is left out: %s\n" % e)
     return LIB
 
 

@@ -13,8 +13,12 @@
 #include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/version.h>
 
 #include <algorithm>
+
+#define GSA_STR2(x) #x
+#define GSA_STR(x) GSA_STR2(x)
 
 namespace {
 
@@ -110,4 +114,15 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_binding", nullptr, -1, methods, n
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__binding(void) { return PyModule_Create(&module); }
+// built_for: the versions of torch and Python whose headers this was compiled against; the loader compares them with its own.
+PyMODINIT_FUNC PyInit__binding(void)
+{
+    PyObject *m = PyModule_Create(&module);
+    PyObject *built = m ? Py_BuildValue("(ss)", TORCH_VERSION, GSA_STR(PY_MAJOR_VERSION) "." GSA_STR(PY_MINOR_VERSION)) : nullptr;
+    if (!built || PyModule_AddObject(m, "built_for", built) < 0) {   // takes the reference when it succeeds
+        Py_XDECREF(built);
+        Py_XDECREF(m);
+        return nullptr;
+    }
+    return m;
+}

@@ -1,4 +1,10 @@
 """The native part of the decode step's binding against the general one in api.py, over what the entry point takes."""
+import os
+import shutil
+import subprocess
+import sys
+from types import SimpleNamespace
+
 import pytest
 import torch
 
@@ -39,6 +45,53 @@ def test_native_part_is_built_and_leaves_other_cases_alone():
     assert _lib.native.decode_step(1, None, None, *list(x.values())[1:], *rest) is None
     with pytest.raises(TypeError):
         _lib.native.decode_step(1, None)
+
+
+def test_package_imports_with_a_native_part_that_does_not(tmp_path):
+    """A file that is no module, as one built against another torch or Python would be."""
+    from paper_2409_07146_amd import _lib
+    here = os.path.dirname(_lib.__file__)
+    pkg = tmp_path / "paper_2409_07146_amd"
+    pkg.mkdir()
+    for name in os.listdir(here):
+        if name.endswith(".py"):
+            shutil.copy(os.path.join(here, name), pkg)
+    (pkg / "_binding.so").write_bytes(b"not a shared object")
+    code = "import paper_2409_07146_amd as g; from paper_2409_07146_amd import _lib, api; assert _lib.native is None and api._native_decode is None; print(g.__file__)"
+    res = subprocess.run([sys.executable, "-c", code], cwd=tmp_path, env=dict(os.environ, PYTHONPATH=str(tmp_path)), capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr
+    assert str(tmp_path) in res.stdout and "native part of the binding is left out" in res.stderr
+
+
+def test_native_part_of_another_version_is_left_out(monkeypatch):
+    import paper_2409_07146_amd
+    from paper_2409_07146_amd import _lib
+    here = (torch.__version__.split("+")[0], "%d.%d" % sys.version_info[:2])
+    assert _lib.native.built_for == here
+    for other in (SimpleNamespace(built_for=("1.0.0", here[1])), SimpleNamespace(built_for=(here[0], "2.7")), SimpleNamespace()):
+        monkeypatch.setitem(sys.modules, "paper_2409_07146_amd._binding", other)
+        monkeypatch.setattr(paper_2409_07146_amd, "_binding", other)
+        with pytest.warns(UserWarning, match="left out"):
+            assert _lib._load_native() is None
+
+
+@pytest.mark.parametrize("error", [FileNotFoundError("g++"), RuntimeError("no headers")])
+def test_library_is_linked_without_the_native_part(monkeypatch, tmp_path, capsys, error):
+    from paper_2409_07146_amd import build
+
+    def fail():
+        raise error
+    linked = []
+    (tmp_path / "_binding.so").write_bytes(b"older")
+    monkeypatch.setattr(build, "BINDING", str(tmp_path / "_binding.so"))
+    monkeypatch.setattr(build, "OBJ", str(tmp_path))
+    monkeypatch.setattr(build, "LIB", str(tmp_path / "libgsa.so"))
+    monkeypatch.setattr(build, "_compile", lambda src: src)
+    monkeypatch.setattr(build, "_compile_binding", fail)
+    monkeypatch.setattr(build.subprocess, "run", lambda cmd, **kw: linked.append(cmd))
+    assert build.build() == str(tmp_path / "libgsa.so")
+    assert len(linked) == 1 and "-shared" in linked[0] and not (tmp_path / "_binding.so").exists()
+    assert "left out" in capsys.readouterr().err
 
 
 @pytest.mark.gpu
