@@ -47,6 +47,7 @@ bool modes_in_force()
 {
     return at::impl::torch_function_mode_enabled() || c10::impl::TorchDispatchModeTLS::any_modes_set() ||
            c10::impl::tls_is_dispatch_key_included(c10::DispatchKey::FuncTorchDynamicLayerFrontMode) ||
+           c10::impl::tls_is_dispatch_key_included(c10::DispatchKey::Tracer) ||
            c10::impl::tls_is_dispatch_key_included(c10::DispatchKey::Functionalize);
 }
 

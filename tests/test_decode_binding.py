@@ -121,6 +121,17 @@ def test_same_results(monkeypatch, dtype, opts):
 
 
 @pytest.mark.gpu
+def test_traced_calls_take_the_general_way(monkeypatch):
+    from paper_2409_07146_amd import api
+    x, taken = _args(torch.float32, "cuda"), []
+    native = api._native_decode
+    monkeypatch.setattr(api, "_native_decode", lambda *a: taken.append(native(*a)) or taken[-1])
+    rest = {n: a for n, a in x.items() if n != "q"}
+    traced = torch.jit.trace(lambda q: api.gsa_decode_step(q, **rest), x["q"], check_trace=False)
+    assert taken == [None] and "aten::empty_like" in str(traced.graph)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("change", ["strided", "dtype", "shape", "cpu", "readout", "small_ws", "ws_dtype", "mode", "half", "tau"])
 def test_same_treatment_of_the_rest(monkeypatch, change):
     from torch.overrides import TorchFunctionMode
