@@ -27,8 +27,10 @@ def _both(monkeypatch, x, **kw):
         if not native:
             monkeypatch.setattr(api, "_native_decode", None)
         y = {n: (a.clone() if isinstance(a, torch.Tensor) and n.endswith("state") else a) for n, a in x.items()}
+        own = dict(kw, out=torch.full_like(kw["out"], float("nan"))) if "out" in kw else kw
         try:
-            o = api.gsa_decode_step(**y, **kw)
+            o = api.gsa_decode_step(**y, **own)
+            assert "out" not in own or o is own["out"]
             out.append((o, y["K_state"], y["V_state"]))
         except Exception as e:
             out.append(e)
@@ -117,6 +119,7 @@ def test_same_results(monkeypatch, dtype, opts):
         assert o is kw["out"]
     monkeypatch.undo()
     a, b = _both(monkeypatch, x, **kw)
+    assert a[0] is not b[0] and not a[0].isnan().any()
     assert all(torch.equal(s, t) for s, t in zip(a, b))
 
 
