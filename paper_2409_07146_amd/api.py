@@ -229,7 +229,8 @@ def gsa_decode_step(q, k, v, g, K_state, V_state, scale=1.0, out=None, workspace
         res = _native_decode(_lib.load().decode_entry, _raw_stream, q, k, v, g, K_state, V_state, scale, out, workspace, s,
                              READOUTS[readout], gate_tau, FEATURE_MAPS[feature_map])
         if type(res) is int:
-            raise GsaError(res, "gsa_decode_step")
+            ex = s is not None or readout != "softmax" or gate_tau or feature_map != "none"
+            raise GsaError(res, "gsa_decode_step_ex" if ex else "gsa_decode_step_ws" if workspace is not None else "gsa_decode_step")
         if res is not None:
             return res
     # anything but the plain case: looked at here, argument by argument
