@@ -693,7 +693,7 @@ static hipError_t launch_bwd_tm(const Plan &pl, const Work &w, const void *q, co
     // pairs are left to fill the chip.  Time of the backward call with them inside over that without, 64 slots: d = 512 (24
     // units) 1.18 at 8 pairs, 1.08 at 64, 1.02 at 96, 0.94 at 256, 0.92 from 1024 on; d = 1024 (48 units) 1.30, 1.13, 1.08,
     // 0.98, 0.96; d = 128 (6 units) 0.97, 0.95, 0.96, 0.92, 0.90.  With 128 slots 1 to 4 per cent lower throughout (one
-    // workgroup per CU holds the 127 KB, the kernel it replaces reads everything again); with 16 and 32 slots the same up to
+    // workgroup per CU holds the 125.5 KB, the kernel it replaces reads everything again); with 16 and 32 slots the same up to
     // d = 512 and 0.96 to 1.04 above.
     const int64_t pairs = (int64_t)pl.chunk_slots * pl.H;
     const bool wide = sizeof(T) == 2 && !pl.phi && pairs >= 4 * (2 * pl.d_k + pl.d_v) / 64;

@@ -3,9 +3,11 @@
 // Everything here is written in terms of one matrix-core atom: a 16x16 fp32
 // accumulator tile updated with a depth-32 contraction.  For bf16 operands that
 // is one v_mfma_f32_16x16x32_bf16; for fp32 operands it is eight
-// v_mfma_f32_16x16x4_f32.  Both read their operands as "8 consecutive k per
-// lane" fragments from LDS tiles stored contraction-index-fastest, so every
-// kernel is written once and instantiated for both element types.
+// v_mfma_f32_16x16x4_f32.  Both take their operands as fragments of 8 consecutive
+// k per lane, so every kernel is written once and instantiated for both element
+// types.  Where the contraction index runs fastest a fragment is read as it lies (LDS tiles,
+// or memory in fragment order); bf16 tiles that lie the other way go through
+// the transposing LDS load (TrTile).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -43,7 +45,6 @@ template <> struct Atom<bf16_t> {
     typedef bf16x8 Frag;
     static constexpr int kPad = 8;  // elements of padding that keep rows 16-byte aligned
     __device__ static __forceinline__ Frag load(const bf16_t *p) { return *reinterpret_cast<const Frag *>(p); }
-    __device__ static __forceinline__ Frag load_nt(const bf16_t *p) { return __builtin_nontemporal_load(reinterpret_cast<const Frag *>(p)); }
     __device__ static __forceinline__ Frag zero() { Frag f; for (int e = 0; e < 8; ++e) f[e] = (bf16_t)0.f; return f; }
     __device__ static __forceinline__ void mma(f32x4 &c, const Frag &a, const Frag &b) {
         c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
@@ -63,14 +64,6 @@ template <> struct Atom<float> {
     __device__ static __forceinline__ Frag load(const float *p) {
         const f32x4 lo = *reinterpret_cast<const f32x4 *>(p);
         const f32x4 hi = *reinterpret_cast<const f32x4 *>(p + 4);
-        Frag f;
-        f[0] = lo[0]; f[1] = lo[1]; f[2] = lo[2]; f[3] = lo[3];
-        f[4] = hi[0]; f[5] = hi[1]; f[6] = hi[2]; f[7] = hi[3];
-        return f;
-    }
-    __device__ static __forceinline__ Frag load_nt(const float *p) {
-        const f32x4 lo = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(p));
-        const f32x4 hi = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(p + 4));
         Frag f;
         f[0] = lo[0]; f[1] = lo[1]; f[2] = lo[2]; f[3] = lo[3];
         f[4] = hi[0]; f[5] = hi[1]; f[6] = hi[2]; f[7] = hi[3];
@@ -136,12 +129,12 @@ template <> __device__ __forceinline__ void store8<float>(float *dst, const floa
     *reinterpret_cast<f32x4 *>(dst + 4) = f32x4{v[4], v[5], v[6], v[7]};
 }
 
-// Non-temporal forms (load_nt / store_nt below and on the atom): for data a kernel touches once and
+// Non-temporal forms (load_nt / store_nt below, the builtins elsewhere): for data a kernel touches once and
 // nobody reads again soon.  Such traffic then streams through the caches instead of displacing lines
-// that the co-resident workgroups or the next kernel still want.  Which accesses carry the hint was
-// decided by measurement, access by access: the decode memories, the apply kernel's wide operands and
-// outputs and the scans' token tiles gain; the chunk kernels' operands and the scans' snapshot stores
-// (read back by the next kernel) lose.
+// that the co-resident workgroups or the next kernel still want.  They are on the decode memories, the apply
+// kernel's wide operands and outputs, the scans' token tiles, the outputs of the wide contractions, and those
+// operands of the chunk kernels that nobody reads again (said where they are loaded); not on the scans'
+// snapshots, which the next kernel reads.
 // Eight elements held as loaded (no conversion): the unit of register prefetching.
 template <typename T> struct Raw8;
 template <> struct Raw8<bf16_t> {
@@ -358,11 +351,6 @@ __device__ __forceinline__ float swish_slope(float x)
 {
     const float sg = __builtin_amdgcn_rcpf(1.f + __expf(-x));
     return sg * (1.f + x * (1.f - sg));
-}
-template <typename T> __device__ __forceinline__ void swish_frag(typename Atom<T>::Frag &f)
-{
-#pragma unroll
-    for (int e = 0; e < 8; ++e) f[e] = from_f32<T>(swish_value((float)f[e]));
 }
 
 // Loads in this library are never placed under a data-dependent branch (the compiler would have to wait for
